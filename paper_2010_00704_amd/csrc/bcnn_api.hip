@@ -3,6 +3,7 @@
 // synchronisation, no state.
 #include "bcnn.h"
 #include "bcnn_common.h"
+#include "conv_mfma_direct.h"
 
 #include <limits.h>
 
@@ -56,16 +57,22 @@ int conv_entry(const bcnn_conv_desc* desc, const uint32_t* x, const uint32_t* w,
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     switch (variant) {
-        case BCNN_VARIANT_AUTO:
-            // Measured over a grid of shapes (1x1 and 3x3, 128..1024 input and
-            // 32..512 output channels, 49..200 000 pixels): wherever the matrix-core
-            // kernel covers a shape it is faster than the vector-ALU kernel or within
-            // half a microsecond of it, tiny problems included.
-            if (conv_mfma_fp4_supported(s, x, w))
+        case BCNN_VARIANT_AUTO: {
+            // Two matrix-core kernels: the staged one for launches that fill the chip (C_in a multiple of
+            // 128), the direct one for small launches and every other channel count; conv_mfma_direct.hip
+            // weighs them by fitted times.  One of them is faster than the vector-ALU kernels at every size
+            // measured (7 to 1024 input channels, 25 to 430 000 pixels); those take what is left, tensors
+            // beyond 31-bit offsets and sums beyond fp32.
+            const bool staged = conv_mfma_fp4_supported(s, x, w);
+            const int tile = conv_mfma_direct_supported(s) ? conv_mfma_direct_choose(s, false, staged) : DIRECT_NONE;
+            if (tile != DIRECT_NONE)
+                e = launch_conv_mfma_direct(s, x, w, fused ? thr : nullptr, out, nullptr, tile, st);
+            else if (staged)
                 e = launch_conv_mfma_fp4(s, x, w, fused ? thr : nullptr, out, nullptr, 0, st);
             else
                 e = launch_conv_valu(s, x, w, fused ? thr : nullptr, out, nullptr, st);
             break;
+        }
         case BCNN_VARIANT_VALU:
             e = launch_conv_valu(s, x, w, fused ? thr : nullptr, out, nullptr, st);
             break;
@@ -334,19 +341,25 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     hipError_t e;
     const bool mfma_ok = bcnn::conv_mfma_fp4_supported(s, x_packed, w_packed);
-    const int kwords = s.ks * s.ks * s.cw;      // packed words per output element
     switch (variant) {
-        case BCNN_VARIANT_AUTO:
-            // The module epilogue makes the matrix-core kernel's fixed cost about 10 us
-            // against 7 us on the vector ALUs, whose time grows with the words per output
-            // (taps x C_in / 32): measured on 1x1 and 3x3 modules, the matrix cores win at
-            // every size from 16 words on, and below that from about 3e7 output elements x
-            // words on.
-            if (mfma_ok && (kwords >= 16 || (double)s.m * s.c_out * kwords >= 3.0e7))
+        case BCNN_VARIANT_AUTO: {
+            // The staged kernel is weighed in its plain form only (whole 128-channel tiles, every part of the
+            // module present); its general form is behind the direct kernel at every size measured.  1x1
+            // modules of one or two words per pixel are bound by their real-valued epilogue, which is
+            // shorter in the vector-ALU kernel: 64 channels, 112 x 112 map, 32 images, half: 30.4 us against
+            // 35.7; from about 4e6 elements on it is ahead.
+            const bool plain = mfma_ok && s.c_out % 128 == 0 && m.identity && m.r && m.x_next && m.id_channels % 4 == 0;
+            const bool few_words = s.ks == 1 && s.cw <= 2 && (int64_t)s.m * s.c_out >= 4000000;
+            const int tile = !few_words && bcnn::conv_mfma_direct_supported(s)
+                                 ? bcnn::conv_mfma_direct_choose(s, true, plain) : bcnn::DIRECT_NONE;
+            if (tile != bcnn::DIRECT_NONE)
+                e = bcnn::launch_conv_mfma_direct(s, x_packed, w_packed, nullptr, nullptr, &m, tile, st);
+            else if (mfma_ok && !few_words)
                 e = bcnn::launch_conv_mfma_fp4(s, x_packed, w_packed, nullptr, nullptr, &m, 0, st);
             else
                 e = bcnn::launch_conv_valu(s, x_packed, w_packed, nullptr, nullptr, &m, st);
             break;
+        }
         case BCNN_VARIANT_VALU:
             e = bcnn::launch_conv_valu(s, x_packed, w_packed, nullptr, nullptr, &m, st);
             break;

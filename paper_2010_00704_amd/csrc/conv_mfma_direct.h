@@ -1,0 +1,19 @@
+// The matrix-core convolution without LDS staging (kernel and launcher: conv_mfma_direct.hip).
+#pragma once
+#include "bcnn_common.h"
+
+namespace bcnn {
+
+// Tiles: 32-channel x 32-pixel blocks of a wave; _K4: four waves split K, otherwise four waves side by side
+// along the pixels.
+enum { DIRECT_NONE = 0, DIRECT_1x1_K4, DIRECT_2x2_K4, DIRECT_2x1, DIRECT_1x1 };
+
+bool conv_mfma_direct_supported(const ConvShape& s);
+// The tile with the least estimated time; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the call)
+// and that kernel is estimated to be faster.
+int conv_mfma_direct_choose(const ConvShape& s, bool module, bool staged);
+// thr == nullptr: int32 sums, else packed bits; ep != nullptr: module epilogue (thr and out are ignored)
+hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
+                                   const ModuleEp* ep, int tile, hipStream_t stream);
+
+}  // namespace bcnn
