@@ -222,19 +222,20 @@ static int branches_entry(const bcnn_conv_desc* desc, int32_t branches, const ui
     a.zero_pad = pad_mode == BCNN_PAD_ZERO;
     a.scale = scale; a.bias = bias; a.out = out; a.fused = fused; a.tail = tail;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const bool mfma_ok = bcnn::conv_branches_mfma_supported(s, a);
     hipError_t e;
     switch (variant) {
         case BCNN_VARIANT_AUTO:
-            // measured: the matrix-core kernel wins at every size it covers
-            if (mfma_ok) e = bcnn::launch_conv_branches_mfma(s, a, st);
+            // measured over 74 calls (32 to 1024 channels, 49 to 50 000 pixels, both filters, every pad mode and
+            // output): the direct kernel is ahead of the vector ALUs everywhere (1.0 to 6 times) and of the
+            // staged kernel everywhere but one call in 74 (5 % there); others have too many branches or bytes for it
+            if (bcnn::conv_branches_direct_supported(s, a)) e = bcnn::launch_conv_branches_direct(s, a, bcnn::conv_branches_direct_choose(s, a), st);
             else e = bcnn::launch_conv_branches(s, a, st);
             break;
         case BCNN_VARIANT_VALU:
             e = bcnn::launch_conv_branches(s, a, st);
             break;
-        case BCNN_VARIANT_MFMA_FP4:
-            if (!mfma_ok) return BCNN_ERR_UNSUPPORTED;
+        case BCNN_VARIANT_MFMA_FP4:      // the staged kernel in branch mode: a measurement arm, behind the direct one everywhere
+            if (!bcnn::conv_branches_mfma_supported(s, a)) return BCNN_ERR_UNSUPPORTED;
             e = bcnn::launch_conv_branches_mfma(s, a, st);
             break;
         default:

@@ -1,0 +1,104 @@
+// Branch mode of the matrix-core convolution without LDS staging (kernel: conv_mfma_direct_kernel.h).
+#include "conv_mfma_direct.h"
+#include "conv_mfma_direct_kernel.h"
+
+namespace bcnn {
+namespace {
+
+template <int CB, int PB, int WC, int WP, int OUT>
+hipError_t launch_pad(DirectArgs a, const BranchArgs& b, const DirectBranch& br, hipStream_t stream)
+{
+    a.n_ctiles = (a.s.c_out + 32 * CB * WC - 1) / (32 * CB * WC);
+    a.n_ptiles = (a.s.m + 32 * PB * WP - 1) / (32 * PB * WP);
+    a.div_ct = DivBy::make(a.n_ctiles);
+    const dim3 blocks((unsigned)(a.n_ptiles * a.n_ctiles)), threads(64 * WC * WP);
+    const ModuleEp ep = b.tail ? *b.tail : ModuleEp{};
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a, b.x, b.w, (const int32_t*)nullptr, b.out, ep, br);
+    };
+    if (b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, WC, WP, 1, OUT, BRANCH + PAD_NOTHING>);
+    else if (b.pad_words) go(conv_mfma_direct_kernel<CB, PB, WC, WP, 1, OUT, BRANCH + PAD_OPERAND>);
+    else go(conv_mfma_direct_kernel<CB, PB, WC, WP, 1, OUT, BRANCH + PAD_NONE>);
+    return hipGetLastError();
+}
+
+template <int CB, int PB, int WC, int WP>
+hipError_t launch_out(const DirectArgs& a, const BranchArgs& b, const DirectBranch& br, hipStream_t stream)
+{
+    if (b.tail && b.tail->half) return launch_pad<CB, PB, WC, WP, OUT_MODULE + REAL_F16>(a, b, br, stream);
+    if (b.tail) {
+        // (the 2 x 2 tile has no registers for the float stream's identity vectors: never chosen for it)
+        if constexpr (CB * PB < 4) return launch_pad<CB, PB, WC, WP, OUT_MODULE + REAL_F32>(a, b, br, stream);
+        else return hipErrorInvalidValue;
+    }
+    if (b.fused) return launch_pad<CB, PB, WC, WP, OUT_BITS>(a, b, br, stream);
+    return launch_pad<CB, PB, WC, WP, OUT_I32>(a, b, br, stream);
+}
+
+int64_t branch_x_bytes(const ConvShape& s, const BranchArgs& b)
+{
+    const int64_t one = (int64_t)s.n * s.h * s.w * s.cw * 4;
+    return b.x_branch_stride ? (int64_t)(b.branches - 1) * b.x_branch_stride * 4 + one : one;
+}
+
+}  // namespace
+
+bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b)
+{
+    const int64_t w_bytes = (int64_t)s.c_out * b.branches * s.cw * 4;
+    // a branch's sum (K padded to an even number of words) stays exact in fp32; 31-bit byte offsets
+    return b.branches <= MAX_BRANCHES && ((int64_t)s.cw + 1) * 32 < (1 << 22) && branch_x_bytes(s, b) < (1ll << 31) && w_bytes < (1ll << 31);
+}
+
+// Estimated time of a tile in microseconds, as for the plain convolution: a launch, a wave's chain of groups of four
+// K-steps, a wave's set-up and epilogue and its groups where more waves than SIMDs (1024) share the issue slots.
+// Fits over 74 calls; rms error 14 to 19 %, the choice 1 to 2 % over the best tile on average, 24 % at worst.
+struct BranchCost { double fixed, group, wave, wave_group; };
+struct BranchTile { int tile, cb, pb; BranchCost plain, tail; };
+static const BranchTile BRANCH_TILES[] = {
+    {DIRECT_1x1, 1, 1, {2.85, 0.429, 0.184, 0.173}, {4.06, 0.354, 1.109, 0.201}},
+    {DIRECT_2x1, 2, 1, {3.76, 0.598, 0.663, 0.250}, {6.30, 0.472, 1.858, 0.342}},
+    {DIRECT_2x2, 2, 2, {4.67, 0.733, 1.933, 0.322}, {9.60, 0.644, 2.979, 0.491}},
+};
+
+int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b)
+{
+    const double groups = (double)b.branches * (double)(((s.cw + 1) / 2 + 3) / 4);
+    int best = DIRECT_1x1;
+    double least = 1e30;
+    for (const BranchTile& t : BRANCH_TILES) {
+        if (t.cb * t.pb == 4 && b.tail && !b.tail->half) continue;
+        const BranchCost& c = b.tail ? t.tail : t.plain;
+        const double waves = 4.0 * (double)((s.m + 128 * t.pb - 1) / (128 * t.pb)) *
+                             (double)((s.c_out + 32 * t.cb - 1) / (32 * t.cb)) / 1024.0;
+        const double cost = c.fixed + c.group * groups + (c.wave + c.wave_group * groups) * waves;
+        if (cost < least) { least = cost; best = t.tile; }
+    }
+    return best;
+}
+
+hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream)
+{
+    DirectArgs a{};
+    a.s = s;
+    a.taps = b.branches;
+    a.n_words = b.branches * s.cw;
+    a.half_words = (s.cw + 1) / 2;
+    a.z = 64 * a.half_words - s.k / (s.ks * s.ks);           // of one branch
+    a.x_bytes = (int32_t)branch_x_bytes(s, b);
+    a.w_bytes = (int32_t)((int64_t)s.c_out * a.n_words * 4);
+    a.pad_bytes = a.n_words * 4;
+    a.row_jump = (s.w - s.ks) * s.cw;
+    a.tap_step = (int32_t)b.x_branch_stride;
+    a.div_hw = DivBy::make(s.ho * s.wo);
+    a.div_wo = DivBy::make(s.wo);
+    const DirectBranch br{b.scale, b.bias, b.pad_words};
+    switch (tile) {
+        case DIRECT_1x1: return launch_out<1, 1, 1, 4>(a, b, br, stream);
+        case DIRECT_2x1: return launch_out<2, 1, 1, 4>(a, b, br, stream);
+        case DIRECT_2x2: return launch_out<2, 2, 1, 4>(a, b, br, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace bcnn

@@ -6,7 +6,7 @@ namespace bcnn {
 
 // Tiles: 32-channel x 32-pixel blocks of a wave; _K4: four waves split K, otherwise four waves side by side
 // along the pixels.
-enum { DIRECT_NONE = 0, DIRECT_1x1_K4, DIRECT_2x2_K4, DIRECT_2x1, DIRECT_1x1 };
+enum { DIRECT_NONE = 0, DIRECT_1x1_K4, DIRECT_2x2_K4, DIRECT_2x1, DIRECT_1x1, DIRECT_2x2 };
 
 bool conv_mfma_direct_supported(const ConvShape& s);
 // The tile with the least estimated time; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the call)
@@ -15,5 +15,10 @@ int conv_mfma_direct_choose(const ConvShape& s, bool module, bool staged);
 // thr == nullptr: int32 sums, else packed bits; ep != nullptr: module epilogue (thr and out are ignored)
 hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream);
+
+// the same in branch mode (tiles DIRECT_1x1, DIRECT_2x1, DIRECT_2x2: four waves along the pixels)
+bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b);
+int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b);
+hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream);
 
 }  // namespace bcnn

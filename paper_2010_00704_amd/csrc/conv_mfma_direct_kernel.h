@@ -1,0 +1,517 @@
+// Binary convolution on the matrix cores without LDS staging of the operands, for every channel count.
+//
+// Arithmetic as in conv_mfma_fp4_kernel.h (+-1 as 4-bit floats, exact fp32 sums; BCNN paper, Section 1: the
+// operator is a matrix product; Section 4.2.1: operands are +-1, padding is -1), with the plain codes on both
+// sides: bit b of a word becomes the nibble 0b1010 (-1.0) or 0b0010 (+1.0), seven vector instructions a
+// fragment, and positions that are zero in both operands count +1 each, one constant for the whole call.
+//
+// What this kernel is for.  The staged kernel wants long launches of wide tiles: 128 channels x 256 pixels a
+// workgroup, three LDS stages, 16-byte units that never straddle a tap (C_in a multiple of 128).  A small
+// launch leaves it with a few workgroups on 256 compute units, each walking all of K alone, and a ragged channel
+// count does not fit it at all.  Here a wave fetches its operands from global memory straight into the
+// registers the matrix instruction's lanes need (lane = row of the tile, 16 bytes = four K-words of one row), so
+// a tile needs no barrier until its sums are complete, and
+//   - WK waves of a workgroup can split K between them and add their exact partial sums in LDS at the end;
+//   - K is walked in 16-byte units per tap; a tap whose words are no multiple of four ends in a unit that starts
+//     four words before the tap's end, and the words it shares with its neighbour are masked to zero on both
+//     sides (TAIL); taps of fewer than four words are walked word by word over the flattened K axis (WORDS).
+// Bound: latency for the small launches, vector-ALU issue (expansion, about seven instructions per MFMA with
+// 2 x 2 blocks a wave) and the loads' latency for the large ones, HBM and the epilogue for module outputs of small K.
+// Measured (graph replays, us, against the kernel that ran the call before): 3x3, 1024 -> 1024, one 7 x 7 image
+// 25.2 -> 5.1; 3x3, 320 -> 200, 13 maps of 27 x 27 47.7 -> 11.3; 3x3, 64 -> 64, one 14 x 14 image 6.3 -> 4.4 (sums)
+// and 10.3 -> 4.5 (bits); 3x3, 832 -> 224, 22 maps of 30 x 30 232 -> 27; 1x1 module, 1024 channels, 32 maps of
+// 7 x 7 11.5 -> 7.5.  At least two workgroups of a SIMD are asked for in the launch bounds: without that the compiler
+// keeps the accumulators in the accumulation registers and copies them (2 x 1 blocks: 84 registers a lane instead of
+// 96, the first two calls above 5.1 -> 4.9 and 11.3 -> 10.1, the third 4.4 -> 2.9).
+// Branch mode, 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 us in the staged kernel, 33 here (a tap's fold
+// there exchanges its corrections through LDS and costs more than the tap's matrix work); 512 channels, 64 maps of
+// 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.
+#pragma once
+#include "bcnn_common.h"
+#include "div_by.h"
+
+#include <type_traits>
+
+namespace bcnn {
+
+struct DirectArgs {
+    ConvShape s;
+    int32_t n_ptiles, n_ctiles;
+    int32_t per_tap;         // units per tap (WORDS: words per tap)
+    int32_t n_units;         // units along K (WORDS: of the flattened word axis, the last one may be partial)
+    int32_t n_words;         // taps * cw
+    int32_t n_chunks;        // ceil(n_units / 2): a chunk is one unit per lane half = four K-steps
+    int32_t z;               // 256 * n_chunks - K: positions that are zero on both sides and count +1 each
+    int32_t x_bytes, w_bytes;
+    int32_t row_jump;        // words added to the input offset per completed filter row
+    DivBy div_ct, div_hw, div_wo, div_tap;
+    // branch mode
+    int32_t taps;            // branches
+    int32_t half_words;      // ceil(cw / 2): lane half h walks the words h * half_words .. of every tap
+    int32_t tap_step;        // words between the branches' input tensors
+    int32_t pad_bytes, scale_bytes;
+};
+
+// Branch mode: per-branch scales, bias, what a tap outside the image stands for.
+struct DirectBranch {
+    const float* scale;         // [taps][c_out]
+    const float* bias;          // [c_out] or nullptr
+    const uint32_t* pad_words;  // [taps][cw] (PAD_OPERAND)
+};
+
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+enum { OUT_I32 = 0, OUT_BITS = 1, OUT_MODULE = 2 };          // OUT_MODULE + REAL_*
+enum { UNITS = 0, TAIL = 1, WORDS = 2 };
+// Branch mode (F x F convolution as F*F shifted 1x1 branches, or P parallel ones, each with a real scale per output
+// channel: Section 4.2.1, last paragraph; Figure 2, bottom).  OUT_I32 then stores float sums, OUT_BITS z >= 0.
+enum { PAD_NONE = 0, PAD_OPERAND = 1, PAD_NOTHING = 2 };     // outside the image: -1, the branch's pad words, no contribution
+constexpr int BRANCH = 4;                                    // MODE = BRANCH + PAD_*
+constexpr int MAX_BRANCHES = 16;                             // scales kept in LDS
+
+// MFMA row i of a 32-row block carries this channel of the block, so that a lane ends up holding 16
+// consecutive channels of one pixel (lane half h, register r <-> channel 16h + r).
+__device__ __forceinline__ int row_to_channel(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
+
+// A wave owns CB x PB blocks of 32 channels x 32 pixels; a workgroup WC x WP such tiles, each shared by WK
+// waves that split K.
+template <int CB, int PB, int WC, int WP, int WK, int OUT, int MODE>
+__global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
+    DirectArgs a, const uint32_t* __restrict__ x, const uint32_t* __restrict__ w,
+    const int32_t* __restrict__ thr, void* __restrict__ out, ModuleEp ep, DirectBranch br)
+{
+    constexpr bool BR = MODE >= BRANCH;
+    constexpr int PAD = BR ? MODE - BRANCH : PAD_NONE;
+    static_assert(!BR || WK == 1, "a branch's sum is scaled as a whole");
+    constexpr bool MODULE = OUT >= OUT_MODULE;
+    constexpr int REAL = MODULE ? OUT - OUT_MODULE : REAL_F32;
+    constexpr bool HALF = REAL != REAL_F32;
+    using real_t = typename real_type<REAL>::type;
+    typedef real_t real4 __attribute__((ext_vector_type(4)));
+    constexpr int TCH = 32 * CB, TPX = 32 * PB;              // a wave's tile
+    // Partial (WK > 1) or complete sums on their way from the matrix layout to rows of channels.  WK = 1:
+    // every wave turns one pixel block at a time around in a region of its own.
+    constexpr int ROW = TCH + 4;                             // floats; rows stay 16-byte aligned, banks skewed by 4
+    constexpr int REGION = (WK > 1 ? TPX : 32) * ROW;
+    __shared__ __align__(16) float lds[WC * WP * WK * REGION];
+
+    const ConvShape& s = a.s;
+    const int t = threadIdx.x;
+    const int lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wk = wave % WK, wc = (wave / WK) % WC, wp = wave / (WK * WC);
+    const int hsel = lane >> 5, j = lane & 31;
+
+    // workgroup -> tile: each XCD takes a contiguous range, channel tile fastest
+    int tile = blockIdx.x;
+    {
+        const int per_xcd = (a.n_ptiles * a.n_ctiles) >> 3;
+        if (tile < per_xcd * 8) tile = (tile & 7) * per_xcd + (tile >> 3);
+    }
+    const int ptile = a.div_ct(tile);
+    const int o0 = (tile - ptile * a.n_ctiles) * (TCH * WC) + TCH * wc;   // first channel and pixel of the wave's tile
+    const int m0 = ptile * (TPX * WP) + TPX * wp;
+
+    // ---- the lane's rows
+    int wrow[CB];                                            // word offset of the weight row
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int ch = o0 + 32 * cb + row_to_channel(j);
+        wrow[cb] = (ch < s.c_out ? ch : s.c_out - 1) * a.n_words;
+    }
+    int rbase[PB];                                           // word offset of the window's top-left tap
+    uint32_t vmask[PB];                                      // one validity bit per tap
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+        int m = m0 + 32 * pb + j;
+        m = m < s.m ? m : s.m - 1;
+        if (s.ks == 1 && s.stride == 1) {
+            rbase[pb] = m * s.cw;
+            vmask[pb] = 1u;
+        } else {
+            const int hw = s.ho * s.wo;
+            const int n = a.div_hw(m);
+            const int r = m - n * hw;
+            const int oh = a.div_wo(r);
+            const int ph = oh * s.stride - s.pad;
+            const int pw = (r - oh * s.wo) * s.stride - s.pad;
+            rbase[pb] = ((n * s.h + ph) * s.w + pw) * s.cw;
+            uint32_t vm = 1u;                                // 1x1: no padding, always inside
+            if (s.ks == 3) {
+                uint32_t cols = 0;
+                vm = 0;
+#pragma unroll
+                for (int v = 0; v < 3; ++v) cols |= (uint32_t)((uint32_t)(pw + v) < (uint32_t)s.w) << v;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) vm |= ((uint32_t)(ph + u) < (uint32_t)s.h) ? cols << (3 * u) : 0u;
+            }
+            vmask[pb] = vm;
+        }
+    }
+
+    // ---- identity vectors of the module's plain case are requested before the K loop.  After the transpose a
+    // lane holds four consecutive channels, eight lanes a packed word; G such groups per lane.
+    constexpr int CG = TCH / 4;                              // groups per pixel of the wave's tile
+    constexpr int GROUPS = WK > 1 ? (TPX * CG + 64 * WK - 1) / (64 * WK) : TPX * CG / 64;
+    const int lt = WK > 1 ? wk * 64 + lane : lane;           // place among the threads that share the tile
+    const int c0 = o0 + 4 * (lt % CG);
+    constexpr int PX_STEP = (WK > 1 ? 64 * WK : 64) / CG;    // pixels between a lane's groups
+    const int px0 = lt / CG;
+    const bool some = WK == 1 || (64 * WK <= TPX * CG) || px0 < TPX;
+    bool vec = false;
+    real4 ids[MODULE ? GROUPS : 1];
+    const int id0 = MODULE ? c0 % (ep.id_channels > 0 ? ep.id_channels : 1) : 0;
+    if constexpr (MODULE) {
+        const uintptr_t both = reinterpret_cast<uintptr_t>(ep.r) | reinterpret_cast<uintptr_t>(ep.identity);
+        vec = ep.identity && ep.r && ep.x_next && s.c_out % 4 == 0 && ep.id_channels % 4 == 0 && (both & (HALF ? 7 : 15)) == 0;
+        if (vec) {
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g) {
+                const int m = m0 + px0 + g * PX_STEP;
+                ids[g] = real4{(real_t)0, (real_t)0, (real_t)0, (real_t)0};
+                if (some && m < s.m && c0 < s.c_out)
+                    ids[g] = __builtin_nontemporal_load(reinterpret_cast<const real4*>(
+                        static_cast<const real_t*>(ep.identity) + (size_t)m * ep.id_channels + id0));
+            }
+        }
+    }
+
+    // ---- operands of one chunk: a unit (four words) of every row of the tile, straight into registers.  Offsets
+    // past the buffers (taps outside the image, K padding) read as zero.
+    const auto xres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(x), 0, a.x_bytes, 0x00020000);
+    const auto wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(w), 0, a.w_bytes, 0x00020000);
+    struct Chunk { v4i w[CB], x[PB]; };
+    auto fetch = [&](int chunk, Chunk& c) {
+        const int u = 2 * chunk + hsel;
+        if constexpr (MODE == UNITS || MODE == TAIL) {
+            const int tap = a.div_tap(u);
+            const int q = u - tap * a.per_tap;
+            const bool real = u < a.n_units;
+            int k = tap * s.cw + 4 * q;
+            const bool last = MODE == TAIL && q == a.per_tap - 1;
+            if constexpr (MODE == TAIL) {
+                if (last) k = tap * s.cw + s.cw - 4;
+            }
+            const int xo = k + ((tap >= 3) + (tap >= 6)) * a.row_jump;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                c.w[cb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+                    wres, real ? (wrow[cb] + k) * 4 : -16, 0, 0));
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                const bool in = real && ((vmask[pb] >> (tap & 31)) & 1u);
+                c.x[pb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+                    xres, in ? (rbase[pb] + xo) * 4 : -16, 0, 0));
+            }
+        } else if constexpr (MODE == WORDS) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = 4 * u + i;
+                const int tap = a.div_tap(k);
+                const bool real = k < a.n_words;
+                const int xo = k + ((tap >= 3) + (tap >= 6)) * a.row_jump;
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    c.w[cb][i] = __builtin_bit_cast(int, __builtin_amdgcn_raw_buffer_load_b32(
+                        wres, real ? (wrow[cb] + k) * 4 : -4, 0, 0));
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    const bool in = real && ((vmask[pb] >> (tap & 31)) & 1u);
+                    c.x[pb][i] = __builtin_bit_cast(int, __builtin_amdgcn_raw_buffer_load_b32(
+                        xres, in ? (rbase[pb] + xo) * 4 : -4, 0, 0));
+                }
+            }
+        }
+    };
+    // words that a tap's last unit shares with its neighbour count as zero on both sides
+    const int shared = MODE == TAIL ? 4 * a.per_tap - s.cw : 0;   // 1 .. 3
+    auto mask_tail = [&](int chunk, Chunk& c) {
+        if constexpr (MODE == TAIL) {
+            const int u = 2 * chunk + hsel;
+            const int q = u - a.div_tap(u) * a.per_tap;
+            const bool last = q == a.per_tap - 1;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int keep = last && i < shared ? 0 : -1;
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) c.w[cb][i] &= keep;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) c.x[pb][i] &= keep;
+            }
+        }
+    };
+    uint32_t m8, c2;                                         // held in registers: v_and_or_b32 takes no literals
+    asm volatile("v_mov_b32 %0, 0x88888888" : "=v"(m8));
+    asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(c2));
+    auto expand = [&](uint32_t word) -> v8i {
+        return v8i{(int)(((word << 3) & m8) | c2), (int)(((word << 2) & m8) | c2), (int)(((word << 1) & m8) | c2),
+                   (int)((word & m8) | c2), 0, 0, 0, 0};
+    };
+
+    v16f acc[CB][PB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
+    v16f tot[BR ? CB : 1][BR ? PB : 1];                      // branch mode: the scaled sum so far
+
+    auto multiply = [&](const Chunk& c, int steps) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            if (BR && ks >= steps) break;
+            v8i fw[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) fw[cb] = expand((uint32_t)c.w[cb][ks]);
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                const v8i fx = expand((uint32_t)c.x[pb][ks]);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[cb], fx, acc[cb][pb], 4, 4, 0, 0, 0, 0);
+            }
+        }
+    };
+    if constexpr (!BR) {
+        // A wave takes the chunks wk, wk + WK, ...; AHEAD of them are in flight while one is multiplied.
+        constexpr int AHEAD = (CB * PB == 1) ? 4 : 2;
+        Chunk ring[AHEAD];
+        const int mine = (a.n_chunks - wk + WK - 1) / WK;        // may be zero or negative
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+            if (i < mine) fetch(wk + WK * i, ring[i]);
+        for (int i = 0; i < mine; i += AHEAD) {
+#pragma unroll
+            for (int b = 0; b < AHEAD; ++b) {
+                if (i + b < mine) {
+                    mask_tail(wk + WK * (i + b), ring[b]);
+                    multiply(ring[b], 4);
+                    if (i + b + AHEAD < mine) fetch(wk + WK * (i + b + AHEAD), ring[b]);
+                }
+            }
+        }
+    } else {
+        // A tap's words are split between the lane halves (half h: words h * half_words ..) and walked in groups
+        // of four words = four K-steps with one 16-byte load per row; what is left of the half (half_words mod 4)
+        // is a group of single words.  Every load is wave-uniform but for the rows' offsets and their validity.
+        // The accumulators start a tap at minus the positions that are zero on both sides, so that the tap's sum
+        // needs no correction: a completed tap costs one fma per element, tot = fma(scale, y_t, tot) in the order
+        // t = 0, 1, ... (the chain is part of the interface), and one move to restart.
+        const int full = a.half_words >> 2, rest = a.half_words & 3;
+        const int per_tap = full + (rest != 0);
+        const float start = (float)-a.z;                     // a.z: of one tap
+        const auto pres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(br.pad_words), 0, PAD == PAD_OPERAND ? a.pad_bytes : 0, 0x00020000);
+        const int half0 = hsel * a.half_words;
+        auto fetch_group = [&](int tap, int g, Chunk& c) {
+            const int k = half0 + 4 * g;                     // first word within the tap
+            const int wo = tap * s.cw + k;
+            const int xo = k + tap * a.tap_step + (s.ks == 3 ? tap * s.cw + ((tap >= 3) + (tap >= 6)) * a.row_jump : 0);
+            if (g < full) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    c.w[cb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wres, (wrow[cb] + wo) * 4, 0, 0));
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    const bool in = s.ks == 1 || ((vmask[pb] >> tap) & 1u);
+                    c.x[pb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(xres, in ? (rbase[pb] + xo) * 4 : -16, 0, 0));
+                    if constexpr (PAD == PAD_OPERAND) {
+                        if (s.ks == 3)
+                            c.x[pb] |= __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(pres, in ? -16 : wo * 4, 0, 0));
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    if (i >= rest) break;
+                    const bool real = k + i < s.cw;          // an odd count leaves the second half one word short
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+                        c.w[cb][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(wres, real ? (wrow[cb] + wo + i) * 4 : -4, 0, 0);
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) {
+                        const bool in = s.ks == 1 || ((vmask[pb] >> tap) & 1u);
+                        c.x[pb][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(xres, real && in ? (rbase[pb] + xo + i) * 4 : -4, 0, 0);
+                        if constexpr (PAD == PAD_OPERAND) {
+                            if (s.ks == 3)
+                                c.x[pb][i] |= (int)__builtin_amdgcn_raw_buffer_load_b32(pres, real && !in ? (wo + i) * 4 : -4, 0, 0);
+                        }
+                    }
+                }
+            }
+        };
+        __shared__ __align__(16) float scale_lds[MAX_BRANCHES][TCH * WC];
+        for (int i = t; i < a.taps * (TCH * WC); i += 64 * WC * WP) {
+            const int tp = i / (TCH * WC), cl = i - tp * (TCH * WC);
+            const int ch = o0 - TCH * wc + cl;
+            scale_lds[tp][cl] = br.scale[(size_t)tp * s.c_out + (ch < s.c_out ? ch : s.c_out - 1)];
+        }
+        Chunk cur, nxt;
+        fetch_group(0, 0, cur);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            float b[16];
+            const int ch = o0 + 32 * cb + 16 * hsel;         // the lane's 16 channels of the block
+#pragma unroll
+            for (int r = 0; r < 16; ++r) b[r] = br.bias ? br.bias[ch + r < s.c_out ? ch + r : s.c_out - 1] : 0.0f;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { tot[cb][pb][r] = b[r]; acc[cb][pb][r] = start; }
+        }
+        __syncthreads();
+        for (int tap = 0; tap < a.taps; ++tap) {
+            for (int g = 0; g < per_tap; ++g) {
+                const bool more = g + 1 < per_tap;
+                if (more || tap + 1 < a.taps) fetch_group(more ? tap : tap + 1, more ? g + 1 : 0, nxt);
+                multiply(cur, g < full ? 4 : rest);
+                cur = nxt;
+            }
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v4f sc = *reinterpret_cast<const v4f*>(&scale_lds[tap][TCH * wc + 32 * cb + 16 * hsel + 4 * q]);
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) {
+                        const bool in = PAD != PAD_NOTHING || s.ks == 1 || ((vmask[pb] >> tap) & 1u);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float zn = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
+                            tot[cb][pb][4 * q + k] = in ? zn : tot[cb][pb][4 * q + k];
+                            acc[cb][pb][4 * q + k] = start;
+                        }
+                    }
+                }
+        }
+    }
+
+    // ---- epilogue.  A pixel's channels through LDS: lane (pixel j, half h) holds channels 16h .. 16h+15 of a block.
+    float* region = lds + (wp * WC + wc) * WK * REGION;
+    auto park = [&](float* dst, int pb, int row0) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4)
+            {
+                const v16f& v = [&]() -> const v16f& { if constexpr (BR) return tot[cb][pb]; else return acc[cb][pb]; }();
+                *reinterpret_cast<v4f*>(dst + (row0 + j) * ROW + 32 * cb + 16 * hsel + r) = v4f{v[r], v[r + 1], v[r + 2], v[r + 3]};
+            }
+    };
+    const float zf = (float)a.z;
+    // per-channel parameters of the lane's four channels (clamped loads for a ragged c_out)
+    int th[4];
+    float pg[4], pbi[4], pa[4], pc[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int ch = c0 + k < s.c_out ? c0 + k : s.c_out - 1;
+        if constexpr (OUT == OUT_BITS && !BR) th[k] = thr[ch];
+        if constexpr (MODULE) {
+            if constexpr (!BR) { pg[k] = ep.scale[ch]; pbi[k] = ep.bias[ch]; }
+            pa[k] = ep.slope ? ep.slope[ch] : 1.0f;
+            pc[k] = ep.next_bias ? ep.next_bias[ch] : 0.0f;
+        }
+    }
+    const bool out_vec = OUT == OUT_I32 && s.c_out % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+    // four sums (still with the constant z) of pixel m, channels c0 ..; every lane of the wave calls it
+    auto emit = [&](v4f v, int m, bool ok, int g) {
+        const int nch = s.c_out - c0;                        // real channels from c0 on (may be <= 0)
+        uint32_t nib = 0;
+        if constexpr (OUT == OUT_I32) {
+            int32_t* y = static_cast<int32_t*>(out) + (size_t)m * s.c_out + c0;
+            v4i q;
+            if constexpr (BR) q = __builtin_bit_cast(v4i, v);
+            else q = v4i{(int)(v[0] - zf), (int)(v[1] - zf), (int)(v[2] - zf), (int)(v[3] - zf)};
+            if (ok && nch > 0) {
+                if (out_vec) {
+                    __builtin_nontemporal_store(q, reinterpret_cast<v4i*>(y));
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (k < nch) y[k] = q[k];
+                }
+            }
+            return;
+        } else if constexpr (OUT == OUT_BITS) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (BR) nib |= (uint32_t)(k < nch && v[k] >= 0.0f) << k;
+                else nib |= (uint32_t)(k < nch && (int)(v[k] - zf) >= th[k]) << k;
+            }
+        } else {
+            real_t* rp = static_cast<real_t*>(ep.r) + (size_t)m * s.c_out + c0;
+            real4 id = ids[g];
+            if (!vec) {
+                const real_t* idrow = static_cast<const real_t*>(ep.identity) + (size_t)m * ep.id_channels;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) id[k] = (ok && ep.identity && k < nch) ? idrow[(id0 + k) % ep.id_channels] : (real_t)0;
+            }
+            real4 st;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                // a missing slope is the slope 1 (1 * t is t)
+                float val;
+                if constexpr (BR) val = module_tail<REAL>(v[k], vec || ep.identity != nullptr, (float)id[k], true, pa[k]);
+                else val = module_value<REAL>(v[k] - zf, pg[k], pbi[k], vec || ep.identity != nullptr, (float)id[k], true, pa[k]);
+                nib |= (uint32_t)(k < nch && val + pc[k] >= 0.0f) << k;
+                st[k] = (real_t)val;
+            }
+            if (ok && nch > 0) {
+                if (vec) {
+                    *reinterpret_cast<real4*>(rp) = st;
+                } else if (ep.r) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (k < nch) rp[k] = st[k];
+                }
+            }
+        }
+        // eight neighbouring lanes hold the 32 channels of one packed word
+        uint32_t wd = nib << (4 * (lane & 7));
+        wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+        wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+        wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0x141, 0xF, 0xF, true);  // row_half_mirror
+        uint32_t* yp = MODULE ? ep.x_next : static_cast<uint32_t*>(out);
+        if (ok && nch > 0 && (lane & 7) == 0 && (!MODULE || yp)) yp[(size_t)m * s.cwo + (c0 >> 5)] = wd;
+    };
+    if constexpr (WK > 1) {
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) park(region + wk * REGION, pb, 32 * pb);
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+            const int px = px0 + g * PX_STEP;
+            v4f sum = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (some) {
+#pragma unroll
+                for (int k = 0; k < WK; ++k)
+                    sum += *reinterpret_cast<const v4f*>(region + k * REGION + px * ROW + 4 * (lt % CG));
+            }
+            emit(sum, m0 + px, some && m0 + px < s.m, g);
+        }
+    } else {
+        // same wave wrote and reads: LDS operations of a wave complete in order
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            park(region, pb, 0);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int g = 0; g < GROUPS / PB; ++g) {
+                const int px = px0 + g * PX_STEP;
+                const v4f sum = *reinterpret_cast<const v4f*>(region + px * ROW + 4 * (lt % CG));
+                const int m = m0 + 32 * pb + px;
+                emit(sum, m, m < s.m, pb * (GROUPS / PB) + g);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
+}  // namespace
+}  // namespace bcnn
