@@ -344,18 +344,19 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
     const bool mfma_ok = bcnn::conv_mfma_fp4_supported(s, x_packed, w_packed);
     switch (variant) {
         case BCNN_VARIANT_AUTO: {
-            // The staged kernel is weighed in its plain form only (whole 128-channel tiles, every part of the
-            // module present); its general form is behind the direct kernel at every size measured.  1x1
-            // modules of one or two words per pixel are bound by their real-valued epilogue, which is
-            // shorter in the vector-ALU kernel: 64 channels, 112 x 112 map, 32 images, half: 30.4 us against
-            // 35.7; from about 4e6 elements on it is ahead.
+            // 1x1 modules of up to 256 input channels are bound by their real stream: the streaming kernel is ahead
+            // of every other at all 64 sizes measured, or level with the direct one at the smallest.  The
+            // staged kernel is weighed in its plain form only (whole 128-channel tiles, every part of the
+            // module present); its general form is behind the direct kernel at every size measured.
+            if (bcnn::conv_mfma_stream_supported(s, m)) {
+                e = bcnn::launch_conv_mfma_stream(s, x_packed, w_packed, m, st);
+                break;
+            }
             const bool plain = mfma_ok && s.c_out % 128 == 0 && m.identity && m.r && m.x_next && m.id_channels % 4 == 0;
-            const bool few_words = s.ks == 1 && s.cw <= 2 && (int64_t)s.m * s.c_out >= 4000000;
-            const int tile = !few_words && bcnn::conv_mfma_direct_supported(s)
-                                 ? bcnn::conv_mfma_direct_choose(s, true, plain) : bcnn::DIRECT_NONE;
+            const int tile = bcnn::conv_mfma_direct_supported(s) ? bcnn::conv_mfma_direct_choose(s, true, plain) : bcnn::DIRECT_NONE;
             if (tile != bcnn::DIRECT_NONE)
                 e = bcnn::launch_conv_mfma_direct(s, x_packed, w_packed, nullptr, nullptr, &m, tile, st);
-            else if (mfma_ok && !few_words)
+            else if (mfma_ok)
                 e = bcnn::launch_conv_mfma_fp4(s, x_packed, w_packed, nullptr, nullptr, &m, 0, st);
             else
                 e = bcnn::launch_conv_valu(s, x_packed, w_packed, nullptr, nullptr, &m, st);

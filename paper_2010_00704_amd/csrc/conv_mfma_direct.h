@@ -21,4 +21,9 @@ bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b);
 int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b);
 hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream);
 
+// 1x1 modules of at most eight words per pixel, plain case (conv_mfma_stream.hip)
+bool conv_mfma_stream_supported(const ConvShape& s, const ModuleEp& ep);
+hipError_t launch_conv_mfma_stream(const ConvShape& s, const uint32_t* x, const uint32_t* w, const ModuleEp& ep,
+                                   hipStream_t stream);
+
 }  // namespace bcnn

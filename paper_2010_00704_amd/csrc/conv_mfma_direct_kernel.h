@@ -405,17 +405,29 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             }
     };
     const float zf = (float)a.z;
-    // per-channel parameters of the lane's four channels (clamped loads for a ragged c_out)
+    // per-channel parameters of the lane's four channels, through buffers: a channel past the end and a missing array
+    // (no bytes) read as zero, without branches
     int th[4];
     float pg[4], pbi[4], pa[4], pc[4];
+    auto load_params = [&](const void* p, auto& v) {
+        const auto res = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, p ? s.c_out * 4 : 0, 0x00020000);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int ch = c0 + k < s.c_out ? c0 + k : s.c_out - 1;
-        if constexpr (OUT == OUT_BITS && !BR) th[k] = thr[ch];
-        if constexpr (MODULE) {
-            if constexpr (!BR) { pg[k] = ep.scale[ch]; pbi[k] = ep.bias[ch]; }
-            pa[k] = ep.slope ? ep.slope[ch] : 1.0f;
-            pc[k] = ep.next_bias ? ep.next_bias[ch] : 0.0f;
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t q = __builtin_amdgcn_raw_buffer_load_b32(res, (c0 + k) * 4, 0, 0);
+            v[k] = __builtin_bit_cast(std::decay_t<decltype(v[0])>, q);
+        }
+    };
+    if constexpr (OUT == OUT_BITS && !BR) load_params(thr, th);
+    if constexpr (MODULE) {
+        if constexpr (!BR) {
+            load_params(ep.scale, pg);
+            load_params(ep.bias, pbi);
+        }
+        load_params(ep.slope, pa);
+        load_params(ep.next_bias, pc);
+        if (!ep.slope) {                                     // a missing slope is the slope 1 (1 * t is t)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pa[k] = 1.0f;
         }
     }
     const bool out_vec = OUT == OUT_I32 && s.c_out % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
@@ -455,7 +467,6 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             real4 st;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                // a missing slope is the slope 1 (1 * t is t)
                 float val;
                 if constexpr (BR) val = module_tail<REAL>(v[k], vec || ep.identity != nullptr, (float)id[k], true, pa[k]);
                 else val = module_value<REAL>(v[k] - zf, pg[k], pbi[k], vec || ep.identity != nullptr, (float)id[k], true, pa[k]);
