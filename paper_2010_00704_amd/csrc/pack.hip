@@ -5,6 +5,7 @@
 // bandwidth is the only bound and the design goal is wide, coalesced reads
 // with many of them in flight.
 #include "bcnn_common.h"
+#include "div_by.h"
 
 #include <type_traits>
 
@@ -247,6 +248,94 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(
     }
 }
 
+// ---- inner == 1, source rows of whole dwords ----------------------------------
+// A thread owns eight consecutive channels, 16 bytes of a 16-bit row, and four threads a packed word.  Its place
+// along the row, and with it its eight biases, is the same for all its rows: the block's 256 threads are cut into
+// runs of `per_row` threads, one run per row, and a thread takes one row per pass, all passes' loads in flight
+// before the first is used.  Replicated channels read the source row again (channel c reads c mod src_channels).
+// HBM bound.  Graph replays, us, against the kernels that ran these calls before: half, 128 channels with bias, 100 352
+// rows 8.0 -> 4.2 (6.5 TB/s); bfloat16 11.4 -> 4.1; replicated twice from 25 088 rows 9.6 -> 3.2; int8, 256
+// channels, 200 000 rows 50.9 -> 10.2; float, 128 channels 11.2 -> 9.5.  Four passes: one is 5.0 on the first of
+// these, two 4.4, eight 4.4, and on 300 rows all are level.
+// Every access is a raw buffer access with a 32-bit offset from the block's first row: what does not exist (rows past
+// the end, channels past the last row's end) reads as zero and stores nothing, without branches between the loads;
+// the first form of this kernel, with predicated loads, took 8.4 us where this one takes 4.2.
+constexpr int LAST8_PASSES = 4;
+// rows a whole number of dwords apart; the eight channels of a thread must not wrap inside a replica; 256 threads a row
+bool last8_applies(size_t esz, const void* src, int64_t channels, int64_t src_channels)
+{
+    return (src_channels * (int64_t)esz) % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 3) == 0 && channels <= 2048 &&
+           (src_channels == channels || src_channels % 8 == 0);
+}
+
+template <typename T, bool BIAS>
+__global__ __launch_bounds__(256) void pack_last8_kernel(
+    const T* __restrict__ src, const float* __restrict__ bias, int64_t rows, int channels, int src_channels,
+    int cw, int per_row, int rows_per_pass, DivBy div_row, uint32_t* __restrict__ dst)
+{
+    typedef T t8 __attribute__((ext_vector_type(8)));
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    constexpr int ESZ = (int)sizeof(T);
+    constexpr int PASSES = LAST8_PASSES;
+    const int t = threadIdx.x;
+    const int r = div_row(t), q = t - r * per_row;
+    const int c0 = 8 * q;
+    const bool live = c0 < channels;                         // the row's last word may have lanes without channels
+    const int left = channels - c0;
+    const uint32_t valid = left >= 8 ? 0xFFu : left > 0 ? (1u << left) - 1u : 0u;
+    const int64_t first = (int64_t)blockIdx.x * (rows_per_pass * PASSES);
+    const int here = (int)(rows - first < rows_per_pass * PASSES ? rows - first : rows_per_pass * PASSES);
+    const int src_row = src_channels * ESZ, dst_row = cw * 4;
+    const auto sres = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src + first * src_channels), 0, here * src_row, 0x00020000);
+    const auto dres = __builtin_amdgcn_make_buffer_rsrc(dst + first * cw, 0, here * dst_row, 0x00020000);
+    const auto bres = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(bias), 0, BIAS ? channels * 4 : 0, 0x00020000);
+    constexpr uint32_t NOWHERE = 0x7FFFFF00u;                // past every buffer
+    const bool mine = r < rows_per_pass;
+    const int cs = src_channels == channels ? c0 : (int)((uint32_t)c0 % (uint32_t)src_channels);
+    const uint32_t from = mine && live ? (uint32_t)(r * src_row + cs * ESZ) : NOWHERE;
+    const uint32_t to = mine && (q & 3) == 0 ? (uint32_t)(r * dst_row + q) : NOWHERE;      // word q / 4
+    t8 v[PASSES];
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        const int off = (int)(from + (uint32_t)(k * rows_per_pass * src_row));
+        if constexpr (ESZ == 2) {
+            v[k] = __builtin_bit_cast(t8, __builtin_amdgcn_raw_buffer_load_b128(sres, off, 0, 0));
+        } else if constexpr (ESZ == 1) {
+            v[k] = __builtin_bit_cast(t8, __builtin_amdgcn_raw_buffer_load_b64(sres, off, 0, 0));
+        } else {
+            const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(sres, off, 0, 0));
+            const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(sres, off + 16, 0, 0));
+            v[k] = t8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        }
+    }
+    float b[8];
+#pragma unroll
+    for (int h = 0; h < 8; h += 4) {
+        f4 w = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (BIAS) w = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(bres, (c0 + h) * 4, 0, 0));
+        b[h] = w[0]; b[h + 1] = w[1]; b[h + 2] = w[2]; b[h + 3] = w[3];
+    }
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int i = 7; i >= 0; --i) {
+            if constexpr (ESZ == 1 && !BIAS) {
+                bits = 2 * bits + (uint32_t)(v[k][i] >= 0);
+            } else {
+                // bits = 2 * bits + (value + bias >= 0), the comparison entering as the carry
+                const float f = BIAS ? (float)v[k][i] + b[i] : (float)v[k][i];
+                asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(f) : "vcc");
+            }
+        }
+        uint32_t wd = (bits & valid) << (8 * (q & 3));
+        wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+        wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+        __builtin_amdgcn_raw_buffer_store_b32((int)wd, dres, (int)(to + (uint32_t)(k * rows_per_pass * dst_row)), 0, 0);
+    }
+}
+
 // ---- anything else (small inner, e.g. 3x3 filter taps): one thread per word --
 template <typename T, bool BIAS, bool REP>
 __global__ __launch_bounds__(256) void pack_generic_kernel(
@@ -273,7 +362,12 @@ hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t
                          int64_t src_channels, int64_t inner, uint32_t* dst, hipStream_t stream)
 {
     const int64_t cw = (channels + 31) / 32;
-    if (inner == 1) {
+    if (inner == 1 && last8_applies(sizeof(T), src, channels, src_channels)) {
+        const int per_row = (int)cw * 4, rows_per_pass = 256 / per_row, per_block = rows_per_pass * LAST8_PASSES;
+        hipLaunchKernelGGL((pack_last8_kernel<T, BIAS>), dim3((unsigned)((outer + per_block - 1) / per_block)), dim3(256), 0, stream,
+                           src, bias, outer, (int)channels, (int)src_channels, (int)cw, per_row, rows_per_pass,
+                           DivBy::make(per_row), dst);
+    } else if (inner == 1) {
         constexpr int ROWS = 8;
         const int64_t groups = (channels + 63) / 64;
         const int64_t waves = ((outer + ROWS - 1) / ROWS) * groups;
@@ -417,10 +511,11 @@ hipError_t pack_typed(const void* src, const float* bias, int64_t outer, int64_t
 hipError_t launch_pack(const void* src, int dtype, const float* bias, int64_t outer, int64_t channels,
                        int64_t src_channels, int64_t inner, uint32_t* dst, hipStream_t stream)
 {
-    // A channel-last source (inner = 1) with whole 16-byte (float) / 8-byte (half) groups of four
-    // channels is the pooling kernel's case with a 1 x 1 window: a lane takes four channels of a row,
-    // eight lanes make a packed word.  Twice to three times the rate of the lanes-along-channels kernel.
-    if (inner == 1 && src_channels == channels && (dtype == 0 || dtype == 1) && channels % 4 == 0 &&
+    // A channel-last source (inner = 1) of more channels than pack_last8_kernel takes, with whole 16-byte (float) /
+    // 8-byte (half) groups of four channels, is the pooling kernel's case with a 1 x 1 window: a lane takes four
+    // channels of a row, eight lanes make a packed word.  Twice to three times the rate of the
+    // lanes-along-channels kernel.
+    if (inner == 1 && src_channels == channels && channels > 2048 && (dtype == 0 || dtype == 1) && channels % 4 == 0 &&
         outer * 8 * ((channels + 31) / 32) <= 0x7FFFFFFF &&
         (reinterpret_cast<uintptr_t>(src) % (dtype == 0 ? 16 : 8)) == 0 &&
         (reinterpret_cast<uintptr_t>(bias) % 16) == 0)
