@@ -8,6 +8,7 @@
 #include "div_by.h"
 
 #include <type_traits>
+#include <utility>
 
 
 namespace bcnn {
@@ -36,6 +37,26 @@ __device__ __forceinline__ int64_t src_channel(int64_t c, int64_t src_channels)
 {
     if constexpr (REP) return (int64_t)((uint32_t)c % (uint32_t)src_channels);   // both below 2^31
     else return c;
+}
+
+// Compile-time loop: f(std::integral_constant<int, 0>) ... f(<N-1>).
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// `old` with the wave-uniform `word` in lane LANE
+template <int LANE>
+__device__ __forceinline__ uint32_t writelane(uint32_t word, uint32_t old)
+{
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(old) : "s"(word), "n"(LANE));
+    return old;
 }
 
 // ---- [outer][C][inner] with inner >= 64: lanes run along `inner` ------------
@@ -216,6 +237,86 @@ __global__ __launch_bounds__(256) void pack_small_inner_kernel(
     }
 }
 
+// ---- [outer][C][inner], lanes along the channels, ballot = packed words -------
+// A wave owns 64 channels and P positions; lane l reads P consecutive positions of channel l as NV 16-byte vectors, all
+// in flight together, so the wave-wide comparison of position p IS two packed words of that position.  They are
+// collected in two registers, lane p holding position p, and leave as one 8-byte store per lane.  Five vector
+// instructions for 64 elements; biases stay in one register.  A lane's vectors cover one or two cache lines of its row,
+// which the wave's loads share in the first-level cache.  Rows start at any byte: vectors are loaded from the dword
+// below and shifted into place (MIS).  Buffer accesses: channels past the end, and what a row's last vector
+// reads past the image, are zero and not used.
+template <typename T, int NV, bool BIAS, bool MIS>
+__global__ __launch_bounds__(256) void pack_ballot_kernel(
+    const T* __restrict__ src, const float* __restrict__ bias, int channels, int src_channels, int inner, int cw,
+    int groups, int tiles, int tw_shift, int64_t blocks_per_image, uint32_t* __restrict__ dst)
+{
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    constexpr int ESZ = (int)sizeof(T);
+    constexpr int PER = 16 / ESZ, P = NV * PER;
+    static_assert(P <= 64, "a lane per position");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // a block's waves: 1 << tw_shift neighbouring tiles (their rows share cache lines) x the rest along the channels
+    const int tw = 1 << tw_shift, gw = 4 >> tw_shift;
+    const int64_t a = (uint32_t)blockIdx.x / (uint32_t)blocks_per_image;
+    const int at = (int)(blockIdx.x - (uint32_t)a * (uint32_t)blocks_per_image);
+    const int gblocks = (groups + gw - 1) >> (2 - tw_shift);
+    const int tb = at / gblocks;
+    const int tile = tb * tw + (wave & (tw - 1)), g = (at - tb * gblocks) * gw + (wave >> tw_shift);
+    if (tile >= tiles || g >= groups) return;
+    const int i0 = tile * P;
+    const int c = 64 * g + lane;
+    const bool live = c < channels;
+    const int cs = src_channels == channels ? c : (int)((uint32_t)c % (uint32_t)src_channels);
+    const int image = src_channels * inner * ESZ;            // bytes, a multiple of 4
+    const auto sres = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(src) + a * image), 0, image, 0x00020000);
+    const uint32_t byte = (uint32_t)(cs * inner + i0) * ESZ;
+    const int off = live ? (int)(byte & ~3u) : 0x7FFFFF00;   // past every buffer
+    uint32_t d[4 * NV + 1];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const v4i q = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(sres, off + 16 * k, 0, 0));
+        d[4 * k] = q[0]; d[4 * k + 1] = q[1]; d[4 * k + 2] = q[2]; d[4 * k + 3] = q[3];
+    }
+    d[4 * NV] = 0;
+    if constexpr (MIS) d[4 * NV] = __builtin_amdgcn_raw_buffer_load_b32(sres, off + 16 * NV, 0, 0);
+    float b = 0.0f;
+    if constexpr (BIAS) b = bias[live ? c : 0];
+    const uint64_t valid = __ballot(live);
+    uint32_t lo = 0, hi = 0;
+    static_for<4 * NV>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        const uint32_t w = MIS ? __builtin_amdgcn_alignbyte(d[k + 1], d[k], byte) : d[k];
+        static_for<4 / ESZ>([&](auto ec) {
+            constexpr int e = decltype(ec)::value;
+            bool on;
+            if constexpr (ESZ == 4) {
+                const float v = __builtin_bit_cast(float, w);
+                on = (BIAS ? v + b : v) >= 0.0f;
+            } else if constexpr (ESZ == 1) {
+                const int v = __builtin_amdgcn_sbfe((int)w, 8 * e, 8);
+                on = BIAS ? (float)v + b >= 0.0f : v >= 0;
+            } else {
+                const T h = __builtin_bit_cast(T, (uint16_t)(w >> (16 * e)));
+                on = (BIAS ? (float)h + b : (float)h) >= 0.0f;
+            }
+            const uint64_t mask = __ballot(on) & valid;
+            lo = writelane<k * (4 / ESZ) + e>((uint32_t)mask, lo);
+            hi = writelane<k * (4 / ESZ) + e>((uint32_t)(mask >> 32), hi);
+        });
+    });
+    // lane p: the two words of position i0 + p
+    const int here = inner - i0 < P ? inner - i0 : P;
+    const auto dres = __builtin_amdgcn_make_buffer_rsrc(dst + (a * inner + i0) * cw, 0, here * cw * 4, 0x00020000);
+    const uint32_t to = lane < here ? (uint32_t)(lane * cw + 2 * g) * 4u : 0x7FFFFF00u;
+    if (2 * g + 1 < cw) {
+        typedef int v2i __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(v2i{(int)lo, (int)hi}, dres, (int)to, 0, 0);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b32((int)lo, dres, (int)to, 0, 0);
+    }
+}
+
 // ---- inner == 1 (channel-last rows): lanes run along the channels ----------
 // One wave per (row, 64-channel group); the wave-wide ballot IS the two packed
 // words.  Reads are perfectly coalesced.  ROWS rows are handled per wave so
@@ -357,6 +458,37 @@ __global__ __launch_bounds__(256) void pack_generic_kernel(
     dst[t] = word;
 }
 
+// Whether and how pack_ballot_kernel takes a call (nv = 0: it does not).  Timed on rotating buffers beyond the
+// last-level cache: rows of up to 128 bytes (bfloat16, 1024 channels, 256 maps of 7 x 7 12.2 -> 9.5 us; float weights,
+// 1024 x 1024 x 3 x 3 18.4 -> 9.5), launches that do not fill the chip (float, 64 channels, one 14 x 14 map 2.6 -> 2.3).  Longer
+// rows of large launches stream better with the lanes along the positions (float, 256 channels, 64 maps of 56 x 56 39 us
+// against 48, although from cache this kernel is ahead there, 32 against 37).
+struct BallotPlan { int nv, tw_shift, groups, tiles; int64_t blocks_per_image; };
+BallotPlan plan_ballot(int esz, const void* src, int64_t outer, int64_t channels, int64_t src_channels, int64_t inner)
+{
+    BallotPlan p{};
+    const int64_t row = inner * esz;
+    // images a whole number of dwords apart, addressable by 31-bit offsets
+    if (inner < 2 || (src_channels * row) % 4 != 0 || (reinterpret_cast<uintptr_t>(src) & 3) != 0 || src_channels * row >= (1ll << 30) ||
+        channels >= (1 << 24) || inner * ((channels + 31) / 32) >= (1 << 28))
+        return p;
+    const int per = 16 / esz;                                // elements of a vector
+    const int64_t fit = (inner + per - 1) / per;             // vectors of a row
+    p.groups = (int)((channels + 63) / 64);
+    auto tiles = [&](int nv) { return (inner + nv * per - 1) / (nv * per); };
+    const bool whole_rows = fit <= (esz == 1 ? 4 : 8);
+    // a wave takes whole rows (of at most 64 positions), or a few vectors of them where the launch is small
+    p.nv = !whole_rows ? 4 : fit <= 1 ? 1 : fit <= 2 ? 2 : fit <= 4 ? 4 : 8;
+    if (!whole_rows && outer * p.groups * tiles(4) >= 2048) { p.nv = 0; return p; }
+    while (p.nv > 1 && outer * p.groups * tiles(p.nv) < 2048) p.nv /= 2;
+    p.tiles = (int)tiles(p.nv);
+    p.tw_shift = p.tiles < 2 ? 0 : p.tiles < 3 ? 1 : 2;     // neighbouring tiles share cache lines
+    const int gw = 4 >> p.tw_shift;
+    p.blocks_per_image = (int64_t)((p.tiles + (1 << p.tw_shift) - 1) >> p.tw_shift) * ((p.groups + gw - 1) / gw);
+    if (p.blocks_per_image * outer > 0x7FFFFFFF) p.nv = 0;
+    return p;
+}
+
 template <typename T, bool BIAS, bool REP>
 hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t channels,
                          int64_t src_channels, int64_t inner, uint32_t* dst, hipStream_t stream)
@@ -374,6 +506,26 @@ hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t
         const int64_t blocks = (waves + 3) / 4;
         hipLaunchKernelGGL((pack_rows_kernel<T, ROWS, BIAS, REP>), dim3((unsigned)blocks), dim3(256), 0, stream,
                            src, bias, outer, channels, src_channels, cw, dst);
+    } else if (const BallotPlan plan = plan_ballot((int)sizeof(T), src, outer, channels, src_channels, inner); plan.nv) {
+        const bool mis = (inner * (int64_t)sizeof(T)) % 4 != 0;
+        auto go = [&](auto nv) {
+            constexpr int N = decltype(nv)::value;
+            if constexpr (N * 16 / (int)sizeof(T) <= 64) {
+                const dim3 grid((unsigned)(plan.blocks_per_image * outer));
+                auto launch = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, src, bias, (int)channels, (int)src_channels, (int)inner,
+                                       (int)cw, plan.groups, plan.tiles, plan.tw_shift, plan.blocks_per_image, dst);
+                };
+                if (mis) launch(pack_ballot_kernel<T, N, BIAS, true>);
+                else launch(pack_ballot_kernel<T, N, BIAS, false>);
+            }
+        };
+        switch (plan.nv) {
+            case 1: go(std::integral_constant<int, 1>{}); break;
+            case 2: go(std::integral_constant<int, 2>{}); break;
+            case 4: go(std::integral_constant<int, 4>{}); break;
+            default: go(std::integral_constant<int, 8>{}); break;
+        }
     } else if (std::is_same<T, float>::value && inner >= 64 && inner % 4 == 0 && outer * (inner / 4) >= 64 * 128 &&
                (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
         // (from 128 blocks on; smaller inputs spread better over the chip with one pixel per thread)
