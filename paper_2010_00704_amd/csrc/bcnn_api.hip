@@ -64,7 +64,7 @@ int conv_entry(const bcnn_conv_desc* desc, const uint32_t* x, const uint32_t* w,
             // measured (7 to 1024 input channels, 25 to 430 000 pixels); those take what is left, tensors
             // beyond 31-bit offsets and sums beyond fp32.
             const bool staged = conv_mfma_fp4_supported(s, x, w);
-            const int tile = conv_mfma_direct_supported(s) ? conv_mfma_direct_choose(s, false, staged) : DIRECT_NONE;
+            const int tile = conv_mfma_direct_supported(s) ? conv_mfma_direct_choose(s, fused ? KIND_BITS_OUT : KIND_SUMS_OUT, staged) : DIRECT_NONE;
             if (tile != DIRECT_NONE)
                 e = launch_conv_mfma_direct(s, x, w, fused ? thr : nullptr, out, nullptr, tile, st);
             else if (staged)
@@ -353,7 +353,7 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
                 break;
             }
             const bool plain = mfma_ok && s.c_out % 128 == 0 && m.identity && m.r && m.x_next && m.id_channels % 4 == 0;
-            const int tile = bcnn::conv_mfma_direct_supported(s) ? bcnn::conv_mfma_direct_choose(s, true, plain) : bcnn::DIRECT_NONE;
+            const int tile = bcnn::conv_mfma_direct_supported(s) ? bcnn::conv_mfma_direct_choose(s, bcnn::KIND_MODULE_OUT, plain) : bcnn::DIRECT_NONE;
             if (tile != bcnn::DIRECT_NONE)
                 e = bcnn::launch_conv_mfma_direct(s, x_packed, w_packed, nullptr, nullptr, &m, tile, st);
             else if (mfma_ok)

@@ -47,7 +47,7 @@ bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b)
 {
     const int64_t w_bytes = (int64_t)s.c_out * b.branches * s.cw * 4;
     // a branch's sum (K padded to an even number of words) stays exact in fp32; 31-bit byte offsets
-    return b.branches <= MAX_BRANCHES && ((int64_t)s.cw + 1) * 32 < (1 << 22) && branch_x_bytes(s, b) < (1ll << 31) && w_bytes < (1ll << 31);
+    return b.branches <= MAX_BRANCHES && s.c_out <= (1 << 20) && ((int64_t)s.cw + 1) * 32 < (1 << 22) && branch_x_bytes(s, b) < (1ll << 31) && w_bytes < (1ll << 31);
 }
 
 // Estimated time of a tile in microseconds, as for the plain convolution: a launch, a wave's chain of groups of four
@@ -56,9 +56,9 @@ bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b)
 struct BranchCost { double fixed, group, wave, wave_group; };
 struct BranchTile { int tile, cb, pb; BranchCost plain, tail; };
 static const BranchTile BRANCH_TILES[] = {
-    {DIRECT_1x1, 1, 1, {2.85, 0.429, 0.184, 0.173}, {4.06, 0.354, 1.109, 0.201}},
-    {DIRECT_2x1, 2, 1, {3.76, 0.598, 0.663, 0.250}, {6.30, 0.472, 1.858, 0.342}},
-    {DIRECT_2x2, 2, 2, {4.67, 0.733, 1.933, 0.322}, {9.60, 0.644, 2.979, 0.491}},
+    {DIRECT_1x1, 1, 1, {2.88, 0.421, 0.188, 0.165}, {3.97, 0.363, 0.984, 0.176}},
+    {DIRECT_2x1, 2, 1, {3.76, 0.586, 0.696, 0.233}, {5.98, 0.461, 1.685, 0.311}},
+    {DIRECT_2x2, 2, 2, {4.53, 0.722, 1.791, 0.311}, {7.20, 0.708, 3.077, 0.457}},
 };
 
 int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b)

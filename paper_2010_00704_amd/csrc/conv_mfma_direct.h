@@ -9,9 +9,10 @@ namespace bcnn {
 enum { DIRECT_NONE = 0, DIRECT_1x1_K4, DIRECT_2x2_K4, DIRECT_2x1, DIRECT_1x1, DIRECT_2x2 };
 
 bool conv_mfma_direct_supported(const ConvShape& s);
-// The tile with the least estimated time; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the call)
+// The tile with the least estimated time for an output of that kind; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the call)
 // and that kernel is estimated to be faster.
-int conv_mfma_direct_choose(const ConvShape& s, bool module, bool staged);
+enum { KIND_BITS_OUT = 0, KIND_SUMS_OUT = 1, KIND_MODULE_OUT = 2 };
+int conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged);
 // thr == nullptr: int32 sums, else packed bits; ep != nullptr: module epilogue (thr and out are ignored)
 hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream);

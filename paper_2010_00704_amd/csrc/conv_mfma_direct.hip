@@ -43,29 +43,29 @@ bool conv_mfma_direct_supported(const ConvShape& s)
     const int64_t x_bytes = (int64_t)s.n * s.h * s.w * s.cw * 4;
     const int64_t w_bytes = (int64_t)s.c_out * n_words * 4;
     // fp32 sums stay exact (the K axis is padded to at most four words per tap and a chunk); 31-bit byte offsets
-    return (n_words + 3 * s.ks * s.ks + 8) * 32 < (1 << 22) && x_bytes < (1ll << 31) && w_bytes < (1ll << 31);
+    // (c_out bound: a wave's rows of an output tensor by 31-bit offsets)
+    return s.c_out <= (1 << 20) && (n_words + 3 * s.ks * s.ks + 8) * 32 < (1 << 22) && x_bytes < (1ll << 31) && w_bytes < (1ll << 31);
 }
 
 // What a tile of this kernel costs, in microseconds: a launch with its latencies, a wave's chain of chunks, a
 // wave's set-up and epilogue and its chunks where more waves than SIMDs (1024) share the issue slots.  The four
-// numbers of each tile are least-squares fits over 163 measured launches (graph replays; 1x1 and 3x3, strides 1 and
-// 2, 7 to 1024 input and 32 to 1024 output channels, 25 to 430 000 pixels, sums and bits; rms error 11 to 16 %);
-// choosing by them costs 1 % over the best of the tiles on average and 20 % at worst.
+// numbers of each tile and kind of output are least-squares fits over 158 measured launches (graph replays, outputs on
+// rotating buffers; 1x1 and 3x3, strides 1 and 2, 32 to 1024 channels on both sides, 25 to 430 000 pixels; rms error 8 to
+// 15 %); choosing by them costs 1 % over the best of the tiles on average and 20 % at worst.
 struct Cost { double fixed, chunk, wave, wave_chunk; };
-struct TileCost { int tile, cb, pb, wc, wp, wk; Cost plain, module; };
-// (module calls: 63 launches of 1x1 and 3x3 modules, 32 to 845 channels, all three stream types; rms 13 to 17 %,
-// the choice 0.5 % over the best)
+struct TileCost { int tile, cb, pb, wc, wp, wk; Cost kind[3]; };     // kind: packed bits, int32 sums, module
 static const TileCost TILES[] = {
-    {DIRECT_1x1_K4, 1, 1, 1, 1, 4, {2.55, 0.182, 0.129, 0.166}, {2.98, 0.000, 0.643, 0.133}},
-    {DIRECT_2x2_K4, 2, 2, 1, 1, 4, {3.45, 0.450, 0.974, 0.330}, {4.08, 0.243, 2.080, 0.373}},
-    {DIRECT_2x1, 2, 1, 1, 4, 1, {3.48, 0.308, 0.697, 0.205}, {5.30, 0.229, 2.360, 0.256}},
-    {DIRECT_1x1, 1, 1, 1, 4, 1, {2.97, 0.199, 0.404, 0.144}, {3.88, 0.147, 1.350, 0.155}},
+    {DIRECT_1x1_K4, 1, 1, 1, 1, 4, {{2.49, 0.132, 0.050, 0.184}, {2.52, 0.144, 0.136, 0.151}, {2.77, 0.190, 0.267, 0.181}}},
+    {DIRECT_2x2_K4, 2, 2, 1, 1, 4, {{2.89, 0.413, 0.587, 0.372}, {2.78, 0.500, 0.900, 0.306}, {3.80, 0.356, 1.403, 0.383}}},
+    {DIRECT_2x1, 2, 1, 1, 4, 1, {{2.74, 0.299, 0.455, 0.215}, {2.83, 0.319, 1.039, 0.178}, {4.70, 0.289, 1.602, 0.215}}},
+    {DIRECT_1x1, 1, 1, 1, 4, 1, {{2.63, 0.180, 0.238, 0.154}, {2.66, 0.209, 0.513, 0.130}, {3.68, 0.180, 0.790, 0.162}}},
 };
-// The same for the staged kernel's 2 x 4 tile (83 launches, C_in a multiple of 128, rms 16 %; module calls: its plain
-// form, 18 launches, rms 13 %): workgroups of 128 channels x 256 pixels against 256 compute units.
-static double staged_cost(const ConvShape& s, bool module)
+// The same for the staged kernel's 2 x 4 tile (99 launches, C_in a multiple of 128, module calls in its plain form; rms 8,
+// 20 and 10 %): workgroups of 128 channels x 256 pixels against 256 compute units.
+static double staged_cost(const ConvShape& s, int kind)
 {
-    const Cost c = module ? Cost{7.13, 0.772, 7.54, 0.279} : Cost{3.97, 0.597, 2.12, 0.227};
+    static const Cost KINDS[] = {{3.54, 0.594, 1.71, 0.191}, {6.00, 0.587, 5.08, 0.025}, {8.01, 0.575, 7.43, 0.165}};
+    const Cost& c = KINDS[kind];
     const double chunks = (double)((s.ks * s.ks * (s.cw / 4) + 1) / 2);
     const double wgs = (double)((s.m + 255) / 256) * (double)((s.c_out + 127) / 128);
     return c.fixed + c.chunk * chunks + (c.wave + c.wave_chunk * chunks) * wgs / 256.0;
@@ -78,17 +78,17 @@ static int direct_units(const ConvShape& s)
     return s.cw < 4 ? (taps * s.cw + 3) / 4 : taps * ((s.cw + 3) / 4);
 }
 
-int conv_mfma_direct_choose(const ConvShape& s, bool module, bool staged)
+int conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged)
 {
     const int chunks = (direct_units(s) + 1) / 2;
     int best = 0;
-    double least = staged ? staged_cost(s, module) : 1e30;
+    double least = staged ? staged_cost(s, kind) : 1e30;
     for (const TileCost& t : TILES) {
         const double wgs = (double)((s.m + 32 * t.pb * t.wp - 1) / (32 * t.pb * t.wp)) *
                            (double)((s.c_out + 32 * t.cb * t.wc - 1) / (32 * t.cb * t.wc));
         const double waves = wgs * t.wc * t.wp * t.wk / 1024.0;
         const double mine = (double)((chunks + t.wk - 1) / t.wk);
-        const Cost& c = module ? t.module : t.plain;
+        const Cost& c = t.kind[kind];
         const double cost = c.fixed + c.chunk * mine + (c.wave + c.wave_chunk * mine) * waves;
         if (cost < least) { least = cost; best = t.tile; }
     }

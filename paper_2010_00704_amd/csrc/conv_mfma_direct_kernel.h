@@ -23,6 +23,8 @@
 // 7 x 7 11.5 -> 7.5.  At least two workgroups of a SIMD are asked for in the launch bounds: without that the compiler
 // keeps the accumulators in the accumulation registers and copies them (2 x 1 blocks: 84 registers a lane instead of
 // 96, the first two calls above 5.1 -> 4.9 and 11.3 -> 10.1, the third 4.4 -> 2.9).
+// Buffer accesses in the epilogue instead of predicated ones: float module, 1x1, 256 channels, 32 maps of 56 x 56 (1 x 1
+// blocks) 39.3 -> 33.2, half, 64 channels, 112 x 112 30.9 -> 24.8; sums, 1x1, 256 -> 256, 32 maps of 56 x 56 19.3 (staged 22.5).
 // Branch mode, 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 us in the staged kernel, 33 here (a tap's fold
 // there exchanges its corrections through LDS and costs more than the tap's matrix work); 512 channels, 64 maps of
 // 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.
@@ -167,17 +169,33 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
     bool vec = false;
     real4 ids[MODULE ? GROUPS : 1];
     const int id0 = MODULE ? c0 % (ep.id_channels > 0 ? ep.id_channels : 1) : 0;
+    // Output tensors (and the identity) are raw buffers per wave tile: base = the row of the tile's first pixel, size =
+    // its rows that exist.  Rows past the end read zeros and store nothing, and so does a lane without channels, whose
+    // offset is past every size: no predicates between the accesses.
+    constexpr uint32_t NOWHERE = 0x7FFFFF00u;
+    const bool chan_ok = some && c0 < s.c_out;
+    auto rows_of = [&](const void* base, int row_bytes) {
+        int rows = s.m - m0;
+        rows = rows < 0 ? 0 : (rows > TPX ? TPX : rows);
+        const uint64_t at = reinterpret_cast<uint64_t>(base) + (uint64_t)m0 * (uint64_t)row_bytes;
+        const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+        const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>((hi << 32) | lo), 0,
+                                                 __builtin_amdgcn_readfirstlane(base ? rows * row_bytes : 0), 0x00020000);
+    };
+    constexpr int ESZ = (int)sizeof(real_t);
     if constexpr (MODULE) {
         const uintptr_t both = reinterpret_cast<uintptr_t>(ep.r) | reinterpret_cast<uintptr_t>(ep.identity);
-        vec = ep.identity && ep.r && ep.x_next && s.c_out % 4 == 0 && ep.id_channels % 4 == 0 && (both & (HALF ? 7 : 15)) == 0;
+        vec = ep.identity && ep.r && ep.x_next && s.c_out % 4 == 0 && ep.id_channels % 4 == 0 && (both & 3) == 0;
         if (vec) {
+            const int row_bytes = ep.id_channels * ESZ;
+            const auto res = rows_of(ep.identity, row_bytes);
+            const uint32_t off = chan_ok ? (uint32_t)(px0 * row_bytes + id0 * ESZ) : NOWHERE;
 #pragma unroll
             for (int g = 0; g < GROUPS; ++g) {
-                const int m = m0 + px0 + g * PX_STEP;
-                ids[g] = real4{(real_t)0, (real_t)0, (real_t)0, (real_t)0};
-                if (some && m < s.m && c0 < s.c_out)
-                    ids[g] = __builtin_nontemporal_load(reinterpret_cast<const real4*>(
-                        static_cast<const real_t*>(ep.identity) + (size_t)m * ep.id_channels + id0));
+                const int at = (int)(off + (uint32_t)(g * PX_STEP * row_bytes));
+                if constexpr (HALF) ids[g] = __builtin_bit_cast(real4, __builtin_amdgcn_raw_buffer_load_b64(res, at, 0, 0));
+                else ids[g] = __builtin_bit_cast(real4, __builtin_amdgcn_raw_buffer_load_b128(res, at, 0, 0));
             }
         }
     }
@@ -430,24 +448,30 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             for (int k = 0; k < 4; ++k) pa[k] = 1.0f;
         }
     }
-    const bool out_vec = OUT == OUT_I32 && s.c_out % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-    // four sums (still with the constant z) of pixel m, channels c0 ..; every lane of the wave calls it
-    auto emit = [&](v4f v, int m, bool ok, int g) {
-        const int nch = s.c_out - c0;                        // real channels from c0 on (may be <= 0)
+    const int nch = s.c_out - c0;                            // real channels from c0 on (may be <= 0)
+    const int out_row = (OUT == OUT_I32 ? s.c_out : OUT == OUT_BITS ? s.cwo : 0) * 4;
+    const auto out_res = rows_of(MODULE ? nullptr : out, out_row);
+    const int r_row = s.c_out * ESZ, xn_row = s.cwo * 4;
+    const auto r_res = rows_of(MODULE ? ep.r : nullptr, r_row);
+    const auto xn_res = rows_of(MODULE ? ep.x_next : nullptr, xn_row);
+    const uint32_t word_off = chan_ok && (lane & 7) == 0 ? (uint32_t)(c0 >> 5) * 4u : NOWHERE;
+    // four sums (still with the constant z) of the tile's pixel px, channels c0 ..; every lane of the wave calls it
+    auto emit = [&](v4f v, int px, int g) {
         uint32_t nib = 0;
         if constexpr (OUT == OUT_I32) {
-            int32_t* y = static_cast<int32_t*>(out) + (size_t)m * s.c_out + c0;
             v4i q;
             if constexpr (BR) q = __builtin_bit_cast(v4i, v);
             else q = v4i{(int)(v[0] - zf), (int)(v[1] - zf), (int)(v[2] - zf), (int)(v[3] - zf)};
-            if (ok && nch > 0) {
-                if (out_vec) {
-                    __builtin_nontemporal_store(q, reinterpret_cast<v4i*>(y));
-                } else {
+            const uint32_t at = (uint32_t)(px * out_row + c0 * 4);
+            // whole groups of four, non-temporal (aux 2) where a block's 32 channels are whole cache lines; written that
+            // way, partial lines cost twice (1x1, 128 -> 100 on 200 704 pixels 35 us against 16)
+            const int off = (int)(chan_ok && nch >= 4 ? at : NOWHERE);
+            if (s.c_out % 32 == 0) __builtin_amdgcn_raw_buffer_store_b128(q, out_res, off, 0, 2);
+            else __builtin_amdgcn_raw_buffer_store_b128(q, out_res, off, 0, 0);
+            if (s.c_out % 4 != 0) {                          // the row's last group
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (k < nch) y[k] = q[k];
-                }
+                for (int k = 0; k < 3; ++k)
+                    __builtin_amdgcn_raw_buffer_store_b32(q[k], out_res, (int)(chan_ok && nch < 4 && k < nch ? at + 4 * k : NOWHERE), 0, 0);
             }
             return;
         } else if constexpr (OUT == OUT_BITS) {
@@ -457,7 +481,8 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
                 else nib |= (uint32_t)(k < nch && (int)(v[k] - zf) >= th[k]) << k;
             }
         } else {
-            real_t* rp = static_cast<real_t*>(ep.r) + (size_t)m * s.c_out + c0;
+            const int m = m0 + px;
+            const bool ok = some && m < s.m;
             real4 id = ids[g];
             if (!vec) {
                 const real_t* idrow = static_cast<const real_t*>(ep.identity) + (size_t)m * ep.id_channels;
@@ -473,14 +498,15 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
                 nib |= (uint32_t)(k < nch && val + pc[k] >= 0.0f) << k;
                 st[k] = (real_t)val;
             }
-            if (ok && nch > 0) {
-                if (vec) {
-                    *reinterpret_cast<real4*>(rp) = st;
-                } else if (ep.r) {
+            if (vec) {
+                const int at = (int)(chan_ok ? (uint32_t)(px * r_row + c0 * ESZ) : NOWHERE);
+                if constexpr (HALF) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, st), r_res, at, 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, st), r_res, at, 0, 0);
+            } else if (ok && ep.r) {
+                real_t* rp = static_cast<real_t*>(ep.r) + (size_t)m * s.c_out + c0;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (k < nch) rp[k] = st[k];
-                }
+                for (int k = 0; k < 4; ++k)
+                    if (k < nch) rp[k] = st[k];
             }
         }
         // eight neighbouring lanes hold the 32 channels of one packed word
@@ -488,8 +514,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
         wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
         wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
         wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0x141, 0xF, 0xF, true);  // row_half_mirror
-        uint32_t* yp = MODULE ? ep.x_next : static_cast<uint32_t*>(out);
-        if (ok && nch > 0 && (lane & 7) == 0 && (!MODULE || yp)) yp[(size_t)m * s.cwo + (c0 >> 5)] = wd;
+        __builtin_amdgcn_raw_buffer_store_b32((int)wd, MODULE ? xn_res : out_res, (int)(word_off + (uint32_t)(px * xn_row)), 0, 0);
     };
     if constexpr (WK > 1) {
 #pragma unroll
@@ -504,7 +529,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
                 for (int k = 0; k < WK; ++k)
                     sum += *reinterpret_cast<const v4f*>(region + k * REGION + px * ROW + 4 * (lt % CG));
             }
-            emit(sum, m0 + px, some && m0 + px < s.m, g);
+            emit(sum, px, g);
         }
     } else {
         // same wave wrote and reads: LDS operations of a wave complete in order
@@ -516,8 +541,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             for (int g = 0; g < GROUPS / PB; ++g) {
                 const int px = px0 + g * PX_STEP;
                 const v4f sum = *reinterpret_cast<const v4f*>(region + px * ROW + 4 * (lt % CG));
-                const int m = m0 + 32 * pb + px;
-                emit(sum, m, m < s.m, pb * (GROUPS / PB) + g);
+                emit(sum, 32 * pb + px, pb * (GROUPS / PB) + g);
             }
             __builtin_amdgcn_wave_barrier();
         }

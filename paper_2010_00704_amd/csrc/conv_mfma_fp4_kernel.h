@@ -1229,7 +1229,11 @@ __device__ __forceinline__ void conv_mfma_fp4_tile(
                     // channels past c_out (offsets set past every size) are dropped by the bounds check
                     const uint32_t row_off = (uint32_t)((32 * pb + 4 * g) * s.c_out * 4);
                     if (vec_ok) {
-                        __builtin_amdgcn_raw_buffer_store_b128(v4i{q.x, q.y, q.z, q.w}, y_res, (int)(y_off[0] + row_off), 0, 2);
+                        // non-temporal (aux 2) where 32 channels are whole cache lines: partial lines cost twice that way
+                        if (s.c_out % 32 == 0)
+                            __builtin_amdgcn_raw_buffer_store_b128(v4i{q.x, q.y, q.z, q.w}, y_res, (int)(y_off[0] + row_off), 0, 2);
+                        else
+                            __builtin_amdgcn_raw_buffer_store_b128(v4i{q.x, q.y, q.z, q.w}, y_res, (int)(y_off[0] + row_off), 0, 0);
                     } else {
                         __builtin_amdgcn_raw_buffer_store_b32(q.x, y_res, (int)(y_off[0] + row_off), 0, 2);
                         __builtin_amdgcn_raw_buffer_store_b32(q.y, y_res, (int)(y_off[1] + row_off), 0, 2);
