@@ -63,7 +63,7 @@ static const BranchTile BRANCH_TILES[] = {
 
 int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b)
 {
-    const double groups = (double)b.branches * (double)(((s.cw + 1) / 2 + 3) / 4);
+    const double groups = (double)b.branches * (double)BranchWalk::make(s.cw).groups();
     int best = DIRECT_1x1;
     double least = 1e30;
     for (const BranchTile& t : BRANCH_TILES) {
@@ -83,8 +83,7 @@ hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, 
     a.s = s;
     a.taps = b.branches;
     a.n_words = b.branches * s.cw;
-    a.half_words = (s.cw + 1) / 2;
-    a.z = 64 * a.half_words - s.k / (s.ks * s.ks);           // of one branch
+    a.z = 64 * BranchWalk::make(s.cw).half_words - s.k / (s.ks * s.ks);   // of one branch
     a.x_bytes = (int32_t)branch_x_bytes(s, b);
     a.w_bytes = (int32_t)((int64_t)s.c_out * a.n_words * 4);
     a.pad_bytes = a.n_words * 4;

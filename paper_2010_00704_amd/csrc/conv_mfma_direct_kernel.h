@@ -30,6 +30,7 @@
 // 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.
 #pragma once
 #include "bcnn_common.h"
+#include "branch_walk.h"
 #include "div_by.h"
 
 #include <type_traits>
@@ -49,7 +50,6 @@ struct DirectArgs {
     DivBy div_ct, div_hw, div_wo, div_tap;
     // branch mode
     int32_t taps;            // branches
-    int32_t half_words;      // ceil(cw / 2): lane half h walks the words h * half_words .. of every tap
     int32_t tap_step;        // words between the branches' input tensors
     int32_t pad_bytes, scale_bytes;
 };
@@ -316,22 +316,21 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             }
         }
     } else {
-        // A tap's words are split between the lane halves (half h: words h * half_words ..) and walked in groups
-        // of four words = four K-steps with one 16-byte load per row; what is left of the half (half_words mod 4)
-        // is a group of single words.  Every load is wave-uniform but for the rows' offsets and their validity.
+        // A tap's words are split between the lane halves and walked in groups of four words = four K-steps with one
+        // 16-byte load per row; the last group is single words (branch_walk.h).  Every load is wave-uniform but for the
+        // rows' offsets and their validity.
         // The accumulators start a tap at minus the positions that are zero on both sides, so that the tap's sum
         // needs no correction: a completed tap costs one fma per element, tot = fma(scale, y_t, tot) in the order
         // t = 0, 1, ... (the chain is part of the interface), and one move to restart.
-        const int full = a.half_words >> 2, rest = a.half_words & 3;
-        const int per_tap = full + (rest != 0);
+        const BranchWalk walk = BranchWalk::make(s.cw);
+        const int per_tap = walk.groups();
         const float start = (float)-a.z;                     // a.z: of one tap
         const auto pres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(br.pad_words), 0, PAD == PAD_OPERAND ? a.pad_bytes : 0, 0x00020000);
-        const int half0 = hsel * a.half_words;
         auto fetch_group = [&](int tap, int g, Chunk& c) {
-            const int k = half0 + 4 * g;                     // first word within the tap
+            const int k = walk.first(hsel, g);               // first word within the tap
             const int wo = tap * s.cw + k;
             const int xo = k + tap * a.tap_step + (s.ks == 3 ? tap * s.cw + ((tap >= 3) + (tap >= 6)) * a.row_jump : 0);
-            if (g < full) {
+            if (g < walk.full) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
                     c.w[cb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wres, (wrow[cb] + wo) * 4, 0, 0));
@@ -346,9 +345,9 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
                 }
             } else {
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    if (i >= rest) break;
-                    const bool real = k + i < s.cw;          // an odd count leaves the second half one word short
+                for (int i = 0; i < 4; ++i) {
+                    if (i >= walk.rest) break;
+                    const bool real = walk.real(k + i);      // an odd count leaves the second half one word short
 #pragma unroll
                     for (int cb = 0; cb < CB; ++cb)
                         c.w[cb][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(wres, real ? (wrow[cb] + wo + i) * 4 : -4, 0, 0);
@@ -388,7 +387,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             for (int g = 0; g < per_tap; ++g) {
                 const bool more = g + 1 < per_tap;
                 if (more || tap + 1 < a.taps) fetch_group(more ? tap : tap + 1, more ? g + 1 : 0, nxt);
-                multiply(cur, g < full ? 4 : rest);
+                multiply(cur, walk.steps(g));
                 cur = nxt;
             }
 #pragma unroll

@@ -1,6 +1,8 @@
 """Branch sums on the matrix cores without LDS staging, through the calls that AUTO routes to it, against the oracle:
 words per lane half around a group of four (single words, whole groups, both), odd word counts, every pad mode, own and
 shared tensors, the three tiles, ragged channels and pixels, operands at 4-byte alignment."""
+import random
+
 import numpy as np
 import pytest
 import torch
@@ -21,6 +23,14 @@ SHAPES = [
     (2, 288, 5, 7, 64, 1, 1, 4, False),      # nine: a group and a single word, odd
     (1, 352, 7, 7, 65, 3, 1, 9, True),       # eleven
     (1, 512, 8, 8, 32, 1, 2, 16, True),      # two groups, the most branches that are kept in LDS
+    # an odd count whose longer half is whole groups of four: the shorter half is a word short in its last group
+    (1, 193, 4, 5, 33, 3, 1, 9, False),      # seven
+    (2, 224, 7, 6, 40, 3, 2, 9, True),       # seven, odd map under stride 2
+    (1, 224, 5, 9, 64, 1, 1, 3, True),       # seven, parallel branches
+    (2, 224, 6, 4, 36, 1, 1, 2, False),      # seven, parallel branches of one tensor
+    (1, 480, 6, 7, 70, 3, 1, 9, False),      # fifteen
+    (1, 736, 5, 5, 32, 3, 1, 9, True),       # twenty-three
+    (3, 992, 3, 4, 96, 1, 1, 4, True),       # thirty-one
     (60, 128, 28, 28, 96, 3, 1, 9, False),   # two channel blocks per wave
     (20, 512, 28, 28, 288, 1, 1, 3, False),  # 2 x 2 blocks per wave, ragged last channel tile
 ]
@@ -38,9 +48,23 @@ def as_bytes(a, dev):
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("mode", ["minus", "words", "zero"])
 def test_branches_direct(dev, shape, mode):
+    check(dev, shape, mode, 61000 + 13 * shape[1] + shape[2])
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_random_channel_counts(dev, seed):
+    """Any channel count up to 1024 on small maps: every word count of a tap is as likely as another."""
+    rng = random.Random(62000 + seed)
+    for _ in range(4):
+        k = rng.choice([1, 3])
+        shape = (rng.randint(1, 3), rng.randint(1, 1024), rng.randint(3, 9), rng.randint(3, 9), rng.randint(32, 100), k,
+                 rng.choice([1, 1, 2]), 9 if k == 3 else rng.randint(1, 5), rng.random() < 0.4)
+        check(dev, shape, rng.choice(["minus", "words", "zero"]), rng.randrange(1 << 20))
+
+
+def check(dev, shape, mode, seed):
     n, c, h, w, o, k, stride, taps, own = shape
     pad = (k - 1) // 2
-    seed = 61000 + 13 * c + h
     xs = [W.pm1(seed + 20 + t, (n, c, h, w), 0.5) for t in range(taps if own else 1)]
     wt = W.pm1(seed, (o, c, taps))
     scale, bias = W.uniform_f32(seed + 1, (taps, o), -0.4, 0.4), W.uniform_f32(seed + 2, (o,), -3.0, 3.0)
