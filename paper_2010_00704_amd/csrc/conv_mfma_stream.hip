@@ -16,8 +16,7 @@
 //   - Parameters are vector loads through buffers (a missing one is a buffer of no bytes): scalar loads under branches
 //     cost more than the rest of a wave (28.6 against 22.9 us).
 //   - One block per wave: walking two or four with the next one's operands in flight was slower at 55 of 64 shapes.
-//   - Real-valued chain: the interface's order, one rounding per step; a bit enters its word as the carry of an
-//     addition (two instructions with its comparison).
+//   - Real-valued chain: the interface's order, one rounding per step.
 // The plain case only (every part of the module present, rows of whole 16-byte vectors); everything else takes the
 // direct kernel.
 // Measured (graph replays, us, against the kernel that ran the call before): half, 32 images: 64 channels, 112 x 112
@@ -26,6 +25,7 @@
 #include "bcnn_common.h"
 #include "conv_mfma_direct.h"
 #include "div_by.h"
+#include "sign_bits.h"
 
 #include <type_traits>
 
@@ -220,13 +220,9 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
             st[k] = (real_t)t;
             stored[k] = (float)st[k];
         }
-        uint32_t bits = 0;
 #pragma unroll
-        for (int k = PER - 1; k >= 0; --k) {
-            // bits = 2 * bits + (stored + next bias >= 0)
-            const float v = stored[k] + pc[k];
-            asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(v) : "vcc");
-        }
+        for (int k = 0; k < PER; ++k) stored[k] = stored[k] + pc[k];
+        const uint32_t bits = sign_bits(stored);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, st), r_res, (int)(r_off + (uint32_t)(g * PX_STEP * r_row)), 0, 0);
         // 32 / PER neighbouring lanes hold the 32 channels of one packed word
         uint32_t wd = (chan_ok ? bits : 0u) << (cl & 31);

@@ -6,6 +6,7 @@
 // with many of them in flight.
 #include "bcnn_common.h"
 #include "div_by.h"
+#include "sign_bits.h"
 
 #include <type_traits>
 #include <utility>
@@ -420,15 +421,14 @@ __global__ __launch_bounds__(256) void pack_last8_kernel(
 #pragma unroll
     for (int k = 0; k < PASSES; ++k) {
         uint32_t bits = 0;
+        if constexpr (ESZ == 1 && !BIAS) {
 #pragma unroll
-        for (int i = 7; i >= 0; --i) {
-            if constexpr (ESZ == 1 && !BIAS) {
-                bits = 2 * bits + (uint32_t)(v[k][i] >= 0);
-            } else {
-                // bits = 2 * bits + (value + bias >= 0), the comparison entering as the carry
-                const float f = BIAS ? (float)v[k][i] + b[i] : (float)v[k][i];
-                asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(f) : "vcc");
-            }
+            for (int i = 7; i >= 0; --i) bits = 2 * bits + (uint32_t)(v[k][i] >= 0);
+        } else {
+            float f[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[i] = BIAS ? (float)v[k][i] + b[i] : (float)v[k][i];
+            bits = sign_bits(f);
         }
         uint32_t wd = (bits & valid) << (8 * (q & 3));
         wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]

@@ -18,6 +18,7 @@
 
 #include "bcnn_common.h"
 #include "div_by.h"
+#include "sign_bits.h"
 
 namespace bcnn {
 namespace {
@@ -232,18 +233,17 @@ __global__ __launch_bounds__(256) void avgpool_pack8_kernel(const T* __restrict_
         bs[h] = w[0]; bs[h + 1] = w[1]; bs[h + 2] = w[2]; bs[h + 3] = w[3];
     }
     e8 kept;
-    uint32_t w = 0;
+    float f[8];
 #pragma unroll
-    for (int i = 7; i >= 0; --i) {
+    for (int i = 0; i < 8; ++i) {
         float acc = (float)v[0][i];
 #pragma unroll
         for (int a = 1; a < SF * SF; ++a) acc = acc + (float)v[a][i];
         const float mean = (SF == 2 || SF == 4) ? acc * (1.0f / (SF * SF)) : acc / (float)(SF * SF);
         kept[i] = (E)mean;                               // to nearest even
-        const float f = (float)kept[i] + bs[i];
-        // w = 2 * w + (f >= 0), the comparison entering as the carry
-        asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(w) : "v"(f) : "vcc");
+        f[i] = (float)kept[i] + bs[i];
     }
+    uint32_t w = sign_bits(f);
     const uint32_t px = (uint32_t)r;
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, kept), pres, (int)(live ? px * (uint32_t)row_bytes + (uint32_t)c0 * 2u : NOWHERE), 0, 0);
     w = live ? w << (8 * (q & 3)) : 0u;
