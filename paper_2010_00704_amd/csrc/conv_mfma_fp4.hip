@@ -171,7 +171,7 @@ hipError_t launch_conv_branches_mfma(const ConvShape& s, const BranchArgs& b, hi
     a.n_units = a.taps * a.units_per_tap;
     a.n_chunks = a.n_units / 2;
     a.chunks_per_tap = s.cw / 8;
-    a.z = 0;
+    a.z = 32 * s.cw - s.k / (s.ks * s.ks);      // of one branch: channels past the last one, zero on both sides
     a.x_bytes = (int32_t)branch_x_bytes(s, b);
     a.w_bytes = (int32_t)((int64_t)s.c_out * a.n_units * 16);
     // 3x3: the input offset walks on through the taps of a filter row and jumps at

@@ -559,7 +559,7 @@ __device__ __forceinline__ void conv_mfma_fp4_tile(
     // 1x1 branches), each with its own real scale per output channel (BCNN
     // paper, Section 4.2.1, last paragraph; Figure 2, bottom).  A tap's chunks
     // accumulate in `acc` as usual; when the tap is complete its exact integer
-    // sum y_t = acc - (2*pop_t(channel) - 192*chunks_per_tap) is folded into the
+    // sum y_t = acc - (2*pop_t(channel) - 192*chunks_per_tap + z) is folded into the
     // float totals, tot = fma(scale[t][channel], y_t, tot), and acc restarts at
     // zero.  pop_t are the weight-bit counts of that tap alone, exchanged
     // through LDS at every fold.  A pixel whose tap lies outside the image has
@@ -944,7 +944,7 @@ __device__ __forceinline__ void conv_mfma_fp4_tile(
     {
         int b0 = 0, b1 = STAGE_BYTES, b2 = 2 * STAGE_BYTES;   // byte offsets of the three stages
         int tap = 0, chunk_in_tap = 0, par = 0;
-        const int c_in = 256 * a.chunks_per_tap;
+        const int c_in = 256 * a.chunks_per_tap - a.z;   // branch mode: a.z channels of a tap's last word do not exist
         for (int chunk = 0; chunk < n_chunks; ++chunk) {
             if constexpr (PADMODE == 1)   // pad words of the chunk whose weights this body reads ahead
                 padq = *reinterpret_cast<const uint4*>(pad_lds + 8 * (chunk + 1) + 4 * hsel);
@@ -965,7 +965,7 @@ __device__ __forceinline__ void conv_mfma_fp4_tile(
                     const int bothp = wpad[cb] + __shfl_xor(wpad[cb], 32, 64);
                     if (hsel == 0) {          // one lane per channel turns the counts into the two terms
                         const int ch = 64 * wc + 32 * cb + row_to_channel(j);
-                        tapf_lds[par][0][ch] = (float)(2 * both - 192 * a.chunks_per_tap);
+                        tapf_lds[par][0][ch] = (float)(2 * both - 192 * a.chunks_per_tap + a.z);
                         if constexpr (PADMODE == 1) tapf_lds[par][1][ch] = (float)(c_in - 2 * bothp);
                     }
                     wpop[cb] = wnext[cb];

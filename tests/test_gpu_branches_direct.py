@@ -51,6 +51,14 @@ def test_branches_direct(dev, shape, mode):
     check(dev, shape, mode, 61000 + 13 * shape[1] + shape[2])
 
 
+@pytest.mark.parametrize("shape", [(1, 226, 5, 6, 40, 3, 1, 9, False), (2, 250, 7, 4, 130, 3, 2, 9, True), (1, 500, 6, 5, 64, 1, 1, 4, True),
+                                   (1, 737, 4, 4, 33, 3, 1, 9, False)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("mode", ["minus", "words", "zero"])
+def test_staged_branches_with_a_partial_last_word(dev, shape, mode):
+    """Channel counts short of whole 256-channel chunks on the kernel that stages its operands in LDS."""
+    check(dev, shape, mode, 63000 + 13 * shape[1] + shape[2], B.BCNN_VARIANT_MFMA_FP4)
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_channel_counts(dev, seed):
     """Any channel count up to 1024 on small maps: every word count of a tap is as likely as another."""
@@ -62,7 +70,7 @@ def test_random_channel_counts(dev, seed):
         check(dev, shape, rng.choice(["minus", "words", "zero"]), rng.randrange(1 << 20))
 
 
-def check(dev, shape, mode, seed):
+def check(dev, shape, mode, seed, variant=B.BCNN_VARIANT_AUTO):
     n, c, h, w, o, k, stride, taps, own = shape
     pad = (k - 1) // 2
     xs = [W.pm1(seed + 20 + t, (n, c, h, w), 0.5) for t in range(taps if own else 1)]
@@ -83,8 +91,8 @@ def check(dev, shape, mode, seed):
     args = (d, taps, xt.data_ptr() + 4 * off, xw.size // taps if own else 0, wtt.data_ptr() + 4 * off,
             pw if mode == "words" else None, B.BCNN_PAD_ZERO if mode == "zero" else B.BCNN_PAD_WORDS, up(scale, dev), up(bias, dev))
     zf, bits = Guarded(m * o, dev), Guarded(m * cwo, dev)
-    B.check(B.bcnn_conv2d_binary_branches(*args, zf.ptr), "branches")
-    B.check(B.bcnn_conv2d_binary_branches_sign_pack(*args, bits.ptr), "sign_pack")
+    B.check(B.bcnn_conv2d_binary_branches(*args, zf.ptr, variant), "branches")
+    B.check(B.bcnn_conv2d_binary_branches_sign_pack(*args, bits.ptr, variant), "sign_pack")
     assert np.array_equal(zf.get(np.float32).reshape(m, o), z.reshape(m, o))
     signs = np.where(z >= 0, 1, -1).astype(np.int8).reshape(m, o, 1)
     assert np.array_equal(bits.get(np.uint32).reshape(m, cwo), oracle.pack_channels(signs)[:, 0, :])
@@ -98,7 +106,7 @@ def check(dev, shape, mode, seed):
             r, xn = Guarded.of_bytes(m * o * esz, dev), Guarded(m * cwo, dev)
             B.check(B.bcnn_conv2d_binary_branches_module(
                 *args, as_bytes(ident, dev) if whole else None, up(alpha, dev) if whole else None,
-                up(nxt, dev) if whole else None, real_code(half), r.ptr, xn.ptr), "module")
+                up(nxt, dev) if whole else None, real_code(half), r.ptr, xn.ptr, variant), "module")
             t = z.reshape(m, o).astype(np.float32)
             if whole:
                 t = t + real_values(ident, half)
