@@ -6,6 +6,7 @@
 // with many of them in flight.
 #include "bcnn_common.h"
 #include "div_by.h"
+#include "pack_plan.h"
 #include "sign_bits.h"
 
 #include <type_traits>
@@ -257,14 +258,10 @@ __global__ __launch_bounds__(256) void pack_ballot_kernel(
     static_assert(P <= 64, "a lane per position");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // a block's waves: 1 << tw_shift neighbouring tiles (their rows share cache lines) x the rest along the channels
-    const int tw = 1 << tw_shift, gw = 4 >> tw_shift;
     const int64_t a = (uint32_t)blockIdx.x / (uint32_t)blocks_per_image;
     const int at = (int)(blockIdx.x - (uint32_t)a * (uint32_t)blocks_per_image);
-    const int gblocks = (groups + gw - 1) >> (2 - tw_shift);
-    const int tb = at / gblocks;
-    const int tile = tb * tw + (wave & (tw - 1)), g = (at - tb * gblocks) * gw + (wave >> tw_shift);
-    if (tile >= tiles || g >= groups) return;
+    int tile, g;
+    if (!ballot_place(at, wave, tw_shift, groups, tiles, tile, g)) return;
     const int i0 = tile * P;
     const int c = 64 * g + lane;
     const bool live = c < channels;
@@ -458,37 +455,6 @@ __global__ __launch_bounds__(256) void pack_generic_kernel(
     dst[t] = word;
 }
 
-// Whether and how pack_ballot_kernel takes a call (nv = 0: it does not).  Timed on rotating buffers beyond the
-// last-level cache: rows of up to 128 bytes (bfloat16, 1024 channels, 256 maps of 7 x 7 12.2 -> 9.5 us; float weights,
-// 1024 x 1024 x 3 x 3 18.4 -> 9.5), launches that do not fill the chip (float, 64 channels, one 14 x 14 map 2.6 -> 2.3).  Longer
-// rows of large launches stream better with the lanes along the positions (float, 256 channels, 64 maps of 56 x 56 39 us
-// against 48, although from cache this kernel is ahead there, 32 against 37).
-struct BallotPlan { int nv, tw_shift, groups, tiles; int64_t blocks_per_image; };
-BallotPlan plan_ballot(int esz, const void* src, int64_t outer, int64_t channels, int64_t src_channels, int64_t inner)
-{
-    BallotPlan p{};
-    const int64_t row = inner * esz;
-    // images a whole number of dwords apart, addressable by 31-bit offsets
-    if (inner < 2 || (src_channels * row) % 4 != 0 || (reinterpret_cast<uintptr_t>(src) & 3) != 0 || src_channels * row >= (1ll << 30) ||
-        channels >= (1 << 24) || inner * ((channels + 31) / 32) >= (1 << 28))
-        return p;
-    const int per = 16 / esz;                                // elements of a vector
-    const int64_t fit = (inner + per - 1) / per;             // vectors of a row
-    p.groups = (int)((channels + 63) / 64);
-    auto tiles = [&](int nv) { return (inner + nv * per - 1) / (nv * per); };
-    const bool whole_rows = fit <= (esz == 1 ? 4 : 8);
-    // a wave takes whole rows (of at most 64 positions), or a few vectors of them where the launch is small
-    p.nv = !whole_rows ? 4 : fit <= 1 ? 1 : fit <= 2 ? 2 : fit <= 4 ? 4 : 8;
-    if (!whole_rows && outer * p.groups * tiles(4) >= 2048) { p.nv = 0; return p; }
-    while (p.nv > 1 && outer * p.groups * tiles(p.nv) < 2048) p.nv /= 2;
-    p.tiles = (int)tiles(p.nv);
-    p.tw_shift = p.tiles < 2 ? 0 : p.tiles < 3 ? 1 : 2;     // neighbouring tiles share cache lines
-    const int gw = 4 >> p.tw_shift;
-    p.blocks_per_image = (int64_t)((p.tiles + (1 << p.tw_shift) - 1) >> p.tw_shift) * ((p.groups + gw - 1) / gw);
-    if (p.blocks_per_image * outer > 0x7FFFFFFF) p.nv = 0;
-    return p;
-}
-
 template <typename T, bool BIAS, bool REP>
 hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t channels,
                          int64_t src_channels, int64_t inner, uint32_t* dst, hipStream_t stream)
@@ -499,14 +465,14 @@ hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t
         hipLaunchKernelGGL((pack_last8_kernel<T, BIAS>), dim3((unsigned)((outer + per_block - 1) / per_block)), dim3(256), 0, stream,
                            src, bias, outer, (int)channels, (int)src_channels, (int)cw, per_row, rows_per_pass,
                            DivBy::make(per_row), dst);
-    } else if (inner == 1) {
+    } else if (inner == 1 && (outer + 7) / 8 * ((channels + 63) / 64) <= 4 * MAX_BLOCKS_256) {
         constexpr int ROWS = 8;
         const int64_t groups = (channels + 63) / 64;
         const int64_t waves = ((outer + ROWS - 1) / ROWS) * groups;
         const int64_t blocks = (waves + 3) / 4;
         hipLaunchKernelGGL((pack_rows_kernel<T, ROWS, BIAS, REP>), dim3((unsigned)blocks), dim3(256), 0, stream,
                            src, bias, outer, channels, src_channels, cw, dst);
-    } else if (const BallotPlan plan = plan_ballot((int)sizeof(T), src, outer, channels, src_channels, inner); plan.nv) {
+    } else if (const BallotPlan plan = plan_ballot((int)sizeof(T), reinterpret_cast<uintptr_t>(src), outer, channels, src_channels, inner); plan.nv) {
         const bool mis = (inner * (int64_t)sizeof(T)) % 4 != 0;
         auto go = [&](auto nv) {
             constexpr int N = decltype(nv)::value;
@@ -550,7 +516,7 @@ hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t
     } else if (inner >= 5) {
         const int64_t groups = (cw + 7) / 8;
         const int64_t blocks = outer * groups;
-        if (blocks > 0x7FFFFFFF) goto generic;
+        if (blocks > MAX_BLOCKS_256) goto generic;
         if (inner > 32)
             hipLaunchKernelGGL((pack_small_inner_kernel<T, 64, BIAS, REP>), dim3((unsigned)blocks), dim3(256), 0, stream,
                                src, bias, channels, src_channels, (int)inner, cw, (int)groups, dst);

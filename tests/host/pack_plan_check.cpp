@@ -1,0 +1,54 @@
+// Host-only check of the ballot pack's plan (csrc/pack_plan.h): for many sources, walk every wave of one image's workgroups
+// through the functions the launcher and the kernel use and check that
+//   - every tile of the rows and every group of 64 channels is taken by exactly one wave, tiles of at most 64 positions,
+//   - tiles cover the row, groups the channels,
+//   - the launch stays below 2^32 threads, whatever the number of images (up to 2^31 - 1 output words).
+// Prints "mismatches: N"; exit status 0 = none.
+#include "pack_plan.h"
+
+#include <cstdio>
+#include <vector>
+
+using namespace bcnn;
+
+static long check(int esz, int64_t outer, int64_t channels, int64_t inner, long* taken)
+{
+    const BallotPlan p = plan_ballot(esz, 0, outer, channels, channels, inner);
+    if (p.nv == 0) return 0;
+    ++*taken;
+    long bad = 0;
+    const int64_t positions = (int64_t)p.nv * 16 / esz;
+    if (positions > 64 || positions * p.tiles < inner || 64ll * p.groups < channels) ++bad;
+    if (p.blocks_per_image * outer > MAX_BLOCKS_256 || p.blocks_per_image * outer < 1) {
+        if (!bad) printf("launch of %lld workgroups: %d bytes [%lld][%lld][%lld]\n", (long long)(p.blocks_per_image * outer), esz,
+                         (long long)outer, (long long)channels, (long long)inner);
+        ++bad;
+    }
+    std::vector<int> seen((size_t)p.tiles * p.groups, 0);
+    for (int64_t at = 0; at < p.blocks_per_image; ++at)
+        for (int wave = 0; wave < 4; ++wave) {
+            int tile, g;
+            if (!ballot_place((int)at, wave, p.tw_shift, p.groups, p.tiles, tile, g)) continue;
+            if (tile < 0 || g < 0) { ++bad; continue; }
+            ++seen[(size_t)tile * p.groups + g];
+        }
+    for (int n : seen)
+        if (n != 1) ++bad;
+    return bad;
+}
+
+int main()
+{
+    long bad = 0, taken = 0;
+    const int64_t counts[] = {1, 2, 3, 4, 8, 20, 31, 32, 33, 64, 65, 100, 128, 192, 256, 257, 320, 512, 1000, 1024, 2048, 4096};
+    for (int esz : {1, 2, 4})
+        for (int64_t channels : counts)
+            for (int64_t inner = 1; inner <= 260; inner += inner < 70 ? 1 : 13)
+                for (int64_t outer : {1ll, 2ll, 7ll, 64ll, 300ll, 2048ll, 5000ll, 1ll << 20, (1ll << 24) - 1, 1ll << 24, 1ll << 26, 1ll << 29}) {
+                    if (outer * inner * ((channels + 31) / 32) > 0x7FFFFFFF) continue;   // refused by the entry point
+                    bad += check(esz, outer, channels, inner, &taken);
+                }
+    if (taken < 1000) ++bad;
+    printf("plans: %ld\nmismatches: %ld\n", taken, bad);
+    return bad ? 1 : 0;
+}

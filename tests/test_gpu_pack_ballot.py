@@ -48,3 +48,15 @@ def test_pack_planes(shape, kind):
         out = Guarded(n * inner * ((c + 31) // 32), dev)
         B.check(B.bcnn_pack(buf.data_ptr() + off, code, n, c, inner, out.ptr), "pack")
         assert np.array_equal(out.get(np.uint32).reshape(n, inner, -1), oracle.pack_channels(oracle.sign_f32(v32)))
+
+
+@pytest.mark.parametrize("inner", [2, 5])
+def test_more_images_than_a_launch_has_workgroups(inner):
+    """2^24 images of two channels: a launch holds fewer than 2^32 threads, so not a workgroup of 256 per image."""
+    dev = gpu_device()
+    n = 1 << 24
+    src = torch.randint(-100, 101, (n, 2, inner), dtype=torch.int8, device=dev)
+    out = torch.full((n, inner), 77, dtype=torch.int32, device=dev)
+    B.check(B.bcnn_pack(src, B.BCNN_I8, n, 2, inner, out), "pack")
+    on = src >= 0
+    assert torch.equal(out, on[:, 0].int() + 2 * on[:, 1].int())
