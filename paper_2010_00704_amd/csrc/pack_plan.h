@@ -18,10 +18,27 @@ constexpr int64_t MAX_BLOCKS_256 = (1 << 24) - 1;
 // neighbouring tiles of a row x the rest along the groups of 64 channels.
 struct BallotPlan { int nv, tw_shift, groups, tiles; int64_t blocks_per_image; };
 
-// Timed on rotating buffers beyond the last-level cache: rows of up to 128 bytes (bfloat16, 1024 channels, 256 maps of 7 x 7
-// 12.2 -> 9.5 us; float weights, 1024 x 1024 x 3 x 3 18.4 -> 9.5), launches that do not fill the chip (float, 64 channels, one
-// 14 x 14 map 2.6 -> 2.3).  Longer rows of large launches stream better with the lanes along the positions (float, 256
-// channels, 64 maps of 56 x 56 39 us against 48, although from cache this kernel is ahead there, 32 against 37).
+// Whether the ballot kernel is ahead of the kernel that the call would take otherwise, from 1872 calls (float, half and
+// int8, rows of 2 to 64 positions, 1 to 1024 channels, 1e5 to 2e7 elements; us there and here).
+inline bool ballot_pays(int esz, int64_t blocks, int64_t outer, int64_t channels, int64_t inner)
+{
+    // Up to four positions the other kernel has a thread per word.  Here a workgroup costs 0.52 ns of the launch whatever it
+    // holds, so it has to hold enough elements, or there are so few that their number does not count: int8, [416666][16][3]
+    // 22 and 220; [104166][64][3] 38 and 58; float, [52083][96][4] 52 and 35; [1562][64][3] 6.6 and 3.2.
+    if (inner <= 4) return blocks <= 2048 || channels * inner * outer >= (esz == 4 ? 288 : esz == 2 ? 384 : 640) * blocks;
+    // Half of the lanes have no channel: rows of a cache line's better part make up for it (float, [1.1e6][2][9] level, half,
+    // [25000][32][25] 1.26 times), shorter ones do not (float, [21428][2][7] 11.6 and 13.5; int8, [39062][32][16] 22 and 23).
+    if (channels <= 32 && inner * esz < 36) return false;
+    // 64 positions of one to four channels: other kernel a thread per word again (int8, [156250][2][64] 60 and 105)
+    if (channels <= 32 && inner == 64 && esz < 4) return channels * inner >= 512;
+    return true;
+}
+
+// Timed on rotating buffers beyond the last-level cache: rows of up to 128 bytes, float 112 (bfloat16, 1024 channels, 256
+// maps of 7 x 7 12.2 -> 9.5 us; float weights, 1024 x 1024 x 3 x 3 18.4 -> 9.5), launches that do not fill the chip (float,
+// 64 channels, one 14 x 14 map 2.6 -> 2.3; 512 waves are level, 1000 are 0.83 to 1.05 times).  Longer rows of large
+// launches stream better with the lanes along the positions (float, 256 channels, 64 maps of 56 x 56 39 us against 48,
+// although from cache this kernel is ahead there, 32 against 37).
 inline BallotPlan plan_ballot(int esz, uintptr_t src, int64_t outer, int64_t channels, int64_t src_channels, int64_t inner)
 {
     BallotPlan p{};
@@ -34,16 +51,19 @@ inline BallotPlan plan_ballot(int esz, uintptr_t src, int64_t outer, int64_t cha
     const int64_t fit = (inner + per - 1) / per;             // vectors of a row
     p.groups = (int)((channels + 63) / 64);
     auto tiles = [&](int nv) { return (inner + nv * per - 1) / (nv * per); };
-    const bool whole_rows = fit <= (esz == 1 ? 4 : 8);
+    const bool whole_rows = fit <= (esz == 1 ? 4 : esz == 2 ? 8 : 7);
     // a wave takes whole rows (of at most 64 positions), or a few vectors of them where the launch is small
     p.nv = !whole_rows ? 4 : fit <= 1 ? 1 : fit <= 2 ? 2 : fit <= 4 ? 4 : 8;
-    if (!whole_rows && outer * p.groups * tiles(4) >= 2048) { p.nv = 0; return p; }
+    // (a partial last word makes the other kernel walk its channels one by one)
+    const int64_t small = channels > 32 && channels % 32 != 0 ? 2048 : 512;
+    if (!whole_rows && outer * p.groups * tiles(4) >= small) { p.nv = 0; return p; }
     while (p.nv > 1 && outer * p.groups * tiles(p.nv) < 2048) p.nv /= 2;
     p.tiles = (int)tiles(p.nv);
     p.tw_shift = p.tiles < 2 ? 0 : p.tiles < 3 ? 1 : 2;     // neighbouring tiles share cache lines
     const int gw = 4 >> p.tw_shift;
     p.blocks_per_image = (int64_t)((p.tiles + (1 << p.tw_shift) - 1) >> p.tw_shift) * ((p.groups + gw - 1) / gw);
-    if (p.blocks_per_image * outer > MAX_BLOCKS_256) p.nv = 0;
+    const int64_t blocks = p.blocks_per_image * outer;
+    if (blocks > MAX_BLOCKS_256 || !ballot_pays(esz, blocks, outer, channels, inner)) p.nv = 0;
     return p;
 }
 
