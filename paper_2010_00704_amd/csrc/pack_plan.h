@@ -1,5 +1,6 @@
-// Which calls the ballot kernel of the pack takes, and how its workgroups cover them (kernel: pack.hip).  Plain C++ on
-// purpose: launcher and kernel use these functions, and a host-only test walks the workgroups with them.
+// Which calls the ballot kernel of the pack takes, and how its workgroups cover them (kernel: pack.hip); which windows the
+// pooling kernel with eight channels a thread takes (pool.hip).  Plain C++ on purpose: launchers and kernel use these
+// functions, and a host-only test walks the workgroups with them.
 #pragma once
 #include <stdint.h>
 
@@ -76,6 +77,16 @@ BCNN_PACK_INLINE bool ballot_place(int at, int wave, int tw_shift, int groups, i
     tile = tb * tw + (wave & (tw - 1));
     g = (at - tb * gblocks) * gw + (wave >> tw_shift);
     return tile < tiles && g < groups;
+}
+
+// S x S windows of 16-bit streams, m output pixels: with eight channels a thread, or with four a lane?  2 x 2 with eight at
+// every size (1.07 to 1.42 times over 42 calls; us with four and with eight from here on).  Larger windows keep too few
+// threads with too many loads each in flight (half, 4 x 4, 64 channels, one map of 56 x 56 3.1 and 3.6; 4882 of 8 x 8
+// 10.0 and 10.9): eight only where four leave most lanes without a channel and the launch fills the chip (8 channels,
+// 797 maps of 56 x 56, 3 x 3 18.0 and 12.7, 4 x 4 16.4 and 12.2; 16 channels, 1714 of 27 x 27, 3 x 3 12.3 and 11.4).
+inline bool pool_by_eight(int s, int64_t channels, int64_t m)
+{
+    return s == 2 || ((s == 3 || s == 4) && channels <= 16 && m >= (1 << 16));
 }
 
 }  // namespace bcnn

@@ -18,6 +18,7 @@
 
 #include "bcnn_common.h"
 #include "div_by.h"
+#include "pack_plan.h"
 #include "sign_bits.h"
 
 namespace bcnn {
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(256) void avgpool_pack4_kernel(const T* __restrict_
     }
 }
 
-// The same for 16-bit streams with channels a multiple of 8 and 16-byte rows, S = 2, 3, 4: a thread owns eight channels
+// The same for 16-bit streams with channels a multiple of 8 and 16-byte rows, S = 2, 3, 4 (pool_by_eight): a thread owns eight channels
 // of one output pixel (one 16-byte load per window element), four threads a packed word; the block's threads are cut
 // into runs of `per_px`, one run per output pixel.  All accesses are raw buffer accesses from the block's first window
 // on (what does not exist reads zero and stores nothing): no branches between the loads.  A window of 4 or 16 elements
@@ -296,7 +297,7 @@ hipError_t launch_typed(const T* src, const float* bias, PoolShape p, T* pooled,
                            (reinterpret_cast<uintptr_t>(bias) % 16) == 0;
     const int64_t m = (int64_t)p.n * p.ho * p.wo;
     if constexpr (sizeof(T) == 2) {
-        if (p.s >= 2 && p.s <= 4 && p.c % 8 == 0 && p.c <= 2048 && (int64_t)p.n * p.h * p.w < (1 << 30) && (int64_t)p.w * p.c < (1 << 22) && (reinterpret_cast<uintptr_t>(src) & 15) == 0 &&
+        if (pool_by_eight(p.s, p.c, m) && p.c % 8 == 0 && p.c <= 2048 && (int64_t)p.n * p.h * p.w < (1 << 30) && (int64_t)p.w * p.c < (1 << 22) && (reinterpret_cast<uintptr_t>(src) & 15) == 0 &&
             (reinterpret_cast<uintptr_t>(pooled) & 15) == 0) {
             const int per_px = 4 * p.cw, px_per_pass = 256 / per_px;
             const DivBy dp = DivBy::make(per_px), dw = DivBy::make(p.wo), dh = DivBy::make(p.ho);

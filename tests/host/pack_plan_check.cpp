@@ -62,6 +62,12 @@ int main()
             printf("route: %d bytes [%lld][%lld][%lld]\n", r.esz, (long long)r.outer, (long long)r.channels, (long long)r.inner);
             ++bad;
         }
+    const struct { int s; int64_t channels, m; bool eight; } pools[] = {
+        {2, 8, 1, true}, {2, 2048, 100, true}, {3, 64, 324, false}, {4, 64, 19528, false}, {4, 8, 585, false},
+        {3, 16, 138834, true}, {4, 8, 156212, true}, {5, 8, 1 << 20, false}, {1, 8, 1 << 20, false},
+    };
+    for (const auto& r : pools)
+        if (pool_by_eight(r.s, r.channels, r.m) != r.eight) { printf("pool: %d %lld %lld\n", r.s, (long long)r.channels, (long long)r.m); ++bad; }
     printf("plans: %ld\nmismatches: %ld\n", taken, bad);
     return bad ? 1 : 0;
 }

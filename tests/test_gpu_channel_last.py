@@ -59,7 +59,7 @@ def test_pack_rows(shape, kind):
 POOLS = [
     # n, h, w, channels, window
     (1, 2, 2, 8, 2), (2, 9, 7, 40, 2), (3, 31, 30, 64, 2), (1, 7, 65, 200, 2), (2, 10, 11, 32, 3), (1, 13, 9, 2048, 3),
-    (5, 8, 9, 72, 4), (1, 4, 4, 1000, 4),
+    (5, 8, 9, 72, 4), (1, 4, 4, 1000, 4), (29, 146, 147, 16, 3), (17, 255, 256, 8, 4), (16, 255, 256, 8, 4),
 ]
 
 
