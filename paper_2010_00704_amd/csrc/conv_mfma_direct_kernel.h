@@ -186,7 +186,8 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
     constexpr int ESZ = (int)sizeof(real_t);
     if constexpr (MODULE) {
         const uintptr_t both = reinterpret_cast<uintptr_t>(ep.r) | reinterpret_cast<uintptr_t>(ep.identity);
-        vec = ep.identity && ep.r && ep.x_next && s.c_out % 4 == 0 && ep.id_channels % 4 == 0 && (both & 3) == 0;
+        // (a missing identity, real stream or next packing is a buffer of no bytes)
+        vec = s.c_out % 4 == 0 && ep.id_channels % 4 == 0 && (both & 3) == 0;
         if (vec) {
             const int row_bytes = ep.id_channels * ESZ;
             const auto res = rows_of(ep.identity, row_bytes);
@@ -492,8 +493,8 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 float val;
-                if constexpr (BR) val = module_tail<REAL>(v[k], vec || ep.identity != nullptr, (float)id[k], true, pa[k]);
-                else val = module_value<REAL>(v[k] - zf, pg[k], pbi[k], vec || ep.identity != nullptr, (float)id[k], true, pa[k]);
+                if constexpr (BR) val = module_tail<REAL>(v[k], ep.identity != nullptr, (float)id[k], true, pa[k]);
+                else val = module_value<REAL>(v[k] - zf, pg[k], pbi[k], ep.identity != nullptr, (float)id[k], true, pa[k]);
                 nib |= (uint32_t)(k < nch && val + pc[k] >= 0.0f) << k;
                 st[k] = (real_t)val;
             }

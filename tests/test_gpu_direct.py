@@ -88,3 +88,43 @@ def test_direct(dev, shape, offset):
 def up_bytes(a, dev):
     """Any real type as raw bytes on the device."""
     return torch.from_numpy(np.ascontiguousarray(a).view(np.uint8).reshape(-1)).to(dev)
+
+
+PARTS = [(True, True, False), (True, False, True), (False, True, True), (False, True, False), (False, False, True)]
+
+
+@pytest.mark.parametrize("half", [False, True, "bf16"], ids=["f32", "f16", "bf16"])
+@pytest.mark.parametrize("parts", PARTS, ids=lambda p: "".join(n for n, on in zip(("id", "r", "x"), p) if on))
+@pytest.mark.parametrize("shape", [(2, 130, 7, 6, 64, 3, 1, 1), (3, 64, 9, 9, 36, 1, 2, 0), (40, 96, 28, 28, 72, 1, 1, 0)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_module_without_some_parts(dev, shape, parts, half):
+    """Identity, real stream or next packing missing where channels come in whole fours; some channels give -0 or +0, which
+    a missing identity leaves as it is."""
+    n, c, h, w, o, k, stride, pad = shape
+    has_id, has_r, has_x = parts
+    seed = 53000 + c + 7 * o
+    x, wt = W.pm1(seed, (n, c, h, w), 0.45), W.pm1(seed + 1, (o, c, k, k))
+    y = oracle.conv2d_pm1(x, wt, stride, pad)
+    m, cwo = y.size // o, (o + 31) // 32
+    g, b = W.uniform_f32(seed + 3, (o,), -0.3, 0.3), W.uniform_f32(seed + 4, (o,), -3.0, 3.0)
+    g[::5], b[::5] = 0.0, -0.0
+    alpha, nxt = W.uniform_f32(seed + 5, (o,), 0.05, 0.5), W.uniform_f32(seed + 6, (o,), -5.0, 5.0)
+    ident = real_store(W.uniform_f32(seed + 7, (m, o), -9.0, 9.0), half)
+    esz = np.dtype(real_np_dtype(half)).itemsize
+    d = B.conv_desc(n, c, h, w, o, k, stride, pad)
+    r, xn = Guarded.of_bytes(m * o * esz, dev), Guarded(m * cwo, dev)
+    B.check(B.bcnn_conv2d_binary_module(
+        d, up(pack_x(x), dev), up(i32(oracle.pack_channels(wt.reshape(o, c, k * k))), dev), up(g, dev), up(b, dev),
+        up_bytes(ident, dev) if has_id else None, up(alpha, dev), up(nxt, dev), real_code(half), r.ptr if has_r else None,
+        xn.ptr if has_x else None), "module")
+    _, r32 = oracle.module_epilogue(y, g, b, real_values(ident, half).reshape(y.shape) if has_id else None, alpha)
+    want = real_store(r32.reshape(m, o), half)
+    if has_r:
+        assert np.array_equal(r.get(real_np_dtype(half), m * o).reshape(m, o).view(np.uint8), want.view(np.uint8))
+    else:
+        assert np.all(r.get(np.uint32) == 0x5A5A5A5A)
+    if has_x:
+        sb = oracle.sign_bias_f32(real_values(want, half).reshape(m, o, 1), nxt)
+        assert np.array_equal(xn.get(np.uint32).reshape(m, cwo), oracle.pack_channels(sb.reshape(m, o, 1))[:, 0, :])
+    else:
+        assert np.all(xn.get(np.uint32) == 0x5A5A5A5A)
