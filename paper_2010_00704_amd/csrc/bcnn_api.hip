@@ -2,6 +2,7 @@
 // host, then one kernel launch on the caller's stream.  No allocation, no
 // synchronisation, no state.
 #include "bcnn.h"
+#include "auto_plan.h"
 #include "bcnn_common.h"
 #include "conv_mfma_direct.h"
 
@@ -60,11 +61,11 @@ int conv_entry(const bcnn_conv_desc* desc, const uint32_t* x, const uint32_t* w,
         case BCNN_VARIANT_AUTO: {
             // Two matrix-core kernels: the staged one for launches that fill the chip (C_in a multiple of
             // 128), the direct one for small launches and every other channel count; conv_mfma_direct.hip
-            // weighs them by fitted times.  One of them is faster than the vector-ALU kernels at every size
-            // measured (7 to 1024 input channels, 25 to 430 000 pixels); those take what is left, tensors
-            // beyond 31-bit offsets and sums beyond fp32.
+            // weighs them by fitted times.  The vector ALUs take packed bits of one or two words (auto_plan.h),
+            // tensors beyond 31-bit offsets and sums beyond fp32.
             const bool staged = conv_mfma_fp4_supported(s, x, w);
-            const int tile = conv_mfma_direct_supported(s) ? conv_mfma_direct_choose(s, fused ? KIND_BITS_OUT : KIND_SUMS_OUT, staged) : DIRECT_NONE;
+            const bool direct = conv_mfma_direct_supported(s) && !(fused && direct_behind_on_bits(s.ks, s.cw, (int64_t)s.m * s.c_out));
+            const int tile = direct ? conv_mfma_direct_choose(s, fused ? KIND_BITS_OUT : KIND_SUMS_OUT, staged) : DIRECT_NONE;
             if (tile != DIRECT_NONE)
                 e = launch_conv_mfma_direct(s, x, w, fused ? thr : nullptr, out, nullptr, tile, st);
             else if (staged)
