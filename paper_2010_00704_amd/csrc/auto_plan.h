@@ -16,4 +16,21 @@ inline bool direct_behind_on_bits(int ks, int cw, int64_t outputs)
     return ks == 1 && ((cw == 1 && outputs >= 4000000) || (cw == 2 && outputs >= 15000000));
 }
 
+// Modules on a float stream that the streaming kernel does not take; has_*: which of the tensors the call has.  Rows leave the
+// direct kernel in pieces of 128 bytes from many waves, which costs where there is little else (vector ALUs, or the
+// staged kernel where it covers the call, and direct):
+//   - without the stream or the bits out, 1x1 of up to two words: 64 -> 64 channels, 256 maps of 56 x 56 without the stream 44
+//     and 50; 15 -> 64, 122 maps of 28 x 28 without the bits 13.3 and 16.0; 64 -> 320, 3000 pixels of it level;
+//   - without identity, 1x1 of up to eight words, from 80 million outputs on: 64 -> 512, 240 maps of 56 x 56 345 and 443; 128 ->
+//     512, 120 maps 181 and 222; 64 -> 256, 64 maps (51 million) 1.14 times ahead;
+//   - rows that are no whole 16-byte vectors: up to three words there, and 3x3 of so many: 64 -> 717, 30 maps of 56 x 56 254 and
+//     279; 96 -> 717 without the stream, 1x1, 89 and 104; 64 -> 226 level.
+inline bool direct_behind_on_float_module(int ks, int cw, int c_out, bool has_id, bool has_r, bool has_x, int64_t outputs)
+{
+    const int few = c_out % 4 == 0 ? 2 : 3;
+    if (ks == 1 && cw <= few && !(has_r && has_x)) return outputs >= (cw <= 2 ? 4000000 : 50000000);
+    if (ks == 1 && cw <= 8 && !has_id && has_r) return outputs >= 80000000;
+    return ks == 3 && cw <= few && c_out % 4 != 0 && has_id && outputs >= 50000000;
+}
+
 }  // namespace bcnn
