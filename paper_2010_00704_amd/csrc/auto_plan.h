@@ -33,4 +33,16 @@ inline bool direct_behind_on_float_module(int ks, int cw, int c_out, bool has_id
     return ks == 3 && cw <= few && c_out % 4 != 0 && has_id && outputs >= 50000000;
 }
 
+// Branch sums that go on into a module's tail, `words` = branches x words per pixel: the same as for modules, and the vector ALUs
+// walk all branches at once.  Streams that fit the last-level cache are ahead on the direct kernel (vector ALUs and direct):
+// float, 128 channels x 2 -> 448, 120 maps of 56 x 56 266 and 317, 60 maps of 28 x 28 level; 320 x 2 1.2 times ahead; rows that
+// are no whole 16-byte vectors, 32 x 8 -> 451, 60 maps of 56 x 56 280 and 375, 3x3, 32 -> 717 448 and 572, 200 x 8 -> 717 1.1 times
+// ahead; half, 64 x 2 -> 451 0.95 times, 32 -> 448 0.90, 64 x 4 -> 448 1.1.
+inline bool direct_behind_on_branch_tail(int cw, int words, int c_out, bool half, int64_t outputs)
+{
+    if (cw % 8 == 0 && c_out % 4 == 0) return false;         // (not measured against the vector ALUs)
+    if (c_out % 4 != 0) return outputs >= 40000000 && words <= (half ? 8 : 32);
+    return half ? outputs >= 80000000 && words <= 2 : outputs >= 40000000 && words <= 8;
+}
+
 }  // namespace bcnn
