@@ -349,9 +349,8 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
         case BCNN_VARIANT_AUTO: {
             // 1x1 modules of up to 256 input channels are bound by their real stream: the streaming kernel is ahead
             // of every other at all 64 sizes measured, or level with the direct one at the smallest.  The
-            // staged kernel is weighed in its plain form only (whole 128-channel tiles, every part of the
-            // module present); its general form, like the vector ALUs, is ahead of the direct kernel on large float
-            // streams only (auto_plan.h).
+            // staged kernel has a plain form (whole 128-channel tiles, every part of the module present) and a general
+            // one; direct_plan.h weighs both.  Large float streams: auto_plan.h.
             if (bcnn::conv_mfma_stream_supported(s, m)) {
                 e = bcnn::launch_conv_mfma_stream(s, x_packed, w_packed, m, st);
                 break;
@@ -359,7 +358,7 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
             const bool plain = mfma_ok && s.c_out % 128 == 0 && m.identity && m.r && m.x_next && m.id_channels % 4 == 0;
             const bool direct = bcnn::conv_mfma_direct_supported(s) &&
                 !(m.half == bcnn::REAL_F32 && bcnn::direct_behind_on_float_module(s.ks, s.cw, s.c_out, m.identity, m.r, m.x_next, (int64_t)s.m * s.c_out));
-            const int tile = direct ? bcnn::conv_mfma_direct_choose(s, bcnn::KIND_MODULE_OUT, plain) : bcnn::DIRECT_NONE;
+            const int tile = direct ? bcnn::conv_mfma_direct_choose(s, plain ? bcnn::KIND_MODULE_PLAIN : bcnn::KIND_MODULE_GENERAL, mfma_ok) : bcnn::DIRECT_NONE;
             if (tile != bcnn::DIRECT_NONE)
                 e = bcnn::launch_conv_mfma_direct(s, x_packed, w_packed, nullptr, nullptr, &m, tile, st);
             else if (mfma_ok)

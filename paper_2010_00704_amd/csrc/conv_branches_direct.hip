@@ -50,31 +50,9 @@ bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b)
     return b.branches <= MAX_BRANCHES && s.c_out <= (1 << 20) && ((int64_t)s.cw + 1) * 32 < (1 << 22) && branch_x_bytes(s, b) < (1ll << 31) && w_bytes < (1ll << 31);
 }
 
-// Estimated time of a tile in microseconds, as for the plain convolution: a launch, a wave's chain of groups of four
-// K-steps, a wave's set-up and epilogue and its groups where more waves than SIMDs (1024) share the issue slots.
-// Fits over 74 calls; rms error 14 to 19 %, the choice 1 to 2 % over the best tile on average, 24 % at worst.
-struct BranchCost { double fixed, group, wave, wave_group; };
-struct BranchTile { int tile, cb, pb; BranchCost plain, tail; };
-static const BranchTile BRANCH_TILES[] = {
-    {DIRECT_1x1, 1, 1, {2.88, 0.421, 0.188, 0.165}, {3.97, 0.363, 0.984, 0.176}},
-    {DIRECT_2x1, 2, 1, {3.76, 0.586, 0.696, 0.233}, {5.98, 0.461, 1.685, 0.311}},
-    {DIRECT_2x2, 2, 2, {4.53, 0.722, 1.791, 0.311}, {7.20, 0.708, 3.077, 0.457}},
-};
-
 int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b)
 {
-    const double groups = (double)b.branches * (double)BranchWalk::make(s.cw).groups();
-    int best = DIRECT_1x1;
-    double least = 1e30;
-    for (const BranchTile& t : BRANCH_TILES) {
-        if (t.cb * t.pb == 4 && b.tail && !b.tail->half) continue;
-        const BranchCost& c = b.tail ? t.tail : t.plain;
-        const double waves = 4.0 * (double)((s.m + 128 * t.pb - 1) / (128 * t.pb)) *
-                             (double)((s.c_out + 32 * t.cb - 1) / (32 * t.cb)) / 1024.0;
-        const double cost = c.fixed + c.group * groups + (c.wave + c.wave_group * groups) * waves;
-        if (cost < least) { least = cost; best = t.tile; }
-    }
-    return best;
+    return branches_direct_choose(s.m, s.c_out, s.cw, b.branches, b.tail != nullptr, b.tail && b.tail->half);
 }
 
 hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream)

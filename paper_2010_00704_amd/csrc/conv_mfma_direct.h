@@ -1,17 +1,13 @@
-// The matrix-core convolution without LDS staging (kernel and launcher: conv_mfma_direct.hip).
+// The matrix-core convolution without LDS staging (kernel: conv_mfma_direct_kernel.h; launchers: conv_mfma_direct.hip,
+// conv_branches_direct.hip; tiles and their choice: direct_plan.h).
 #pragma once
 #include "bcnn_common.h"
+#include "direct_plan.h"
 
 namespace bcnn {
 
-// Tiles: 32-channel x 32-pixel blocks of a wave; _K4: four waves split K, otherwise four waves side by side
-// along the pixels.
-enum { DIRECT_NONE = 0, DIRECT_1x1_K4, DIRECT_2x2_K4, DIRECT_2x1, DIRECT_1x1, DIRECT_2x2 };
-
 bool conv_mfma_direct_supported(const ConvShape& s);
-// The tile with the least estimated time for an output of that kind; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the call)
-// and that kernel is estimated to be faster.
-enum { KIND_BITS_OUT = 0, KIND_SUMS_OUT = 1, KIND_MODULE_OUT = 2 };
+// A tile, or DIRECT_NONE: the staged kernel (direct_plan.h).
 int conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged);
 // thr == nullptr: int32 sums, else packed bits; ep != nullptr: module epilogue (thr and out are ignored)
 hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,

@@ -31,6 +31,7 @@
 #pragma once
 #include "bcnn_common.h"
 #include "branch_walk.h"
+#include "direct_plan.h"
 #include "div_by.h"
 
 #include <type_traits>
@@ -51,7 +52,7 @@ struct DirectArgs {
     // branch mode
     int32_t taps;            // branches
     int32_t tap_step;        // words between the branches' input tensors
-    int32_t pad_bytes, scale_bytes;
+    int32_t pad_bytes;
 };
 
 // Branch mode: per-branch scales, bias, what a tap outside the image stands for.
@@ -70,7 +71,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 enum { OUT_I32 = 0, OUT_BITS = 1, OUT_MODULE = 2 };          // OUT_MODULE + REAL_*
-enum { UNITS = 0, TAIL = 1, WORDS = 2 };
 // Branch mode (F x F convolution as F*F shifted 1x1 branches, or P parallel ones, each with a real scale per output
 // channel: Section 4.2.1, last paragraph; Figure 2, bottom).  OUT_I32 then stores float sums, OUT_BITS z >= 0.
 enum { PAD_NONE = 0, PAD_OPERAND = 1, PAD_NOTHING = 2 };     // outside the image: -1, the branch's pad words, no contribution
