@@ -11,9 +11,11 @@ namespace bcnn {
 // Measured (vector ALUs and direct): 64 -> 64 channels, 802 816 pixels 17.3 and 22.2, 200 704 pixels 7.9 and 7.8; 32 -> 128,
 // 200 704 pixels 9.5 and 12.2, 50 176 pixels 5.1 and 5.3; 64 -> 512, 50 176 pixels 12.3 and 12.4.  Three words, and one word
 // under a 3x3 filter, are ahead on the matrix cores or level at every size.
-inline bool direct_behind_on_bits(int ks, int cw, int64_t outputs)
+// (up to 32 channels are one block of the direct kernel's tile whatever their number: 64 -> 16, 802 816 pixels 13.3 and 16.0)
+inline bool direct_behind_on_bits(int ks, int cw, int c_out, int64_t outputs)
 {
-    return ks == 1 && ((cw == 1 && outputs >= 4000000) || (cw == 2 && outputs >= 15000000));
+    if (ks != 1 || cw > 2) return false;
+    return outputs >= (cw == 1 ? 4000000 : c_out <= 32 ? 6000000 : 15000000);
 }
 
 // Modules on a float stream that the streaming kernel does not take; has_*: which of the tensors the call has.  Rows leave the

@@ -64,7 +64,7 @@ int conv_entry(const bcnn_conv_desc* desc, const uint32_t* x, const uint32_t* w,
             // weighs them by fitted times.  The vector ALUs take packed bits of one or two words (auto_plan.h),
             // tensors beyond 31-bit offsets and sums beyond fp32.
             const bool staged = conv_mfma_fp4_supported(s, x, w);
-            const bool direct = conv_mfma_direct_supported(s) && !(fused && direct_behind_on_bits(s.ks, s.cw, (int64_t)s.m * s.c_out));
+            const bool direct = conv_mfma_direct_supported(s) && !(fused && direct_behind_on_bits(s.ks, s.cw, s.c_out, (int64_t)s.m * s.c_out));
             const int tile = direct ? conv_mfma_direct_choose(s, fused ? KIND_BITS_OUT : KIND_SUMS_OUT, staged) : DIRECT_NONE;
             if (tile != DIRECT_NONE)
                 e = launch_conv_mfma_direct(s, x, w, fused ? thr : nullptr, out, nullptr, tile, st);

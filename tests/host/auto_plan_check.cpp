@@ -14,13 +14,14 @@ static void check(bool got, bool want, const char* what)
 
 int main()
 {
-    check(direct_behind_on_bits(1, 2, 802816ll * 64), true, "bits 64 -> 64, 256 maps of 56 x 56");
-    check(direct_behind_on_bits(1, 1, 200704ll * 128), true, "bits 32 -> 128, 64 maps of 56 x 56");
-    check(direct_behind_on_bits(1, 2, 200704ll * 512), true, "bits 64 -> 512, 64 maps of 56 x 56");
-    check(direct_behind_on_bits(1, 1, 3136ll * 256), false, "bits 32 -> 256, one map of 56 x 56");
-    check(direct_behind_on_bits(1, 2, 50176ll * 256), false, "bits 64 -> 256, 16 maps of 56 x 56");
-    check(direct_behind_on_bits(1, 3, 802816ll * 256), false, "bits 96 -> 256, 256 maps of 56 x 56");
-    check(direct_behind_on_bits(3, 1, 802816ll * 256), false, "bits 3x3, 32 -> 256, 256 maps of 56 x 56");
+    check(direct_behind_on_bits(1, 2, 64, 802816ll * 64), true, "bits 64 -> 64, 256 maps of 56 x 56");
+    check(direct_behind_on_bits(1, 1, 128, 200704ll * 128), true, "bits 32 -> 128, 64 maps of 56 x 56");
+    check(direct_behind_on_bits(1, 2, 512, 200704ll * 512), true, "bits 64 -> 512, 64 maps of 56 x 56");
+    check(direct_behind_on_bits(1, 1, 256, 3136ll * 256), false, "bits 32 -> 256, one map of 56 x 56");
+    check(direct_behind_on_bits(1, 2, 256, 50176ll * 256), false, "bits 64 -> 256, 16 maps of 56 x 56");
+    check(direct_behind_on_bits(1, 2, 16, 802816ll * 16), true, "bits 64 -> 16, 256 maps of 56 x 56");
+    check(direct_behind_on_bits(1, 3, 256, 802816ll * 256), false, "bits 96 -> 256, 256 maps of 56 x 56");
+    check(direct_behind_on_bits(3, 1, 256, 802816ll * 256), false, "bits 3x3, 32 -> 256, 256 maps of 56 x 56");
     check(direct_behind_on_float_module(1, 2, 64, true, false, true, 802816ll * 64), true, "module without stream, 64 -> 64");
     check(direct_behind_on_float_module(1, 1, 64, true, true, false, 95648ll * 64), true, "module without bits, 15 -> 64");
     check(direct_behind_on_float_module(1, 2, 512, false, true, true, 752640ll * 512), true, "module without identity, 64 -> 512");
