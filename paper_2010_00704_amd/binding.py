@@ -107,11 +107,17 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The raw handle of torch's current stream, without the Stream object around it: that object cost 2.7 us of the
+# 7.1 us a call took to enqueue, more than the rest of the marshalling together.  torch's own code calls this function
+# but does not document it, so a version without it gets the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    # The raw handle of torch's current stream, without the Stream object around it: that object cost 2.7 us of
-    # the 7.1 us a call took to enqueue, more than the rest of the marshalling together.
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
