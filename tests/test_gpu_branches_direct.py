@@ -1,6 +1,6 @@
 """Branch sums on the matrix cores without LDS staging, through the calls that AUTO routes to it, against the oracle:
 words per lane half around a group of four (single words, whole groups, both), odd word counts, every pad mode, own and
-shared tensors, the three tiles, ragged channels and pixels, operands at 4-byte alignment."""
+shared tensors, ragged channels and pixels, operands at 4-byte alignment.  (Its tiles: test_gpu_direct_tiles.py.)"""
 import random
 
 import numpy as np
@@ -31,8 +31,8 @@ SHAPES = [
     (1, 480, 6, 7, 70, 3, 1, 9, False),      # fifteen
     (1, 736, 5, 5, 32, 3, 1, 9, True),       # twenty-three
     (3, 992, 3, 4, 96, 1, 1, 4, True),       # thirty-one
-    (60, 128, 28, 28, 96, 3, 1, 9, False),   # two channel blocks per wave
-    (20, 512, 28, 28, 288, 1, 1, 3, False),  # 2 x 2 blocks per wave, ragged last channel tile
+    (60, 128, 28, 28, 96, 3, 1, 9, False),   # many workgroups, three channel blocks
+    (20, 512, 28, 28, 288, 1, 1, 3, False),  # parallel branches, many workgroups
 ]
 
 

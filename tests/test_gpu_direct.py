@@ -1,6 +1,7 @@
 """The matrix-core convolution without LDS staging, through the calls that AUTO routes to it, against the oracle:
 channel counts around every unit of its K walk (words per tap 1 to 12, with and without tail bits), pixel and channel
-counts around its 32 x 32 blocks and its 128-pixel workgroups, strides, borders, operands at 4-byte alignment."""
+counts around its 32 x 32 blocks and its 128-pixel workgroups, strides, borders, operands at 4-byte alignment.  (Every
+tile with every walk: test_gpu_direct_tiles.py.)"""
 import numpy as np
 import pytest
 import torch

@@ -89,12 +89,12 @@ def gpu_module(dev, x, wt, stride, pad, g, b, ident, alpha, c, half, variant, wa
 
 MODULE_SHAPES = [
     # n, c_in, h, w, c_out, k, stride, pad
-    (2, 128, 24, 24, 128, 1, 1, 0),    # the paper's 1x1 module, matrix-core path
+    (2, 128, 24, 24, 128, 1, 1, 0),    # the paper's 1x1 module
     (1, 256, 33, 31, 64, 1, 1, 0),
     (2, 128, 23, 23, 192, 3, 1, 1),
     (3, 256, 20, 20, 100, 3, 2, 1),    # ragged c_out on the matrix-core path
     (1, 128, 40, 40, 70, 1, 2, 0),
-    (2, 64, 14, 14, 64, 1, 1, 0),      # vector-ALU path
+    (2, 64, 14, 14, 64, 1, 1, 0),      # two words per pixel
     (3, 33, 9, 7, 40, 3, 1, 1),
     (1, 100, 12, 12, 7, 1, 1, 0),
     (40, 96, 14, 14, 96, 3, 1, 1),     # two pixels per lane on the vector-ALU path

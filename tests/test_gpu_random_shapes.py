@@ -213,7 +213,7 @@ def test_random_branches(dev, seed):
 
 TINY = [
     # n, c_in, h, w, c_out, k, stride, pad: problems far smaller than one matrix-core tile, which AUTO
-    # still sends to the matrix-core kernel whenever the channel count allows it
+    # still sends to the matrix cores
     (1, 128, 1, 1, 1, 1, 1, 0),
     (1, 128, 1, 1, 32, 1, 1, 0),
     (1, 256, 1, 2, 100, 1, 1, 0),
@@ -250,7 +250,7 @@ def test_tiny_problems_on_every_path(dev, shape):
         if rc != B.BCNN_ERR_UNSUPPORTED or v in COVER_ALL:
             B.check(rc, "fused")
             assert np.array_equal(bits.get(np.uint32).reshape(want_bits.shape), want_bits), "variant %d bits" % v
-    # the module call on the same tiny problem (AUTO stays on the vector ALUs here, the matrix cores are forced)
+    # the module call on the same tiny problem, on AUTO's choice and on both forced paths
     _, ho, wo, _ = y.shape
     m = n * ho * wo
     g = W.uniform_f32(seed + 3, (o,), -1.5, 1.5)
