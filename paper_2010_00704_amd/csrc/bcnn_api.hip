@@ -347,8 +347,8 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
     const bool mfma_ok = bcnn::conv_mfma_fp4_supported(s, x_packed, w_packed);
     switch (variant) {
         case BCNN_VARIANT_AUTO: {
-            // 1x1 modules of up to 256 input channels are bound by their real stream: the streaming kernel is ahead
-            // of every other at all 64 sizes measured, or level with the direct one at the smallest.  The
+            // 1x1 modules of up to 256 input channels are bound by their real stream: the streaming kernel is ahead of
+            // every other or level at all but 3 of 1098 calls measured (0.92 times the staged kernel at worst).  The
             // staged kernel has a plain form (whole 128-channel tiles, every part of the module present) and a general
             // one; direct_plan.h weighs both.  Large float streams: auto_plan.h.
             if (bcnn::conv_mfma_stream_supported(s, m)) {

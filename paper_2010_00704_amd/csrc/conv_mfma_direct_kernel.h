@@ -18,16 +18,18 @@
 // Bound: latency for the small launches, vector-ALU issue (expansion, about seven instructions per MFMA with
 // 2 x 2 blocks a wave) and the loads' latency for the large ones, HBM and the epilogue for module outputs of small K.
 // Measured (graph replays, us, against the kernel that ran the call before): 3x3, 1024 -> 1024, one 7 x 7 image
-// 25.2 -> 5.1; 3x3, 320 -> 200, 13 maps of 27 x 27 47.7 -> 11.3; 3x3, 64 -> 64, one 14 x 14 image 6.3 -> 4.4 (sums)
+// 25.2 -> 5.1; 3x3, 320 -> 200, 13 maps of 27 x 27 47.7 -> 10.1 (8.9 among other calls); 3x3, 64 -> 64, one 14 x 14 image 6.3 -> 4.4 (sums)
 // and 10.3 -> 4.5 (bits); 3x3, 832 -> 224, 22 maps of 30 x 30 232 -> 27; 1x1 module, 1024 channels, 32 maps of
 // 7 x 7 11.5 -> 7.5.  At least two workgroups of a SIMD are asked for in the launch bounds: without that the compiler
 // keeps the accumulators in the accumulation registers and copies them (2 x 1 blocks: 84 registers a lane instead of
-// 96, the first two calls above 5.1 -> 4.9 and 11.3 -> 10.1, the third 4.4 -> 2.9).
+// 96; the second call above took 11.3 before that, the third takes 2.9 since).
 // Buffer accesses in the epilogue instead of predicated ones: float module, 1x1, 256 channels, 32 maps of 56 x 56 (1 x 1
 // blocks) 39.3 -> 33.2, half, 64 channels, 112 x 112 30.9 -> 24.8; sums, 1x1, 256 -> 256, 32 maps of 56 x 56 19.3 (staged 22.5).
 // Branch mode, 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 us in the staged kernel, 33 here (a tap's fold
 // there exchanges its corrections through LDS and costs more than the tap's matrix work); 512 channels, 64 maps of
-// 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.
+// 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.  The check of a tap's last words
+// (branch_walk.h) is 1 % of the first of these (33.2 -> 33.7); 224 channels, whose taps are single words only, -> 128, 16
+// maps of 14 x 14, 12.5 against 66.5 on the vector ALUs.
 #pragma once
 #include "bcnn_common.h"
 #include "branch_walk.h"

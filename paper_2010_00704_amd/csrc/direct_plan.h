@@ -29,7 +29,9 @@ enum { KIND_BITS_OUT = 0, KIND_SUMS_OUT = 1, KIND_MODULE_PLAIN = 2, KIND_MODULE_
 // wave's set-up and epilogue and its chunks where more waves than SIMDs (1024) share the issue slots.  The four
 // numbers of each tile and kind of output are least-squares fits over 158 measured launches (graph replays, outputs on
 // rotating buffers; 1x1 and 3x3, strides 1 and 2, 32 to 1024 channels on both sides, 25 to 430 000 pixels; rms error 8 to
-// 15 %); choosing by them costs 1 % over the best of the tiles on average and 20 % at worst.
+// 15 %); choosing by them costs 1 % over the best of the tiles on average and 20 % at worst.  (To fit them again: time every
+// tile, forced in the launcher, over such launches, and solve for the four numbers by non-negative least squares on the
+// relative error.)
 struct DirectCost { double fixed, chunk, wave, wave_chunk; };
 struct DirectTile { int tile, cb, pb, wc, wp, wk; DirectCost kind[3]; };     // kind: packed bits, int32 sums, module
 static const DirectTile DIRECT_TILES[] = {

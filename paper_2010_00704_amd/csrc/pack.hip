@@ -53,7 +53,8 @@ __device__ __forceinline__ void static_for(F&& f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// `old` with the wave-uniform `word` in lane LANE
+// `old` with the wave-uniform `word` in lane LANE.  (The words come from a scalar AND, not from a comparison directly: a
+// mask that a vector instruction wrote could not be read here at once.)
 template <int LANE>
 __device__ __forceinline__ uint32_t writelane(uint32_t word, uint32_t old)
 {
@@ -352,13 +353,14 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(
 // along the row, and with it its eight biases, is the same for all its rows: the block's 256 threads are cut into
 // runs of `per_row` threads, one run per row, and a thread takes one row per pass, all passes' loads in flight
 // before the first is used.  Replicated channels read the source row again (channel c reads c mod src_channels).
-// HBM bound.  Graph replays, us, against the kernels that ran these calls before: half, 128 channels with bias, 100 352
-// rows 8.0 -> 4.2 (6.5 TB/s); bfloat16 11.4 -> 4.1; replicated twice from 25 088 rows 9.6 -> 3.2; int8, 256
-// channels, 200 000 rows 50.9 -> 10.2; float, 128 channels 11.2 -> 9.5.  Four passes: one is 5.0 on the first of
-// these, two 4.4, eight 4.4, and on 300 rows all are level.
+// HBM bound.  Graph replays, us, against the kernels that ran these calls before, on rotating buffers beyond the last-level
+// cache: half, 64 channels with bias, 312 500 rows 13.4 -> 9.2 (4.6 TB/s); replicated twice from 156 250 rows 30.5 -> 6.8;
+// int8, 1000 channels, 20 000 rows 27.9 -> 7.0; float, 64 channels, 312 500 rows 18.7 -> 15.9 (5.2 TB/s).  From the
+// cache: half, 128 channels, 100 352 rows 8.0 -> 4.2; four passes there: one is 5.0, two 4.4, eight 4.4, and on 300 rows
+// all are level.
 // Every access is a raw buffer access with a 32-bit offset from the block's first row: what does not exist (rows past
 // the end, channels past the last row's end) reads as zero and stores nothing, without branches between the loads;
-// the first form of this kernel, with predicated loads, took 8.4 us where this one takes 4.2.
+// the first form of this kernel, with predicated loads, took 8.4 us where this one takes 4.2 (both from the cache).
 constexpr int LAST8_PASSES = 4;
 // rows a whole number of dwords apart; the eight channels of a thread must not wrap inside a replica; 256 threads a row
 bool last8_applies(size_t esz, const void* src, int64_t channels, int64_t src_channels)
@@ -373,7 +375,6 @@ __global__ __launch_bounds__(256) void pack_last8_kernel(
     int cw, int per_row, int rows_per_pass, DivBy div_row, uint32_t* __restrict__ dst)
 {
     typedef T t8 __attribute__((ext_vector_type(8)));
-    typedef int v4i __attribute__((ext_vector_type(4)));
     typedef float f4 __attribute__((ext_vector_type(4)));
     constexpr int ESZ = (int)sizeof(T);
     constexpr int PASSES = LAST8_PASSES;

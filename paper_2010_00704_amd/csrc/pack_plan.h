@@ -19,8 +19,8 @@ constexpr int64_t MAX_BLOCKS_256 = (1 << 24) - 1;
 // neighbouring tiles of a row x the rest along the groups of 64 channels.
 struct BallotPlan { int nv, tw_shift, groups, tiles; int64_t blocks_per_image; };
 
-// Whether the ballot kernel is ahead of the kernel that the call would take otherwise, from 1872 calls (float, half and
-// int8, rows of 2 to 64 positions, 1 to 1024 channels, 1e5 to 2e7 elements; us there and here).
+// Whether the ballot kernel is ahead of the kernel that the call would take otherwise, from 4347 calls (float, half and
+// int8, rows of 2 to 784 positions, 1 to 1024 channels, 1e5 to 2e7 elements; us there and here).
 inline bool ballot_pays(int esz, int64_t blocks, int64_t outer, int64_t channels, int64_t inner)
 {
     // Up to four positions the other kernel has a thread per word.  Here a workgroup costs 0.52 ns of the launch whatever it

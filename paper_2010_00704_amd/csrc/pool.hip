@@ -183,8 +183,9 @@ __global__ __launch_bounds__(256) void avgpool_pack4_kernel(const T* __restrict_
 // of one output pixel (one 16-byte load per window element), four threads a packed word; the block's threads are cut
 // into runs of `per_px`, one run per output pixel.  All accesses are raw buffer accesses from the block's first window
 // on (what does not exist reads zero and stores nothing): no branches between the loads.  A window of 4 or 16 elements
-// is divided by a multiplication (by a power of two: the same result).  HBM bound: half, 2 x 2, 128 channels, 32 maps of
-// 56 x 56 6.4 -> 5.1 us (6.4 TB/s), 64 channels, 32 maps of 112 x 112 12.6 -> 11.4; two pixels a thread 5.5 and 11.8.
+// is divided by a multiplication (by a power of two: the same result).  HBM bound: half, 2 x 2, 64 channels, 99 maps of
+// 56 x 56 12.6 -> 11.1 us from memory (4.5 TB/s); 128 channels, 32 maps of 56 x 56 6.4 -> 5.1 from the last-level cache; two
+// pixels a thread 5.5 there.
 template <typename T> struct pool_vec { using type = T; };
 template <> struct pool_vec<__half> { using type = _Float16; };
 template <typename T, int SF>
