@@ -5,6 +5,7 @@
 #include "auto_plan.h"
 #include "bcnn_common.h"
 #include "conv_mfma_direct.h"
+#include "conv_mfma_shared.h"
 
 #include <limits.h>
 
@@ -59,15 +60,18 @@ int conv_entry(const bcnn_conv_desc* desc, const uint32_t* x, const uint32_t* w,
     hipError_t e;
     switch (variant) {
         case BCNN_VARIANT_AUTO: {
-            // Two matrix-core kernels: the staged one for launches that fill the chip (C_in a multiple of
-            // 128), the direct one for small launches and every other channel count; conv_mfma_direct.hip
-            // weighs them by fitted times.  The vector ALUs take packed bits of one or two words (auto_plan.h),
+            // Three matrix-core forms: the staged kernel for launches that fill the chip (C_in a multiple of
+            // 128), the direct one for small launches and every other channel count, and its form with shared weights
+            // for the larger of those; direct_plan.h and shared_plan.h weigh them by fitted times.  The vector ALUs take packed bits of one or two words (auto_plan.h),
             // tensors beyond 31-bit offsets and sums beyond fp32.
             const bool staged = conv_mfma_fp4_supported(s, x, w);
             const bool direct = conv_mfma_direct_supported(s) && !(fused && direct_behind_on_bits(s.ks, s.cw, s.c_out, (int64_t)s.m * s.c_out));
-            const int tile = direct ? conv_mfma_direct_choose(s, fused ? KIND_BITS_OUT : KIND_SUMS_OUT, staged) : DIRECT_NONE;
-            if (tile != DIRECT_NONE)
-                e = launch_conv_mfma_direct(s, x, w, fused ? thr : nullptr, out, nullptr, tile, st);
+            const DirectChoice choice = direct ? conv_mfma_direct_choose(s, fused ? KIND_BITS_OUT : KIND_SUMS_OUT, staged) : DirectChoice{DIRECT_NONE, 0.0};
+            const int shared = direct ? conv_mfma_shared_choose(s, fused ? SHARED_BITS : SHARED_SUMS, choice) : SHARED_NONE;
+            if (shared != SHARED_NONE)
+                e = launch_conv_mfma_shared(s, x, w, fused ? thr : nullptr, out, nullptr, shared, st);
+            else if (choice.tile != DIRECT_NONE)
+                e = launch_conv_mfma_direct(s, x, w, fused ? thr : nullptr, out, nullptr, choice.tile, st);
             else if (staged)
                 e = launch_conv_mfma_fp4(s, x, w, fused ? thr : nullptr, out, nullptr, 0, st);
             else
@@ -350,7 +354,7 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
             // 1x1 modules of up to 256 input channels are bound by their real stream: the streaming kernel is ahead of
             // every other or level at all but 3 of 1098 calls measured (0.92 times the staged kernel at worst).  The
             // staged kernel has a plain form (whole 128-channel tiles, every part of the module present) and a general
-            // one; direct_plan.h weighs both.  Large float streams: auto_plan.h.
+            // one; direct_plan.h weighs both, shared_plan.h the form with shared weights.  Large float streams: auto_plan.h.
             if (bcnn::conv_mfma_stream_supported(s, m)) {
                 e = bcnn::launch_conv_mfma_stream(s, x_packed, w_packed, m, st);
                 break;
@@ -358,9 +362,12 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
             const bool plain = mfma_ok && s.c_out % 128 == 0 && m.identity && m.r && m.x_next && m.id_channels % 4 == 0;
             const bool direct = bcnn::conv_mfma_direct_supported(s) &&
                 !(m.half == bcnn::REAL_F32 && bcnn::direct_behind_on_float_module(s.ks, s.cw, s.c_out, m.identity, m.r, m.x_next, (int64_t)s.m * s.c_out));
-            const int tile = direct ? bcnn::conv_mfma_direct_choose(s, plain ? bcnn::KIND_MODULE_PLAIN : bcnn::KIND_MODULE_GENERAL, mfma_ok) : bcnn::DIRECT_NONE;
-            if (tile != bcnn::DIRECT_NONE)
-                e = bcnn::launch_conv_mfma_direct(s, x_packed, w_packed, nullptr, nullptr, &m, tile, st);
+            const bcnn::DirectChoice choice = direct ? bcnn::conv_mfma_direct_choose(s, plain ? bcnn::KIND_MODULE_PLAIN : bcnn::KIND_MODULE_GENERAL, mfma_ok) : bcnn::DirectChoice{bcnn::DIRECT_NONE, 0.0};
+            const int shared = direct ? bcnn::conv_mfma_shared_choose(s, m.half ? bcnn::SHARED_HALF : bcnn::SHARED_FLOAT, choice) : bcnn::SHARED_NONE;
+            if (shared != bcnn::SHARED_NONE)
+                e = bcnn::launch_conv_mfma_shared(s, x_packed, w_packed, nullptr, nullptr, &m, shared, st);
+            else if (choice.tile != bcnn::DIRECT_NONE)
+                e = bcnn::launch_conv_mfma_direct(s, x_packed, w_packed, nullptr, nullptr, &m, choice.tile, st);
             else if (mfma_ok)
                 e = bcnn::launch_conv_mfma_fp4(s, x_packed, w_packed, nullptr, nullptr, &m, 0, st);
             else

@@ -7,8 +7,8 @@
 namespace bcnn {
 
 bool conv_mfma_direct_supported(const ConvShape& s);
-// A tile, or DIRECT_NONE: the staged kernel (direct_plan.h).
-int conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged);
+// A tile and its estimated time, or DIRECT_NONE: the staged kernel (direct_plan.h).
+DirectChoice conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged);
 // thr == nullptr: int32 sums, else packed bits; ep != nullptr: module epilogue (thr and out are ignored)
 hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream);

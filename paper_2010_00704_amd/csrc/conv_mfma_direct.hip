@@ -47,7 +47,7 @@ bool conv_mfma_direct_supported(const ConvShape& s)
     return s.c_out <= (1 << 20) && (n_words + 3 * s.ks * s.ks + 8) * 32 < (1 << 22) && x_bytes < (1ll << 31) && w_bytes < (1ll << 31);
 }
 
-int conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged) { return direct_choose(s.m, s.c_out, s.cw, s.ks, kind, staged); }
+DirectChoice conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged) { return direct_estimate(s.m, s.c_out, s.cw, s.ks, kind, staged); }
 
 hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream)

@@ -25,6 +25,20 @@
 // 96; the second call above took 11.3 before that, the third takes 2.9 since).
 // Buffer accesses in the epilogue instead of predicated ones: float module, 1x1, 256 channels, 32 maps of 56 x 56 (1 x 1
 // blocks) 39.3 -> 33.2, half, 64 channels, 112 x 112 30.9 -> 24.8; sums, 1x1, 256 -> 256, 32 maps of 56 x 56 19.3 (staged 22.5).
+// Shared weights (WIDE > 0): the larger launches of those.  There every wave expanded both operands for itself, seven
+// instructions a fragment, and read its weight rows 16 bytes to a cache line: vector issue and L1 look-ups bound it at three
+// to six times the matrix cores' time.  Now a workgroup expands a stage of weights once, into LDS, for its four waves, which
+// lie along the pixels: a fragment is one 16-byte LDS read, and what is left of the expansion is the inputs'.  Two stages
+// in turn, one barrier each (LDS only: loads stay in flight across it); a 2 x 2 tile keeps LDS reads at half of their rate
+// (2 x 1: all of it, and still level, because its launches balance better).  Weights of words that do not exist are 0.0, so the
+// walk needs no masks on the inputs and no constant afterwards; bits start their sums at 1/2 - threshold and leave as signs,
+// without a turn through LDS.  Phase clocks of 3x3, 256 -> 256, 784 workgroups: set-up 3400 cycles, the loop 36 to 40 cycles per
+// MFMA and SIMD with two to four workgroups a compute unit (the instruction's own rate is 35.4), end 30: the launch is
+// bound by what the dispatcher leaves uneven (two to four workgroups a compute unit where three would do).
+// Measured (us, before and after): bits, 3x3, 320 -> 192, 39 maps of 38 x 38 27.9 -> 16.3; 220 -> 64, 440 000 pixels 45 -> 27; 1x1,
+// 704 -> 704, 40 maps of 26 x 26 14.9 -> 10.8; sums, 3x3, 468 -> 39, 191 maps of 37 x 36 52 -> 38; half module, 3x3, 131 -> 256,
+// 97 500 pixels 49 -> 41.  Tried: 4 x 2 and 2 x 4 blocks a wave (one wave per SIMD takes 67 cycles per MFMA, waiting for LDS
+// and barriers; nowhere ahead), halves of a tap side by side in 32-byte pieces (wide rows no faster, all rows 3 % slower).
 // Branch mode, 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 us in the staged kernel, 33 here (a tap's fold
 // there exchanges its corrections through LDS and costs more than the tap's matrix work); 512 channels, 64 maps of
 // 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.  The check of a tap's last words
@@ -57,17 +71,21 @@ struct DirectArgs {
     int32_t pad_bytes;
 };
 
-// Branch mode: per-branch scales, bias, what a tap outside the image stands for.
+// What only some forms of the kernel read.  Branch mode: per-branch scales, bias, what a tap outside the image stands for;
+// shared weights: how a tap's words are split (shared_plan.h).
 struct DirectBranch {
     const float* scale;         // [taps][c_out]
     const float* bias;          // [c_out] or nullptr
     const uint32_t* pad_words;  // [taps][cw] (PAD_OPERAND)
+    int32_t half;               // words of the longer lane half
+    uint32_t last_bits;         // channels of a pixel's last word
 };
 
 namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v3i __attribute__((ext_vector_type(3)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -85,8 +103,8 @@ __device__ __forceinline__ int row_to_channel(int i) { return 16 * ((i >> 2) & 1
 
 // A wave owns CB x PB blocks of 32 channels x 32 pixels; a workgroup WC x WP such tiles, each shared by WK
 // waves that split K.
-template <int CB, int PB, int WC, int WP, int WK, int OUT, int MODE>
-__global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
+template <int CB, int PB, int WC, int WP, int WK, int OUT, int MODE, int WIDE = 0>
+__global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OUT != OUT_MODULE) ? 3 : 2) void conv_mfma_direct_kernel(
     DirectArgs a, const uint32_t* __restrict__ x, const uint32_t* __restrict__ w,
     const int32_t* __restrict__ thr, void* __restrict__ out, ModuleEp ep, DirectBranch br)
 {
@@ -103,7 +121,14 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
     // every wave turns one pixel block at a time around in a region of its own.
     constexpr int ROW = TCH + 4;                             // floats; rows stay 16-byte aligned, banks skewed by 4
     constexpr int REGION = (WK > 1 ? TPX : 32) * ROW;
-    __shared__ __align__(16) float lds[WC * WP * WK * REGION];
+    constexpr bool SHARED = WIDE > 0;
+    static_assert(!SHARED || (WC == 1 && WK == 1), "shared weights: the workgroup's waves lie along the pixels");
+    constexpr int SG = SHARED ? WP / CB : 1;                 // groups of a stage: every thread expands one unit of it
+    constexpr int STEPS = WIDE < 3 ? 4 : WIDE;               // K-steps of a group
+    constexpr int STAGE = SG * STEPS * CB * 1024;            // bytes
+    constexpr bool SIGN_OUT = SHARED && OUT == OUT_BITS && !BR;
+    constexpr int EP_FLOATS = SIGN_OUT ? 0 : WC * WP * WK * REGION;
+    __shared__ __align__(16) float lds[EP_FLOATS > 2 * STAGE / 4 || !SHARED ? EP_FLOATS : 2 * STAGE / 4];
 
     const ConvShape& s = a.s;
     const int t = threadIdx.x;
@@ -122,10 +147,18 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
     const int o0 = (tile - ptile * a.n_ctiles) * (TCH * WC) + TCH * wc;   // first channel and pixel of the wave's tile
     const int m0 = ptile * (TPX * WP) + TPX * wp;
 
+    // shared weights: what a channel's sums start from is asked for first (see below)
+    int start = 0;
+    if constexpr (SHARED && (BR || SIGN_OUT)) {
+        const void* from = BR ? static_cast<const void*>(br.bias) : thr;
+        const auto res = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(from), 0, from ? s.c_out * 4 : 0, 0x00020000);
+        start = (int)__builtin_amdgcn_raw_buffer_load_b32(res, (o0 + t) * 4, 0, 0);
+    }
+
     // ---- the lane's rows
     int wrow[CB];                                            // word offset of the weight row
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
+    for (int cb = 0; cb < CB && !SHARED; ++cb) {
         const int ch = o0 + 32 * cb + row_to_channel(j);
         wrow[cb] = (ch < s.c_out ? ch : s.c_out - 1) * a.n_words;
     }
@@ -137,7 +170,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
         m = m < s.m ? m : s.m - 1;
         if (s.ks == 1 && s.stride == 1) {
             rbase[pb] = m * s.cw;
-            vmask[pb] = 1u;
+            vmask[pb] = 0xFFFFu;
         } else {
             const int hw = s.ho * s.wo;
             const int n = a.div_hw(m);
@@ -146,7 +179,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             const int ph = oh * s.stride - s.pad;
             const int pw = (r - oh * s.wo) * s.stride - s.pad;
             rbase[pb] = ((n * s.h + ph) * s.w + pw) * s.cw;
-            uint32_t vm = 1u;                                // 1x1: no padding, always inside
+            uint32_t vm = 0xFFFFu;                           // 1x1: no padding, every branch is inside
             if (s.ks == 3) {
                 uint32_t cols = 0;
                 vm = 0;
@@ -300,7 +333,249 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
             }
         }
     };
-    if constexpr (!BR) {
+    if constexpr (SHARED) {
+        // Weights: a stage of SG groups of four K-steps is expanded once for all waves, in LDS, double buffered; thread t
+        // expands four words of row t % (32 CB), fetched a stage ahead.  Inputs: every wave's own rows, a group in
+        // registers two groups ahead.  Words that do not exist (the shorter half's last one, groups past the end,
+        // channels past c_in) are 0.0 on the weights' side, whatever the input's words are: no constant is left to correct.
+        constexpr bool NARROW = WIDE < 3;                    // several taps a group
+        constexpr int ROWS = 32 * CB, TPG = NARROW ? 4 / WIDE : 1;
+        char* const stage = reinterpret_cast<char*>(lds);
+        const int urow = t % ROWS, unit = ROWS >= 64 ? wave / (ROWS / 64) : t / ROWS;
+        const int ugroup = unit >> 1, uhalf = unit & 1;
+        int urow_words;
+        {
+            const int ch = o0 + (urow & ~31) + row_to_channel(urow & 31);
+            urow_words = (ch < s.c_out ? ch : s.c_out - 1) * a.n_words;
+        }
+        const int n_groups = a.n_units;
+        const int tap_words = a.tap_step + (s.ks == 3 ? s.cw : 0), row_words = s.ks == 3 ? a.row_jump : 0;
+        // word offset of a tap in the input, from the window's top-left one; (11 tap) >> 5 is tap / 3 up to 8
+        auto tap_at = [&](int tap) __attribute__((always_inline)) { return tap * tap_words + ((tap * 11) >> 5) * row_words; };
+        int rb[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) rb[pb] = (rbase[pb] + hsel * br.half) * 4;
+        const auto pres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(br.pad_words), 0, PAD == PAD_OPERAND ? a.pad_bytes : 0, 0x00020000);
+        auto load_words = [&](auto res, int off, auto& v, int at) __attribute__((always_inline)) {
+            if constexpr (WIDE >= 4) {
+                const v4i q = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(res, off, 0, 0));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = q[i];
+                if constexpr (WIDE == 5) v[4] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, off, 16, 0);
+            } else if constexpr (WIDE == 3) {
+                const v3i q = __builtin_bit_cast(v3i, __builtin_amdgcn_raw_buffer_load_b96(res, off, 0, 0));
+#pragma unroll
+                for (int i = 0; i < 3; ++i) v[i] = q[i];
+            } else if constexpr (WIDE == 2) {
+                const v2i q = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(res, off, 0, 0));
+                v[at] = q[0];
+                v[at + 1] = q[1];
+            } else v[at] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, off, 0, 0);
+        };
+        struct Inputs { int x[PB][STEPS]; };
+        auto fetch_x = [&](int gi, Inputs& c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < TPG; ++i) {
+                const int tap = NARROW ? gi * TPG + i : a.div_tap(gi);
+                const int k = NARROW ? 0 : WIDE * (gi - tap * a.per_tap);
+                const int bit = tap < a.taps ? tap : 31;     // (bit 31 is never set)
+                const int xo = (tap_at(tap) + k) * 4;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    const int in = __builtin_amdgcn_sbfe((int)vmask[pb], (uint32_t)bit, 1u);     // all bits or none
+                    load_words(xres, ((rb[pb] + xo) & in) | (~in & -16), c.x[pb], i * WIDE);
+                    if constexpr (PAD == PAD_OPERAND) {
+                        if (s.ks == 3) {
+                            int p[STEPS];
+                            load_words(pres, (((tap * s.cw + hsel * br.half + k) * 4) & ~in) | (in & -16), p, i * WIDE);
+#pragma unroll
+                            for (int q = i * WIDE; q < (i + 1) * WIDE; ++q) c.x[pb][q] |= p[q];
+                        }
+                    }
+                }
+            }
+        };
+        auto fetch_w = [&](int st, int (&v)[STEPS]) __attribute__((always_inline)) {
+            const int gi = st * SG + ugroup;
+#pragma unroll
+            for (int i = 0; i < TPG; ++i) {
+                const int tap = NARROW ? gi * TPG + i : a.div_tap(gi);
+                const int k = tap * s.cw + uhalf * br.half + (NARROW ? 0 : WIDE * (gi - tap * a.per_tap));
+                load_words(wres, (urow_words + k) * 4, v, i * WIDE);
+            }
+        };
+        const int uwords = uhalf ? s.cw - br.half : br.half;   // words of a tap that this thread's half has
+        auto put_w = [&](int st, const int (&v)[STEPS]) __attribute__((always_inline)) {
+            const int gi = st * SG + ugroup;
+            char* const to = stage + (st & 1) * STAGE + ugroup * (STEPS * CB * 1024) + (urow >> 5) * 1024 + (uhalf * 32 + (urow & 31)) * 16;
+            const int tap0 = NARROW ? gi * TPG : a.div_tap(gi), k0 = NARROW ? 0 : WIDE * (gi - tap0 * a.per_tap);
+            const int last = NARROW ? tap0 + TPG - 1 : tap0;
+            // the common case in front: every word exists and is whole
+            const bool whole = (last < a.taps) & (NARROW ? uwords == WIDE : k0 + WIDE <= uwords) & ((br.last_bits == ~0u) | (uhalf * br.half + k0 + WIDE < s.cw));
+            if (whole) {
+#pragma unroll
+                for (int i = 0; i < STEPS; ++i) {
+                    const v8i c = expand((uint32_t)v[i]);
+                    *reinterpret_cast<v4i*>(to + i * (CB * 1024)) = v4i{c[0], c[1], c[2], c[3]};
+                }
+                return;
+            }
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i) {
+                const int tap = NARROW ? tap0 + i / WIDE : tap0;
+                const int k = k0 + (NARROW ? i % WIDE : i);  // within the half
+                const bool real = tap < a.taps && k < uwords;
+                const uint32_t bits = real ? (uhalf * br.half + k == s.cw - 1 ? br.last_bits : ~0u) : 0u;
+                const uint32_t word = (uint32_t)v[i];
+                v4i code;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const uint32_t sign = (bits << (3 - jj)) & 0x88888888u;
+                    code[jj] = (int)(((word << (3 - jj)) & sign) | (sign >> 2));
+                }
+                *reinterpret_cast<v4i*>(to + i * (CB * 1024)) = code;
+            }
+        };
+        // weight fragments of a K-step, read one step ahead
+        struct Fragments { v4i f[CB]; };
+        auto read_w = [&](const char* from, int ks, Fragments& fw) __attribute__((always_inline)) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) fw.f[cb] = *reinterpret_cast<const v4i*>(from + (ks * CB + cb) * 1024 + lane * 16);
+        };
+        auto step = [&](const Fragments& fw, const Inputs& c, int ks, bool first) __attribute__((always_inline)) {
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                const v8i fx = expand((uint32_t)c.x[pb][ks]);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    const v8i w8 = {fw.f[cb][0], fw.f[cb][1], fw.f[cb][2], fw.f[cb][3], 0, 0, 0, 0};
+                    const v16f from_zero = {};
+                    acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w8, fx, first ? from_zero : acc[cb][pb], 4, 4, 0, 0, 0, 0);
+                }
+            }
+        };
+        // branch mode: a completed tap's sums join the total, tot = fma(scale, y_t, tot) in the order t = 0, 1, ...
+        __shared__ __align__(16) float scale_lds[BR ? MAX_BRANCHES : 1][TCH];
+        auto fold = [&](int tap) __attribute__((always_inline)) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v4f sc = *reinterpret_cast<const v4f*>(&scale_lds[tap][32 * cb + 16 * hsel + 4 * q]);
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) {
+                        const bool in = PAD != PAD_NOTHING || ((vmask[pb] >> tap) & 1u);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float zn = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
+                            tot[cb][pb][4 * q + k] = in ? zn : tot[cb][pb][4 * q + k];
+                        }
+                    }
+                }
+        };
+        auto group = [&](int gi, const char* from, const Inputs& c) __attribute__((always_inline)) {
+            Fragments fw[2];
+            read_w(from, 0, fw[0]);
+            const int tap0 = NARROW ? gi * TPG : a.div_tap(gi), g = NARROW ? 0 : gi - tap0 * a.per_tap;
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k) {
+                const int tap = NARROW ? tap0 + k / WIDE : tap0;
+                if (k + 1 < STEPS) read_w(from, k + 1, fw[(k + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (!NARROW || k < WIDE || tap < a.taps) {   // (a group of narrow taps may reach past the last one)
+                    if (BR && (NARROW ? k % WIDE == 0 : k == 0 && g == 0)) step(fw[k & 1], c, k, true);
+                    else step(fw[k & 1], c, k, false);
+                    if constexpr (BR) {
+                        if (NARROW ? k % WIDE == WIDE - 1 : k == STEPS - 1 && g == a.per_tap - 1) fold(tap);
+                    }
+                }
+            }
+        };
+        int uw[STEPS];
+        Inputs ring[2];
+        fetch_w(0, uw);
+        fetch_x(0, ring[0]);
+        if constexpr (BR) {
+            for (int i = t; i < a.taps * TCH; i += 64 * WP) {
+                const int tp = i / TCH, cl = i - tp * TCH;
+                scale_lds[tp][cl] = br.scale[(size_t)tp * s.c_out + (o0 + cl < s.c_out ? o0 + cl : s.c_out - 1)];
+            }
+        }
+        // what a channel's sums start from: the bias, or what makes the sums' sign the output bit: sum - thr + 1/2
+        __shared__ __align__(16) float start_lds[BR || SIGN_OUT ? TCH : 1];
+        if constexpr (BR || SIGN_OUT) {
+            if (t < TCH) {
+                if constexpr (BR) start_lds[t] = __int_as_float(start);
+                else start_lds[t] = 0.5f - (float)min(max(start, -s.k), s.k + 1);
+            }
+        }
+        put_w(0, uw);
+        fetch_w(1, uw);
+        fetch_x(1, ring[1]);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if constexpr (BR || SIGN_OUT) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int q = 0; q < 16; q += 4) {
+                        const v4f v = *reinterpret_cast<const v4f*>(&start_lds[32 * cb + 16 * hsel + q]);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            if constexpr (BR) tot[cb][pb][q + k] = v[k];
+                            else acc[cb][pb][q + k] = v[k];
+                        }
+                    }
+        }
+        // `part` groups of a stage; the first one's inputs lie in ring[at]
+        auto walk = [&](int st, auto part, auto at) __attribute__((always_inline)) {
+            const char* from = stage + (st & 1) * STAGE;
+#pragma unroll
+            for (int i = 0; i < decltype(part)::value; ++i) {
+                const int gi = st * SG + i;
+                constexpr int R = decltype(at)::value;
+                group(gi, from + i * (STEPS * CB * 1024), ring[(i + R) & 1]);
+                if constexpr (decltype(part)::value == SG) {
+                    fetch_x(gi + 2, ring[(i + R) & 1]);
+                    if (i == 0) {
+                        put_w(st + 1, uw);
+                        fetch_w(st + 2, uw);
+                    }
+                }
+            }
+            // only LDS is shared: loads in flight stay in flight
+            if constexpr (decltype(part)::value == SG) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        };
+        using C0 = std::integral_constant<int, 0>;
+        using C1 = std::integral_constant<int, 1>;
+        using ALL = std::integral_constant<int, SG>;
+        const int n_full = n_groups / SG;
+        if constexpr (SG == 1) {
+            int st = 0;
+            for (; st + 1 < n_full; st += 2) {
+                walk(st, ALL{}, C0{});
+                walk(st + 1, ALL{}, C1{});
+            }
+            if (st < n_full) walk(st, ALL{}, C0{});
+        } else {
+            for (int st = 0; st < n_full; ++st) walk(st, ALL{}, C0{});
+        }
+        const int left = n_groups - n_full * SG;
+        if constexpr (SG > 1) {
+            if (left == 1) walk(n_full, C1{}, C0{});
+        }
+        if constexpr (SG == 4) {
+            using C2 = std::integral_constant<int, 2>;
+            if (left == 2) walk(n_full, C2{}, C0{});
+            if (left == 3) {
+                walk(n_full, C2{}, C0{});
+                fetch_x(n_full * SG + 2, ring[0]);
+                group(n_full * SG + 2, stage + (n_full & 1) * STAGE + 2 * (STEPS * CB * 1024), ring[0]);
+            }
+        }
+        if (left && !SIGN_OUT) __syncthreads();              // the epilogue's rows lie where the weights were
+    } else if constexpr (!BR) {
         // A wave takes the chunks wk, wk + WK, ...; AHEAD of them are in flight while one is multiplied.
         constexpr int AHEAD = (CB * PB == 1) ? 4 : 2;
         Chunk ring[AHEAD];
@@ -424,6 +699,40 @@ __global__ __launch_bounds__(64 * WC * WP * WK, 2) void conv_mfma_direct_kernel(
                 *reinterpret_cast<v4f*>(dst + (row0 + j) * ROW + 32 * cb + 16 * hsel + r) = v4f{v[r], v[r + 1], v[r + 2], v[r + 3]};
             }
     };
+    if constexpr (SIGN_OUT) {
+        const auto bits_res = rows_of(out, s.cwo * 4);
+        uint32_t half_word[CB][PB];                          // complements of the lane's 16 channels of a block
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                uint32_t wd = 0;
+#pragma unroll
+                for (int r = 15; r >= 0; --r) wd = __builtin_amdgcn_alignbit(wd, __float_as_uint(acc[cb][pb][r]), 31);
+                half_word[cb][pb] = wd;
+            }
+        // lanes of the lower half end up with pixel block 0 (PB = 1: channel block 0), those of the upper half with 1
+        auto put_word = [&](uint32_t lo, uint32_t hi, int px, int cb, bool mine) {
+            const auto both = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+            const int left = s.c_out - (o0 + 32 * cb);       // channels of the word
+            const uint32_t valid = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
+            const uint32_t wd = ~(both[0] | (both[1] << 16)) & valid;
+            const uint32_t at = (uint32_t)(px * s.cwo + (o0 >> 5) + cb) * 4u;
+            __builtin_amdgcn_raw_buffer_store_b32((int)wd, bits_res, (int)(mine && left > 0 ? at : NOWHERE), 0, 0);
+        };
+        if constexpr (PB % 2 == 0) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int pb = 0; pb < PB; pb += 2) put_word(half_word[cb][pb], half_word[cb][pb + 1], 32 * (pb + hsel) + j, cb, true);
+        } else {
+            static_assert(PB == 1, "pixel blocks in pairs, or one");
+#pragma unroll
+            for (int cb = 0; cb + 1 < CB; cb += 2) put_word(half_word[cb][0], half_word[cb + 1][0], j, cb + hsel, true);
+            if constexpr (CB % 2) put_word(half_word[CB - 1][0], half_word[CB - 1][0], j, CB - 1, hsel == 0);
+        }
+        return;
+    }
     const float zf = (float)a.z;
     // per-channel parameters of the lane's four channels, through buffers: a channel past the end and a missing array
     // (no bytes) read as zero, without branches

@@ -59,14 +59,16 @@ inline double staged_cost(int m, int c_out, int cw, int ks, int kind)
 // direct kernel wherever measured.
 static const double STAGED_BIAS[] = {0.85, 0.95, 0.71, 0.85};
 
-// The tile with the least estimated time; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the call) and that
-// kernel is the better choice.
-inline int direct_choose(int m, int c_out, int cw, int ks, int kind, bool staged)
+// The tile with the least estimated time, and that time; DIRECT_NONE if `staged` (the staged matrix-core kernel covers the
+// call) and that kernel is the better choice.
+struct DirectChoice { int tile; double cost; };
+inline DirectChoice direct_estimate(int m, int c_out, int cw, int ks, int kind, bool staged)
 {
     const int chunks = (direct_units(cw, ks) + 1) / 2;
     int best = DIRECT_NONE;
     const bool weigh = staged && !(kind == KIND_MODULE_GENERAL && chunks < 9);
-    double least = weigh ? STAGED_BIAS[kind] * staged_cost(m, c_out, cw, ks, kind) : 1e30;
+    const double rival = weigh ? staged_cost(m, c_out, cw, ks, kind) : 1e30;
+    double least = weigh ? STAGED_BIAS[kind] * rival : 1e30;
     for (const DirectTile& t : DIRECT_TILES) {
         const double wgs = (double)(((int64_t)m + 32 * t.pb * t.wp - 1) / (32 * t.pb * t.wp)) *
                            (double)((c_out + 32 * t.cb * t.wc - 1) / (32 * t.cb * t.wc));
@@ -76,8 +78,9 @@ inline int direct_choose(int m, int c_out, int cw, int ks, int kind, bool staged
         const double cost = c.fixed + c.chunk * mine + (c.wave + c.wave_chunk * mine) * waves;
         if (cost < least) { least = cost; best = t.tile; }
     }
-    return best;
+    return DirectChoice{best, best == DIRECT_NONE ? rival : least};
 }
+inline int direct_choose(int m, int c_out, int cw, int ks, int kind, bool staged) { return direct_estimate(m, c_out, cw, ks, kind, staged).tile; }
 
 // Branch mode: estimated time of a tile as above, with a wave's chain of groups of four K-steps in place of chunks.
 // Fits over 74 calls; rms error 14 to 19 %, the choice 1 to 2 % over the best tile on average, 24 % at worst.

@@ -4,7 +4,7 @@
 #include <stdint.h>
 
 #if defined(__HIPCC__)
-#define BCNN_HOST_DEVICE __host__ __device__
+#define BCNN_HOST_DEVICE __host__ __device__ __forceinline__
 #else
 #define BCNN_HOST_DEVICE
 #endif

@@ -1,0 +1,75 @@
+// When a call takes the direct kernel's form with shared weights (conv_mfma_direct_kernel.h, WIDE > 0), with which tile, and how
+// that form walks K.  Plain C++ on purpose: the launchers use these functions, and a host-only test walks every word count
+// with them.
+#pragma once
+#include <initializer_list>
+#include <stdint.h>
+
+#include "direct_plan.h"
+
+namespace bcnn {
+
+// Tiles: 32-channel x 32-pixel blocks of a wave; four waves along the pixels.
+enum { SHARED_NONE = 0, SHARED_1x1, SHARED_2x1, SHARED_2x2 };
+
+// How a tap's cw words are walked: lane half 0 takes the first `half` of them, half 1 the rest, one K-step a word of each, in
+// groups of `wide` words a load.  Narrow taps (up to four words) go several to a group of four K-steps.  Words that do not
+// exist are zeros on the weights' side.
+struct SharedWalk {
+    int half, wide, per_tap, groups;
+    static SharedWalk make(int cw, int taps)
+    {
+        SharedWalk r;
+        r.half = (cw + 1) / 2;
+        r.wide = r.half < 3 ? r.half : 4;
+        if (r.half >= 3)                                     // fewest K-steps; whole 16-byte loads where level
+            for (int wide : {5, 3})
+                if ((r.half + wide - 1) / wide * wide < (r.half + r.wide - 1) / r.wide * r.wide) r.wide = wide;
+        r.per_tap = (r.half + r.wide - 1) / r.wide;
+        r.groups = r.wide < 3 ? (taps * r.wide + 3) / 4 : taps * r.per_tap;
+        return r;
+    }
+    int steps(int taps) const { return wide < 3 ? taps * wide : groups * wide; }       // K-steps that are multiplied
+};
+
+// Estimated times in microseconds, as for the tiles of direct_plan.h: a launch, its K-steps, and per workgroup and compute unit
+// (256) its set-up with the epilogue and its K-steps.  Fits over 860 calls (500 to 440 000 pixels, 32 to 1024 channels on both
+// sides, 1x1 and 3x3, strides 1 and 2; graph replays), rms 8 to 11 % for bits and sums, 11 to 14 % for modules.
+enum { SHARED_BITS = 0, SHARED_SUMS = 1, SHARED_HALF = 2, SHARED_FLOAT = 3 };
+struct SharedCost { double fixed, step, wg, wg_step; };
+struct SharedTile { int tile, cb, pb; SharedCost kind[4]; };
+static const SharedTile SHARED_TILES[] = {
+    {SHARED_1x1, 1, 1, {{3.04, 0.0411, 0.341, 0.0302}, {3.55, 0.0424, 0.603, 0.0285}, {4.24, 0.0442, 1.27, 0.0236}, {4.50, 0.0420, 1.47, 0.0249}}},
+    {SHARED_2x1, 2, 1, {{3.14, 0.0738, 0.349, 0.0421}, {3.79, 0.0785, 1.10, 0.0327}, {5.27, 0.0859, 2.30, 0.0189}, {6.11, 0.0748, 2.61, 0.0310}}},
+    {SHARED_2x2, 2, 2, {{3.49, 0.1099, 0.498, 0.0618}, {4.53, 0.1208, 2.28, 0.0325}, {0, 0, 0, 0}, {0, 0, 0, 0}}},
+};
+inline double shared_cost(const SharedCost& c, int cb, int pb, int m, int c_out, int steps)
+{
+    const double wgs = (double)(((int64_t)m + 128 * pb - 1) / (128 * pb)) * (double)((c_out + 32 * cb - 1) / (32 * cb)) / 256.0;
+    return c.fixed + c.step * steps + (c.wg + c.wg_step * steps) * wgs;
+}
+
+// The tile, or SHARED_NONE where `other` is estimated to be as good.  Against the tiles that do not split K this form may be
+// estimated a tenth behind (but for sums, which their stores bind): their estimates are that much too low on the calls that
+// this one is ahead on.  Over the 860 calls: bits 1.14 times the other choice on average, sums 1.05, half modules 1.03, float
+// ones 1.01; 7 calls more than 4 % behind it, 14 % at worst.  (us, other and this: bits, 3x3, 320 -> 192, 39 maps of 38 x 38
+// 27.9 and 16.3; 64 -> 64, 156 maps of 25 x 28 9.8 and 6.9; 1x1, 704 -> 704, 40 maps of 26 x 26 14.9 and 10.8; sums, 3x3, 468 -> 39,
+// 191 maps of 37 x 36 52 and 38.)
+inline int shared_choose(int m, int c_out, int cw, int ks, int kind, const DirectChoice& other)
+{
+    // sums of a 1x1 filter are bound by their store, which the other tiles keep busier (64 -> 672, 46 maps of 51 x 29 30.7 and 33.9)
+    if (kind == SHARED_SUMS && ks == 1) return SHARED_NONE;
+    const int taps = ks * ks, steps = SharedWalk::make(cw, taps).steps(taps);
+    const bool whole_k = other.tile == DIRECT_2x1 || other.tile == DIRECT_1x1;
+    double least = other.cost * (whole_k && kind != SHARED_SUMS ? 1.1 : 1.0);
+    int best = SHARED_NONE;
+    for (const SharedTile& t : SHARED_TILES) {
+        const SharedCost& c = t.kind[kind];
+        if (c.fixed == 0) continue;                          // (a 2 x 2 tile leaves a module no registers for its identity)
+        const double cost = shared_cost(c, t.cb, t.pb, m, c_out, steps);
+        if (cost < least) { least = cost; best = t.tile; }
+    }
+    return best;
+}
+
+}  // namespace bcnn
