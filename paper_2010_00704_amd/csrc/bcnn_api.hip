@@ -230,12 +230,15 @@ static int branches_entry(const bcnn_conv_desc* desc, int32_t branches, const ui
     hipError_t e;
     switch (variant) {
         case BCNN_VARIANT_AUTO:
-            // measured over 74 calls (32 to 1024 channels, 49 to 50 000 pixels, both filters, every pad mode and
-            // output): the direct kernel is ahead of the vector ALUs everywhere (1.0 to 6 times) and of the
-            // staged kernel everywhere but one call in 74 (5 % there); the vector ALUs take large tails of few words
-            // (auto_plan.h) and what has too many branches or bytes
+            // the forms of the direct kernel (shared_plan.h) are ahead of the vector ALUs everywhere and of the staged
+            // kernel everywhere but one call in 74 (5 % there, before two of the three forms); the vector ALUs take large
+            // tails of few words (auto_plan.h) and what has too many branches or bytes
             if (bcnn::conv_branches_direct_supported(s, a) &&
-                !(tail && bcnn::direct_behind_on_branch_tail(s.cw, s.cw * branches, s.c_out, tail->half, (int64_t)s.m * s.c_out))) e = bcnn::launch_conv_branches_direct(s, a, bcnn::conv_branches_direct_choose(s, a), st);
+                !(tail && bcnn::direct_behind_on_branch_tail(s.cw, s.cw * branches, s.c_out, tail->half, (int64_t)s.m * s.c_out))) {
+                const bcnn::BranchChoice choice = bcnn::branches_choose(s.m, s.c_out, s.cw, branches, tail != nullptr, tail && tail->half);
+                e = choice.form == bcnn::BRANCH_SHARED ? bcnn::launch_conv_branches_shared(s, a, choice.tile, st)
+                                                       : bcnn::launch_conv_branches_direct(s, a, choice.tile, st);
+            }
             else e = bcnn::launch_conv_branches(s, a, st);
             break;
         case BCNN_VARIANT_VALU:

@@ -5,34 +5,34 @@
 namespace bcnn {
 namespace {
 
-template <int CB, int PB, int WC, int WP, int OUT>
+template <int CB, int PB, int WC, int WP, int WK, int OUT>
 hipError_t launch_pad(DirectArgs a, const BranchArgs& b, const DirectBranch& br, hipStream_t stream)
 {
     a.n_ctiles = (a.s.c_out + 32 * CB * WC - 1) / (32 * CB * WC);
     a.n_ptiles = (a.s.m + 32 * PB * WP - 1) / (32 * PB * WP);
     a.div_ct = DivBy::make(a.n_ctiles);
-    const dim3 blocks((unsigned)(a.n_ptiles * a.n_ctiles)), threads(64 * WC * WP);
+    const dim3 blocks((unsigned)(a.n_ptiles * a.n_ctiles)), threads(64 * WC * WP * WK);
     const ModuleEp ep = b.tail ? *b.tail : ModuleEp{};
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a, b.x, b.w, (const int32_t*)nullptr, b.out, ep, br);
     };
-    if (b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, WC, WP, 1, OUT, BRANCH + PAD_NOTHING>);
-    else if (b.pad_words) go(conv_mfma_direct_kernel<CB, PB, WC, WP, 1, OUT, BRANCH + PAD_OPERAND>);
-    else go(conv_mfma_direct_kernel<CB, PB, WC, WP, 1, OUT, BRANCH + PAD_NONE>);
+    if (b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NOTHING>);
+    else if (b.pad_words) go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_OPERAND>);
+    else go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NONE>);
     return hipGetLastError();
 }
 
-template <int CB, int PB, int WC, int WP>
+template <int CB, int PB, int WC, int WP, int WK>
 hipError_t launch_out(const DirectArgs& a, const BranchArgs& b, const DirectBranch& br, hipStream_t stream)
 {
-    if (b.tail && b.tail->half) return launch_pad<CB, PB, WC, WP, OUT_MODULE + REAL_F16>(a, b, br, stream);
+    if (b.tail && b.tail->half) return launch_pad<CB, PB, WC, WP, WK, OUT_MODULE + REAL_F16>(a, b, br, stream);
     if (b.tail) {
         // (the 2 x 2 tile has no registers for the float stream's identity vectors: never chosen for it)
-        if constexpr (CB * PB < 4) return launch_pad<CB, PB, WC, WP, OUT_MODULE + REAL_F32>(a, b, br, stream);
+        if constexpr (CB * PB < 4) return launch_pad<CB, PB, WC, WP, WK, OUT_MODULE + REAL_F32>(a, b, br, stream);
         else return hipErrorInvalidValue;
     }
-    if (b.fused) return launch_pad<CB, PB, WC, WP, OUT_BITS>(a, b, br, stream);
-    return launch_pad<CB, PB, WC, WP, OUT_I32>(a, b, br, stream);
+    if (b.fused) return launch_pad<CB, PB, WC, WP, WK, OUT_BITS>(a, b, br, stream);
+    return launch_pad<CB, PB, WC, WP, WK, OUT_I32>(a, b, br, stream);
 }
 
 int64_t branch_x_bytes(const ConvShape& s, const BranchArgs& b)
@@ -50,11 +50,6 @@ bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b)
     return b.branches <= MAX_BRANCHES && s.c_out <= (1 << 20) && ((int64_t)s.cw + 1) * 32 < (1 << 22) && branch_x_bytes(s, b) < (1ll << 31) && w_bytes < (1ll << 31);
 }
 
-int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b)
-{
-    return branches_direct_choose(s.m, s.c_out, s.cw, b.branches, b.tail != nullptr, b.tail && b.tail->half);
-}
-
 hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream)
 {
     DirectArgs a{};
@@ -69,11 +64,12 @@ hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, 
     a.tap_step = (int32_t)b.x_branch_stride;
     a.div_hw = DivBy::make(s.ho * s.wo);
     a.div_wo = DivBy::make(s.wo);
-    const DirectBranch br{b.scale, b.bias, b.pad_words};
+    const DirectBranch br{b.scale, b.bias, b.pad_words, 0, 0u};
     switch (tile) {
-        case DIRECT_1x1: return launch_out<1, 1, 1, 4>(a, b, br, stream);
-        case DIRECT_2x1: return launch_out<2, 1, 1, 4>(a, b, br, stream);
-        case DIRECT_2x2: return launch_out<2, 2, 1, 4>(a, b, br, stream);
+        case DIRECT_1x1_K4: return b.branches <= APART_TAPS ? launch_out<1, 1, 1, 1, 4>(a, b, br, stream) : hipErrorInvalidValue;
+        case DIRECT_1x1: return launch_out<1, 1, 1, 4, 1>(a, b, br, stream);
+        case DIRECT_2x1: return launch_out<2, 1, 1, 4, 1>(a, b, br, stream);
+        case DIRECT_2x2: return launch_out<2, 2, 1, 4, 1>(a, b, br, stream);
         default: return hipErrorInvalidValue;
     }
 }

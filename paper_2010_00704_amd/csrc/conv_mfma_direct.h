@@ -13,9 +13,9 @@ DirectChoice conv_mfma_direct_choose(const ConvShape& s, int kind, bool staged);
 hipError_t launch_conv_mfma_direct(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream);
 
-// the same in branch mode (tiles DIRECT_1x1, DIRECT_2x1, DIRECT_2x2: four waves along the pixels)
+// the same in branch mode (tiles DIRECT_1x1, DIRECT_2x1, DIRECT_2x2: four waves along the pixels; DIRECT_1x1_K4: four waves
+// that take whole taps of up to APART_TAPS branches)
 bool conv_branches_direct_supported(const ConvShape& s, const BranchArgs& b);
-int conv_branches_direct_choose(const ConvShape& s, const BranchArgs& b);
 hipError_t launch_conv_branches_direct(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream);
 
 // 1x1 modules of at most eight words per pixel, plain case (conv_mfma_stream.hip)

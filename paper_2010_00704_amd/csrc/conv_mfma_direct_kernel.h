@@ -39,16 +39,20 @@
 // 704 -> 704, 40 maps of 26 x 26 14.9 -> 10.8; sums, 3x3, 468 -> 39, 191 maps of 37 x 36 52 -> 38; half module, 3x3, 131 -> 256,
 // 97 500 pixels 49 -> 41.  Tried: 4 x 2 and 2 x 4 blocks a wave (one wave per SIMD takes 67 cycles per MFMA, waiting for LDS
 // and barriers; nowhere ahead), halves of a tap side by side in 32-byte pieces (wide rows no faster, all rows 3 % slower).
-// Branch mode, 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 us in the staged kernel, 33 here (a tap's fold
-// there exchanges its corrections through LDS and costs more than the tap's matrix work); 512 channels, 64 maps of
-// 28 x 28 149 -> 90; 627 channels, 21 maps of 7 x 7, half tail (vector ALUs before) 118 -> 20.  The check of a tap's last words
-// (branch_walk.h) is 1 % of the first of these (33.2 -> 33.7); 224 channels, whose taps are single words only, -> 128, 16
-// maps of 14 x 14, 12.5 against 66.5 on the vector ALUs.
+// Branch mode has three forms (shared_plan.h): every wave its own operands, shared weights, and for small launches waves that
+// take whole taps of a block and scale and add their sums in order at the end (a wave's chain is a quarter as long).  With
+// shared weights the pixels are the instruction's rows, so that a tap's scale is one register a block: 16-byte scale reads
+// took as much LDS time as the weights (24.7 us against 26.7 on the first call below), and zeros as an inline start
+// operand replace a move per element and tap.  Measured, us: 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 in the
+// staged kernel, 33.7 every wave for itself, 22.9 shared (pad words 3 of that: a second load and an OR); 160 -> 160, 49 maps of
+// 41 x 41, float 44.6 and 24.8; 64 -> 64, 213 maps of 39 x 42, half tail 57 and 39; 384 -> 384, 2 maps of 13 x 13, bits 12.9 and, taps
+// apart, 6.6.  2 x 2 blocks a wave (two waves per SIMD) 28.8 on the first of these, 1 x 2 36.8.
 #pragma once
 #include "bcnn_common.h"
 #include "branch_walk.h"
 #include "direct_plan.h"
 #include "div_by.h"
+#include "shared_plan.h"
 
 #include <type_traits>
 
@@ -110,7 +114,8 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
 {
     constexpr bool BR = MODE >= BRANCH;
     constexpr int PAD = BR ? MODE - BRANCH : PAD_NONE;
-    static_assert(!BR || WK == 1, "a branch's sum is scaled as a whole");
+    constexpr bool TAPS_APART = BR && WK > 1;                // the waves of a tile take whole taps
+    static_assert(!TAPS_APART || (CB == 1 && PB == 1), "one block of 32 x 32 shared by the waves");
     constexpr bool MODULE = OUT >= OUT_MODULE;
     constexpr int REAL = MODULE ? OUT - OUT_MODULE : REAL_F32;
     constexpr bool HALF = REAL != REAL_F32;
@@ -122,12 +127,15 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
     constexpr int ROW = TCH + 4;                             // floats; rows stay 16-byte aligned, banks skewed by 4
     constexpr int REGION = (WK > 1 ? TPX : 32) * ROW;
     constexpr bool SHARED = WIDE > 0;
+    // Branch mode with shared weights has the pixels as the instruction's rows: a lane holds 16 pixels of one channel, and a
+    // tap's scale is one register a block.  Everywhere else a lane holds 16 channels of one pixel.
+    constexpr bool LANE_CHANNEL = SHARED && BR;
     static_assert(!SHARED || (WC == 1 && WK == 1), "shared weights: the workgroup's waves lie along the pixels");
     constexpr int SG = SHARED ? WP / CB : 1;                 // groups of a stage: every thread expands one unit of it
     constexpr int STEPS = WIDE < 3 ? 4 : WIDE;               // K-steps of a group
     constexpr int STAGE = SG * STEPS * CB * 1024;            // bytes
     constexpr bool SIGN_OUT = SHARED && OUT == OUT_BITS && !BR;
-    constexpr int EP_FLOATS = SIGN_OUT ? 0 : WC * WP * WK * REGION;
+    constexpr int EP_FLOATS = SIGN_OUT ? 0 : TAPS_APART ? APART_TAPS * REGION : WC * WP * WK * REGION;
     __shared__ __align__(16) float lds[EP_FLOATS > 2 * STAGE / 4 || !SHARED ? EP_FLOATS : 2 * STAGE / 4];
 
     const ConvShape& s = a.s;
@@ -166,7 +174,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
     uint32_t vmask[PB];                                      // one validity bit per tap
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) {
-        int m = m0 + 32 * pb + j;
+        int m = m0 + 32 * pb + (LANE_CHANNEL ? row_to_channel(j) : j);
         m = m < s.m ? m : s.m - 1;
         if (s.ks == 1 && s.stride == 1) {
             rbase[pb] = m * s.cw;
@@ -315,7 +323,9 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
         for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[cb][pb][r] = 0.0f;
-    v16f tot[BR ? CB : 1][BR ? PB : 1];                      // branch mode: the scaled sum so far
+    v16f tot[BR && !TAPS_APART ? CB : 1][BR && !TAPS_APART ? PB : 1];   // branch mode: the scaled sum so far
+    __shared__ __align__(16) float apart_scale[TAPS_APART ? APART_TAPS : 1][TCH];
+    __shared__ uint32_t apart_mask[32];                      // validity bits of the tile's pixels
 
     auto multiply = [&](const Chunk& c, int steps) {
 #pragma unroll
@@ -345,7 +355,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
         const int ugroup = unit >> 1, uhalf = unit & 1;
         int urow_words;
         {
-            const int ch = o0 + (urow & ~31) + row_to_channel(urow & 31);
+            const int ch = o0 + (LANE_CHANNEL ? urow : (urow & ~31) + row_to_channel(urow & 31));
             urow_words = (ch < s.c_out ? ch : s.c_out - 1) * a.n_words;
         }
         const int n_groups = a.n_units;
@@ -450,28 +460,30 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                 for (int cb = 0; cb < CB; ++cb) {
                     const v8i w8 = {fw.f[cb][0], fw.f[cb][1], fw.f[cb][2], fw.f[cb][3], 0, 0, 0, 0};
                     const v16f from_zero = {};
-                    acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w8, fx, first ? from_zero : acc[cb][pb], 4, 4, 0, 0, 0, 0);
+                    acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(LANE_CHANNEL ? fx : w8, LANE_CHANNEL ? w8 : fx, first ? from_zero : acc[cb][pb], 4, 4, 0, 0, 0, 0);
                 }
             }
         };
         // branch mode: a completed tap's sums join the total, tot = fma(scale, y_t, tot) in the order t = 0, 1, ...
         __shared__ __align__(16) float scale_lds[BR ? MAX_BRANCHES : 1][TCH];
         auto fold = [&](int tap) __attribute__((always_inline)) {
+            float sc[CB];
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int cb = 0; cb < CB; ++cb) sc[cb] = scale_lds[tap][32 * cb + j];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4f sc = *reinterpret_cast<const v4f*>(&scale_lds[tap][32 * cb + 16 * hsel + 4 * q]);
+            for (int pb = 0; pb < PB; ++pb) {
+                // lane i of a half holds the validity of pixel row_to_channel(i): of the lane's r-th one in bit 8 (r / 4) + r % 4
+                const uint32_t inside = PAD == PAD_NOTHING ? (uint32_t)__ballot((vmask[pb] >> tap) & 1u) : ~0u;
+                const uint32_t mine = inside >> (4 * hsel);
 #pragma unroll
-                    for (int pb = 0; pb < PB; ++pb) {
-                        const bool in = PAD != PAD_NOTHING || ((vmask[pb] >> tap) & 1u);
+                for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const float zn = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
-                            tot[cb][pb][4 * q + k] = in ? zn : tot[cb][pb][4 * q + k];
-                        }
+                    for (int r = 0; r < 16; ++r) {
+                        const float zn = __builtin_fmaf(sc[cb], acc[cb][pb][r], tot[cb][pb][r]);
+                        const bool in = PAD != PAD_NOTHING || ((mine >> (8 * (r >> 2) + (r & 3))) & 1u);
+                        tot[cb][pb][r] = in ? zn : tot[cb][pb][r];
                     }
-                }
+            }
         };
         auto group = [&](int gi, const char* from, const Inputs& c) __attribute__((always_inline)) {
             Fragments fw[2];
@@ -513,21 +525,23 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
         fetch_w(1, uw);
         fetch_x(1, ring[1]);
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if constexpr (BR || SIGN_OUT) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
+            for (int pb = 0; pb < PB; ++pb) {
+                if constexpr (BR) {
+                    const float bias = start_lds[32 * cb + j];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) tot[cb][pb][r] = bias;
+                } else if constexpr (SIGN_OUT) {
 #pragma unroll
                     for (int q = 0; q < 16; q += 4) {
                         const v4f v = *reinterpret_cast<const v4f*>(&start_lds[32 * cb + 16 * hsel + q]);
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if constexpr (BR) tot[cb][pb][q + k] = v[k];
-                            else acc[cb][pb][q + k] = v[k];
-                        }
+                        for (int k = 0; k < 4; ++k) acc[cb][pb][q + k] = v[k];
                     }
-        }
+                }
+            }
         // `part` groups of a stage; the first one's inputs lie in ring[at]
         auto walk = [&](int st, auto part, auto at) __attribute__((always_inline)) {
             const char* from = stage + (st & 1) * STAGE;
@@ -594,6 +608,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
             }
         }
     } else {
+        // (a wave of TAPS_APART takes the taps wk, wk + WK, ... and leaves their sums in LDS)
         // A tap's words are split between the lane halves and walked in groups of four words = four K-steps with one
         // 16-byte load per row; the last group is single words (branch_walk.h).  Every load is wave-uniform but for the
         // rows' offsets and their validity.
@@ -641,61 +656,108 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                 }
             }
         };
-        __shared__ __align__(16) float scale_lds[MAX_BRANCHES][TCH * WC];
-        for (int i = t; i < a.taps * (TCH * WC); i += 64 * WC * WP) {
-            const int tp = i / (TCH * WC), cl = i - tp * (TCH * WC);
-            const int ch = o0 - TCH * wc + cl;
-            scale_lds[tp][cl] = br.scale[(size_t)tp * s.c_out + (ch < s.c_out ? ch : s.c_out - 1)];
-        }
-        Chunk cur, nxt;
-        fetch_group(0, 0, cur);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            float b[16];
-            const int ch = o0 + 32 * cb + 16 * hsel;         // the lane's 16 channels of the block
-#pragma unroll
-            for (int r = 0; r < 16; ++r) b[r] = br.bias ? br.bias[ch + r < s.c_out ? ch + r : s.c_out - 1] : 0.0f;
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) { tot[cb][pb][r] = b[r]; acc[cb][pb][r] = start; }
-        }
-        __syncthreads();
-        for (int tap = 0; tap < a.taps; ++tap) {
-            for (int g = 0; g < per_tap; ++g) {
-                const bool more = g + 1 < per_tap;
-                if (more || tap + 1 < a.taps) fetch_group(more ? tap : tap + 1, more ? g + 1 : 0, nxt);
-                multiply(cur, walk.steps(g));
-                cur = nxt;
+        if constexpr (TAPS_APART) {
+            for (int i = t; i < a.taps * TCH; i += 64 * WK) {
+                const int tp = i / TCH, cl = i - tp * TCH;
+                apart_scale[tp][cl] = br.scale[(size_t)tp * s.c_out + (o0 + cl < s.c_out ? o0 + cl : s.c_out - 1)];
             }
+            if (t < 32) apart_mask[t] = vmask[0];
+            constexpr int AHEAD = 4;
+            Chunk ring[AHEAD];
+            const int mine = (a.taps - wk + WK - 1) / WK * per_tap;     // groups of the wave's taps
+            int f_tap = wk, f_g = 0, tap = wk, g = 0;                   // next to fetch, next to multiply
+            auto fetch_next = [&](Chunk& c) {
+                fetch_group(f_tap, f_g, c);
+                const bool done = ++f_g == per_tap;
+                f_g = done ? 0 : f_g;
+                f_tap += done ? WK : 0;
+            };
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int i = 0; i < AHEAD; ++i)
+                if (i < mine) fetch_next(ring[i]);
+            for (int i = 0; i < mine; i += AHEAD) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4f sc = *reinterpret_cast<const v4f*>(&scale_lds[tap][TCH * wc + 32 * cb + 16 * hsel + 4 * q]);
+                for (int b = 0; b < AHEAD; ++b) {
+                    if (i + b < mine) {
+                        multiply(ring[b], walk.steps(g));
+                        if (i + b + AHEAD < mine) fetch_next(ring[b]);
+                        if (++g == per_tap) {
 #pragma unroll
-                    for (int pb = 0; pb < PB; ++pb) {
-                        const bool in = PAD != PAD_NOTHING || s.ks == 1 || ((vmask[pb] >> tap) & 1u);
+                            for (int r = 0; r < 16; r += 4)
+                                *reinterpret_cast<v4f*>(lds + tap * REGION + j * ROW + 16 * hsel + r) =
+                                    v4f{acc[0][0][r] + start, acc[0][0][r + 1] + start, acc[0][0][r + 2] + start, acc[0][0][r + 3] + start};
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const float zn = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
-                            tot[cb][pb][4 * q + k] = in ? zn : tot[cb][pb][4 * q + k];
-                            acc[cb][pb][4 * q + k] = start;
+                            for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
+                            g = 0;
+                            tap += WK;
                         }
                     }
                 }
+            }
+        } else {
+            __shared__ __align__(16) float scale_lds[MAX_BRANCHES][TCH * WC];
+            for (int i = t; i < a.taps * (TCH * WC); i += 64 * WC * WP) {
+                const int tp = i / (TCH * WC), cl = i - tp * (TCH * WC);
+                const int ch = o0 - TCH * wc + cl;
+                scale_lds[tp][cl] = br.scale[(size_t)tp * s.c_out + (ch < s.c_out ? ch : s.c_out - 1)];
+            }
+            Chunk cur, nxt;
+            fetch_group(0, 0, cur);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                float b[16];
+                const int ch = o0 + 32 * cb + 16 * hsel;         // the lane's 16 channels of the block
+#pragma unroll
+                for (int r = 0; r < 16; ++r) b[r] = br.bias ? br.bias[ch + r < s.c_out ? ch + r : s.c_out - 1] : 0.0f;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { tot[cb][pb][r] = b[r]; acc[cb][pb][r] = start; }
+            }
+            __syncthreads();
+            for (int tap = 0; tap < a.taps; ++tap) {
+                for (int g = 0; g < per_tap; ++g) {
+                    const bool more = g + 1 < per_tap;
+                    if (more || tap + 1 < a.taps) fetch_group(more ? tap : tap + 1, more ? g + 1 : 0, nxt);
+                    multiply(cur, walk.steps(g));
+                    cur = nxt;
+                }
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const v4f sc = *reinterpret_cast<const v4f*>(&scale_lds[tap][TCH * wc + 32 * cb + 16 * hsel + 4 * q]);
+#pragma unroll
+                        for (int pb = 0; pb < PB; ++pb) {
+                            const bool in = PAD != PAD_NOTHING || s.ks == 1 || ((vmask[pb] >> tap) & 1u);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const float zn = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
+                                tot[cb][pb][4 * q + k] = in ? zn : tot[cb][pb][4 * q + k];
+                                acc[cb][pb][4 * q + k] = start;
+                            }
+                        }
+                    }
+            }
         }
     }
 
     // ---- epilogue.  A pixel's channels through LDS: lane (pixel j, half h) holds channels 16h .. 16h+15 of a block.
     float* region = lds + (wp * WC + wc) * WK * REGION;
     auto park = [&](float* dst, int pb, int row0) {
+        if constexpr (LANE_CHANNEL) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) dst[(row0 + 16 * hsel + r) * ROW + 32 * cb + j] = tot[cb][pb][r];
+            return;
+        }
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int r = 0; r < 16; r += 4)
             {
-                const v16f& v = [&]() -> const v16f& { if constexpr (BR) return tot[cb][pb]; else return acc[cb][pb]; }();
+                const v16f& v = [&]() -> const v16f& { if constexpr (BR && !TAPS_APART) return tot[cb][pb]; else return acc[cb][pb]; }();
                 *reinterpret_cast<v4f*>(dst + (row0 + j) * ROW + 32 * cb + 16 * hsel + r) = v4f{v[r], v[r + 1], v[r + 2], v[r + 3]};
             }
     };
@@ -827,7 +889,26 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
         wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0x141, 0xF, 0xF, true);  // row_half_mirror
         __builtin_amdgcn_raw_buffer_store_b32((int)wd, MODULE ? xn_res : out_res, (int)(word_off + (uint32_t)(px * xn_row)), 0, 0);
     };
-    if constexpr (WK > 1) {
+    if constexpr (TAPS_APART) {
+        // tot = fma(scale, y_t, tot) in the order t = 0, 1, ..., every thread for its four outputs
+        float first[4];
+        load_params(br.bias, first);
+        __syncthreads();
+        static_assert(GROUPS == 1, "four outputs a thread");
+        v4f sum = {first[0], first[1], first[2], first[3]};
+        const uint32_t valid = PAD == PAD_NOTHING ? apart_mask[px0] : ~0u;
+        for (int tap = 0; tap < a.taps; ++tap) {
+            const v4f y = *reinterpret_cast<const v4f*>(lds + tap * REGION + px0 * ROW + 4 * (lt % CG));
+            const v4f sc = *reinterpret_cast<const v4f*>(&apart_scale[tap][4 * (lt % CG)]);
+            const bool in = (valid >> tap) & 1u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float zn = __builtin_fmaf(sc[k], y[k], sum[k]);
+                sum[k] = in ? zn : sum[k];
+            }
+        }
+        emit(sum, px0, 0);
+    } else if constexpr (WK > 1) {
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) park(region + wk * REGION, pb, 32 * pb);
         __syncthreads();

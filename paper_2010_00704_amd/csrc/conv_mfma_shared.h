@@ -13,4 +13,8 @@ int conv_mfma_shared_choose(const ConvShape& s, int kind, const DirectChoice& ot
 hipError_t launch_conv_mfma_shared(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream);
 
+
+// the same in branch mode (tiles SHARED_1x1, SHARED_2x1)
+hipError_t launch_conv_branches_shared(const ConvShape& s, const BranchArgs& b, int tile, hipStream_t stream);
+
 }  // namespace bcnn

@@ -1,16 +1,26 @@
 // Host-only check of the plan of the direct kernel's form with shared weights (csrc/shared_plan.h).  Without arguments: walks
 // the words of a tap for every word count and prints "mismatches: N", exit status 0 = none.  With an argument: reads calls
 // from standard input, one a line (m c_out cw ks kind staged, kind as in direct_plan.h and, for this form, as in
-// shared_plan.h), prints the tile and the words per load of each.
+// shared_plan.h), prints the tile and the words per load of each; with "branches": m c_out cw branches tail half, prints form,
+// tile and words per load.
 #include "shared_plan.h"
 
 #include <cstdio>
+#include <cstring>
 #include <vector>
 
 using namespace bcnn;
 
-int main(int argc, char**)
+int main(int argc, char** argv)
 {
+    if (argc > 1 && !strcmp(argv[1], "branches")) {
+        int m, c_out, cw, branches, tail, half;
+        while (scanf("%d %d %d %d %d %d", &m, &c_out, &cw, &branches, &tail, &half) == 6) {
+            const BranchChoice c = branches_choose(m, c_out, cw, branches, tail != 0, half != 0);
+            printf("%d %d %d\n", c.form, c.tile, SharedWalk::make(cw, branches).wide);
+        }
+        return 0;
+    }
     if (argc > 1) {
         int m, c_out, cw, ks, kind, mine, staged;
         while (scanf("%d %d %d %d %d %d %d", &m, &c_out, &cw, &ks, &kind, &mine, &staged) == 7)

@@ -1,5 +1,5 @@
 """The direct kernel's form whose workgroups share expanded weights: every tile and width of its loads, for each kind of
-output, against the vector-ALU kernels (which the other tests hold against the oracle).  Pixels, channels and words are
+output, and in branch mode also the form whose waves take whole taps, against the vector-ALU kernels (which the other tests hold against the oracle).  Pixels, channels and words are
 ragged; operands lie a word past an allocation's start, so that the staged kernel covers none of these calls.  Which tile and
 width a call takes is checked on the host, from the same list, by test_host_shared_plan.py."""
 import pytest
@@ -61,9 +61,36 @@ CONVS = [
     (FLOAT, S_2X1, 5, (101, 260, 27, 27, 300, 3, 2)),
 ]
 
-
-def module_parts(form):
-    return "id" in form, "r" in form, "x" in form
+OWN, APART, SHARED = 0, 1, 2                           # branch forms; tile 1 of APART: four waves a block
+BRANCHES = [
+    # form, tile, words per load, output, (n, c_in, h, w, c_out, branches): nine taps of a 3x3 filter, or parallel ones
+    (APART, 1, 1, "bits", (1, 20, 9, 7, 33, 9)),
+    (APART, 1, 2, "f32", (1, 75, 9, 7, 33, 9)),
+    (APART, 1, 3, "module_f16", (2, 140, 13, 11, 70, 9)),
+    (APART, 1, 4, "module_f32", (1, 200, 9, 7, 33, 9)),
+    (APART, 1, 4, "bits", (1, 420, 9, 7, 33, 9)),
+    (APART, 1, 5, "f32", (1, 260, 9, 7, 33, 3)),
+    (APART, 1, 1, "module_f16", (1, 50, 9, 7, 36, 3)),
+    (SHARED, S_1X1, 1, "bits", (1, 20, 9, 7, 33, 16)),
+    (SHARED, S_1X1, 1, "f32", (13, 20, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 1, "module_f16", (61, 20, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 1, "bits", (61, 20, 27, 26, 70, 9)),
+    (SHARED, S_1X1, 2, "f32", (1, 75, 9, 7, 33, 16)),
+    (SHARED, S_1X1, 2, "module_f16", (13, 75, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 2, "f32", (61, 75, 27, 26, 70, 3)),
+    (SHARED, S_1X1, 3, "module_f16", (1, 140, 9, 7, 33, 16)),
+    (SHARED, S_1X1, 3, "module_f32", (13, 140, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 70, 3)),
+    (SHARED, S_1X1, 4, "module_f32", (1, 200, 9, 7, 33, 16)),
+    (SHARED, S_1X1, 4, "bits", (13, 200, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 70, 3)),
+    (SHARED, S_1X1, 5, "bits", (1, 260, 9, 7, 33, 16)),
+    (SHARED, S_1X1, 5, "f32", (13, 260, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 5, "module_f16", (61, 260, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 5, "bits", (61, 260, 27, 26, 70, 3)),
+]
 
 
 @pytest.mark.parametrize("kind,tile,wide,shape", CONVS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
@@ -92,3 +119,32 @@ def test_tile(kind, tile, wide, shape):
                                                                 out[0] if has_r else None, out[1] if has_x else None, v),
                      [((m, o), dtype), ((m, words), torch.int32)])
     del keep_x, keep_w
+
+
+@pytest.mark.parametrize("pad_mode", ["minus", "words", "zero"])
+@pytest.mark.parametrize("form,tile,wide,out,shape", BRANCHES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_branch_form(form, tile, wide, out, shape, pad_mode):
+    gpu_device()
+    n, c, h, w, o, taps = shape
+    k = 3 if taps == 9 else 1
+    d = Draw(84000 + 17 * c + n)
+    own = taps == 3                                     # parallel branches of their own tensors, or of one
+    (x, _, keep_x), (wt, _, keep_w), (pad, _, keep_p) = d.packed(n * (taps if own else 1), c, h, w), d.packed(o, c, taps), d.packed(taps, c, 1)
+    desc = B.conv_desc(n, c, h, w, o, k, 1, k // 2)
+    m, words = n * h * w, (o + 31) // 32
+    scale, bias = d.real((taps, o), 4 / (taps * c) ** 0.5), d.real((o,), 3.0)
+    scale[:, 0], bias[1] = float("inf"), float("nan")   # sums of infinities and no numbers: their sign bits too
+    args = (desc, taps, x, m * ((c + 31) // 32) if own else 0, wt, pad if pad_mode == "words" else None,
+            B.BCNN_PAD_ZERO if pad_mode == "zero" else B.BCNN_PAD_WORDS, scale, bias if out != "f32" else None)
+    if out == "bits":
+        both(lambda z, v: B.bcnn_conv2d_binary_branches_sign_pack(*args, z[0], v), [((m, words), torch.int32)])
+    elif out == "f32":
+        scale[:, 0] = 0.25
+        both(lambda z, v: B.bcnn_conv2d_binary_branches(*args, z[0], v), [((m, o), torch.float32)])
+    else:
+        scale[:, 0], bias[1] = 0.25, 0.5
+        dtype, code = (torch.float16, B.BCNN_F16) if out == "module_f16" else (torch.float32, B.BCNN_F32)
+        ident, slope, nxt = d.real((m, o), 30.0).to(dtype), d.real((o,), 1.0), d.real((o,), 5.0)
+        both(lambda z, v: B.bcnn_conv2d_binary_branches_module(*args, ident, slope, nxt, code, z[0], z[1], v),
+             [((m, o), dtype), ((m, words), torch.int32)])
+    del keep_x, keep_w, keep_p

@@ -23,9 +23,9 @@ def test_every_word_is_walked_once(checker):
     assert out.returncode == 0, out.stdout
 
 
-def choices(checker, calls):
-    lines = "\n".join(" ".join(map(str, c)) for c in calls)
-    out = subprocess.run([checker, "calls"], input=lines, stdout=subprocess.PIPE, text=True, timeout=300, check=True)
+def choices(checker, calls, mode="calls"):
+    lines = "\n".join(" ".join(str(int(v)) for v in c) for c in calls)
+    out = subprocess.run([checker, mode], input=lines, stdout=subprocess.PIPE, text=True, timeout=300, check=True)
     return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
 
 
@@ -42,3 +42,15 @@ def test_every_tile_and_width_is_reached_on_the_gpu(checker):
     listed = {(kind, tile, wide) for kind, tile, wide, _ in G.CONVS}
     reached = {(c[5], tile, wide) for c, (tile, wide) in zip(grid, choices(checker, grid)) if tile}
     assert reached <= listed, sorted(reached - listed)
+
+
+def test_every_branch_form_is_reached_on_the_gpu(checker):
+    def tail(out):
+        return out.startswith("module"), out == "module_f16"
+
+    calls = [(n * h * w, o, (c + 31) // 32, taps, *tail(out)) for _, _, _, out, (n, c, h, w, o, taps) in G.BRANCHES]
+    assert choices(checker, calls, "branches") == [(form, tile, wide) for form, tile, wide, _, _ in G.BRANCHES]
+    grid = [(m, o, cw, p, *tail(out)) for m in (49, 784, 12544, 50176, 200704) for o in (32, 100, 256, 512) for cw in (1, 3, 5, 8, 9, 16, 32)
+            for p in (2, 3, 9, 16) for out in ("bits", "f32", "module_f32", "module_f16")]
+    listed = {(form, tile, wide) for form, tile, wide, _, _ in G.BRANCHES if form == G.SHARED}
+    assert {c for c in choices(checker, grid, "branches") if c[0] == G.SHARED} <= listed
