@@ -1,8 +1,9 @@
-"""ctypes binding of libbcnn.so: the C ABI of include/bcnn.h under the same names.
+"""Binding of libbcnn.so: the C ABI of include/bcnn.h under the same names.
 
-Argument marshalling only.  torch supplies device memory and the stream; every
-step of the computation runs in the library's HIP kernels.  There is no CPU or
-PyTorch fallback: if the library is missing, loading raises.
+Argument marshalling only, the hot calls' in C++ (csrc/marshal.cpp), the rest by
+ctypes.  torch supplies device memory and the stream; every step of the
+computation runs in the library's HIP kernels.  There is no CPU or PyTorch
+fallback: if the library is missing, loading raises.
 """
 import ctypes
 import os
@@ -53,16 +54,23 @@ class BcnnError(RuntimeError):
 
 
 _lib = None
+_marshal = None
 
 
 def lib():
-    """The loaded library.  Raises if libbcnn.so has not been built."""
-    global _lib
+    """The loaded library.  Raises if libbcnn.so or _marshal.so has not been built."""
+    global _lib, _marshal
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
                 "libbcnn.so is missing (%s): build it with `python -m paper_2010_00704_amd.build` "
                 "or __graft_entry__.build(); there is no fallback path" % LIB_PATH)
+        try:
+            from . import _marshal as marshal
+        except ImportError as e:
+            raise RuntimeError("_marshal.so is missing or does not load (%s): build it with `python -m "
+                               "paper_2010_00704_amd.build` or __graft_entry__.build(); there is no fallback path" % e) from e
+        _marshal = marshal
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         dp = ctypes.POINTER(bcnn_conv_desc)
@@ -92,8 +100,18 @@ def lib():
         for name in EXPORTS:
             if name != "bcnn_status_string":
                 getattr(L, name).restype = ctypes.c_int
+        _marshal.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS},
+                      _ptr, _desc, lambda stream: _stream(stream), torch.cuda.is_initialized, bcnn_conv_desc,
+                      ctypes.ArgumentError)
         _lib = L
     return _lib
+
+
+def _calls():
+    """The marshalled entry points, bound to the loaded library."""
+    if _lib is None:
+        lib()
+    return _marshal
 
 
 def _ptr(t):
@@ -138,80 +156,61 @@ def bcnn_out_dim(size, k, stride, pad):
 
 
 def bcnn_pack(src, dtype, outer, channels, inner, dst, stream=None):
-    return lib().bcnn_pack(_ptr(src), dtype, outer, channels, inner, _ptr(dst), _stream(stream))
+    return _calls().pack(src, dtype, outer, channels, inner, dst, stream)
 
 
 def bcnn_pack_bias(src, dtype, outer, channels, inner, bias, dst, stream=None):
-    return lib().bcnn_pack_bias(_ptr(src), dtype, outer, channels, inner, _ptr(bias), _ptr(dst),
-                                _stream(stream))
+    return _calls().pack_bias(src, dtype, outer, channels, inner, bias, dst, stream)
 
 
 def bcnn_conv2d_binary_branches(desc, branches, x_packed, x_branch_stride, w_packed, pad_words, pad_mode,
                                 scale, bias, z, variant=0, stream=None):
-    return lib().bcnn_conv2d_binary_branches(ctypes.byref(_desc(desc)), int(branches), _ptr(x_packed),
-                                             int(x_branch_stride), _ptr(w_packed),
-                                             _ptr(pad_words), int(pad_mode), _ptr(scale), _ptr(bias),
-                                             _ptr(z), int(variant), _stream(stream))
+    return _calls().conv2d_binary_branches(desc, branches, x_packed, x_branch_stride, w_packed, pad_words, pad_mode, scale,
+                                           bias, z, variant, stream)
 
 
 def bcnn_conv2d_binary_branches_sign_pack(desc, branches, x_packed, x_branch_stride, w_packed, pad_words,
                                           pad_mode, scale, bias, z_packed, variant=0, stream=None):
-    return lib().bcnn_conv2d_binary_branches_sign_pack(
-        ctypes.byref(_desc(desc)), int(branches), _ptr(x_packed), int(x_branch_stride),
-        _ptr(w_packed), _ptr(pad_words), int(pad_mode), _ptr(scale), _ptr(bias), _ptr(z_packed),
-        int(variant), _stream(stream))
+    return _calls().conv2d_binary_branches_sign_pack(desc, branches, x_packed, x_branch_stride, w_packed, pad_words,
+                                                     pad_mode, scale, bias, z_packed, variant, stream)
 
 
 def bcnn_pack_bias_replicated(src, dtype, outer, src_channels, inner, replication, bias, dst, stream=None):
-    return lib().bcnn_pack_bias_replicated(_ptr(src), dtype, outer, src_channels, inner, int(replication),
-                                           _ptr(bias), _ptr(dst), _stream(stream))
+    return _calls().pack_bias_replicated(src, dtype, outer, src_channels, inner, replication, bias, dst, stream)
 
 
 def bcnn_avgpool_bias_sign_pack(src, real_dtype, n, h, w, channels, s, bias, pooled, x_packed, stream=None):
-    return lib().bcnn_avgpool_bias_sign_pack(_ptr(src), int(real_dtype), n, h, w, channels, s, _ptr(bias),
-                                             _ptr(pooled), _ptr(x_packed), _stream(stream))
+    return _calls().avgpool_bias_sign_pack(src, real_dtype, n, h, w, channels, s, bias, pooled, x_packed, stream)
 
 
 def bcnn_conv2d_binary_module(desc, x_packed, w_packed, bn_scale, bn_bias, identity, prelu_slope, next_bias,
                               real_dtype, r, x_next_packed, variant=0, stream=None, identity_channels=0):
-    ep = bcnn_module_epilogue(_ptr(bn_scale), _ptr(bn_bias), _ptr(identity), _ptr(prelu_slope),
-                              _ptr(next_bias), int(real_dtype), int(identity_channels))
-    return lib().bcnn_conv2d_binary_module(ctypes.byref(_desc(desc)), _ptr(x_packed), _ptr(w_packed),
-                                           ctypes.byref(ep), _ptr(r), _ptr(x_next_packed), int(variant),
-                                           _stream(stream))
+    return _calls().conv2d_binary_module(desc, x_packed, w_packed, bn_scale, bn_bias, identity, prelu_slope, next_bias,
+                                         real_dtype, r, x_next_packed, variant, stream, identity_channels)
 
 
 def bcnn_conv2d_binary_branches_module(desc, branches, x_packed, x_branch_stride, w_packed, pad_words, pad_mode,
                                        scale, bias, identity, prelu_slope, next_bias, real_dtype, r,
                                        x_next_packed, variant=0, stream=None, identity_channels=0):
-    ep = bcnn_module_epilogue(None, None, _ptr(identity), _ptr(prelu_slope), _ptr(next_bias), int(real_dtype),
-                              int(identity_channels))
-    return lib().bcnn_conv2d_binary_branches_module(
-        ctypes.byref(_desc(desc)), int(branches), _ptr(x_packed), int(x_branch_stride), _ptr(w_packed),
-        _ptr(pad_words), int(pad_mode), _ptr(scale), _ptr(bias), ctypes.byref(ep), _ptr(r),
-        _ptr(x_next_packed), int(variant), _stream(stream))
+    return _calls().conv2d_binary_branches_module(desc, branches, x_packed, x_branch_stride, w_packed, pad_words, pad_mode,
+                                                  scale, bias, identity, prelu_slope, next_bias, real_dtype, r,
+                                                  x_next_packed, variant, stream, identity_channels)
 
 
 def bcnn_conv2d_binary(desc, x_packed, w_packed, y, stream=None):
-    return lib().bcnn_conv2d_binary(ctypes.byref(_desc(desc)), _ptr(x_packed), _ptr(w_packed),
-                                    _ptr(y), _stream(stream))
+    return _calls().conv2d_binary(desc, x_packed, w_packed, y, stream)
 
 
 def bcnn_conv2d_binary_sign_pack(desc, x_packed, w_packed, thr, y_packed, stream=None):
-    return lib().bcnn_conv2d_binary_sign_pack(ctypes.byref(_desc(desc)), _ptr(x_packed),
-                                              _ptr(w_packed), _ptr(thr), _ptr(y_packed),
-                                              _stream(stream))
+    return _calls().conv2d_binary_sign_pack(desc, x_packed, w_packed, thr, y_packed, stream)
 
 
 def bcnn_conv2d_binary_variant(desc, x_packed, w_packed, thr, out, variant, stream=None):
-    return lib().bcnn_conv2d_binary_variant(ctypes.byref(_desc(desc)), _ptr(x_packed),
-                                            _ptr(w_packed), _ptr(thr), _ptr(out), int(variant),
-                                            _stream(stream))
+    return _calls().conv2d_binary_variant(desc, x_packed, w_packed, thr, out, variant, stream)
 
 
 def bcnn_threshold_sign_pack(y, thr, rows, c_out, y_packed, stream=None):
-    return lib().bcnn_threshold_sign_pack(_ptr(y), _ptr(thr), rows, c_out, _ptr(y_packed),
-                                          _stream(stream))
+    return _calls().threshold_sign_pack(y, thr, rows, c_out, y_packed, stream)
 
 
 def bcnn_diag_copy_u32(src, dst, words, stream=None):

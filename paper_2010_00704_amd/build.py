@@ -1,4 +1,4 @@
-"""Builds libbcnn.so (HIP, gfx950) next to this file with hipcc."""
+"""Builds libbcnn.so (HIP, gfx950, with hipcc) and _marshal.so (argument marshalling for Python, with g++) next to this file."""
 import glob
 import os
 import subprocess
@@ -6,6 +6,7 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libbcnn.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -29,9 +30,31 @@ def _run(cmd):
     return proc.returncode, log
 
 
+def build_marshal():
+    """Compile csrc/marshal.cpp, a Python extension on torch's C++ headers, into _marshal.so."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    libs = os.path.join(root, "lib")
+    tmp = MARSHAL_PATH + ".tmp.%d" % os.getpid()
+    rc, log = _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                    "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                    "-I", os.path.join(_ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+                    "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                    "-isystem", "/opt/rocm/include", os.path.join(_HERE, "csrc", "marshal.cpp"), "-o", tmp,
+                    "-L", libs, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + libs])
+    if rc != 0:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        raise RuntimeError("building _marshal.so failed:\n" + log)
+    os.replace(tmp, MARSHAL_PATH)
+    return MARSHAL_PATH
+
+
 def build_library(verbose=False):
     """Compile every .hip file under csrc/ (one hipcc process per file, in
-    parallel) and link them into libbcnn.so.  Always compiles."""
+    parallel) and link them into libbcnn.so; build _marshal.so.  Always compiles."""
     import shutil
     import tempfile
     from concurrent.futures import ThreadPoolExecutor
@@ -44,7 +67,9 @@ def build_library(verbose=False):
         objs = [os.path.join(tmpdir, os.path.basename(src) + ".o") for src in srcs]
         jobs = min(len(srcs), max(1, min(8, os.cpu_count() or 1)))
         with ThreadPoolExecutor(max_workers=jobs) as pool:
+            marshal = pool.submit(build_marshal)
             results = list(pool.map(lambda so: _run([HIPCC] + common + ["-c", so[0], "-o", so[1]]), zip(srcs, objs)))
+        marshal.result()
         logs = []
         for src, (rc, log) in zip(srcs, results):
             if rc != 0:
