@@ -16,7 +16,13 @@
 //   - Parameters are vector loads through buffers (a missing one is a buffer of no bytes): scalar loads under branches
 //     cost more than the rest of a wave (28.6 against 22.9 us).
 //   - One block per wave: walking two or four with the next one's operands in flight was slower at 55 of 64 shapes.
-//   - Real-valued chain: the interface's order, one rounding per step.
+//   - Real-valued chain: the interface's order, one rounding per step.  It is most of a wave's instructions, and on few resident
+//     waves their issue is not hidden: 12.3 us where the same loads and stores alone take 9.5 (half, 128 channels, 32 maps of 56 x
+//     56), 9.7 and 6.7 (256 channels, 28 x 28).  Conversions inside the additions, one rounding per pair of elements, signs without
+//     lane masks and no division where the identity is not replicated took 588 vector instructions to 489 (half; float 503,
+//     bfloat16 553): 12.3 -> 12.1, 9.7 -> 8.7, 128 maps of 28 x 28 26.4 -> 24.2, 96 channels, 32 maps of 56 x 56 11.5 -> 10.9.
+//     Tried: the parameters through LDS (28 registers fewer; 256 channels 24.2 -> 26.2, float 41 -> 45), and on top of it half of the
+//     pixels at a time for a fifth wave on every SIMD (spills; 9.7, 29).
 // The plain case only (every part of the module present, rows of whole 16-byte vectors); everything else takes the
 // direct kernel.
 // Measured (graph replays of one call, so partly from the last-level cache; us, against the kernel that ran the call before):
@@ -51,6 +57,15 @@ struct StreamArgs {
 
 __device__ __forceinline__ int row_to_channel(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
 
+// v + t in float.  Half: one instruction that converts on its way (fma with a factor of one that the compiler does not see; the
+// product is exact, so there is one rounding, as in an addition).
+template <int REAL>
+__device__ __forceinline__ float plus(typename real_type<REAL>::type v, float t, float one)
+{
+    if constexpr (REAL == REAL_F16) return __builtin_fmaf((float)v, one, t);
+    else return (float)v + t;
+}
+
 template <int NKS, int CB, int WC, int REAL>
 __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ? 2 : 3) void conv_mfma_stream_kernel(
     StreamArgs a, const uint32_t* __restrict__ x, const uint32_t* __restrict__ w, ModuleEp ep)
@@ -59,6 +74,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
     constexpr int ESZ = REAL == REAL_F32 ? 4 : 2;
     constexpr int PER = 16 / ESZ;                            // channels of a 16-byte vector
     typedef real_t realv __attribute__((ext_vector_type(PER)));
+    typedef real_t real2 __attribute__((ext_vector_type(2)));
     constexpr int TCH = 32 * CB;
     constexpr int CG = TCH / PER;                            // lanes per pixel
     constexpr int PX_STEP = 64 / CG;                         // pixels per vector instruction
@@ -82,6 +98,8 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
     uint32_t m8, c2;                                         // held in registers: v_and_or_b32 takes no literals
     asm volatile("v_mov_b32 %0, 0x88888888" : "=v"(m8));
     asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(c2));
+    float one;
+    asm volatile("v_mov_b32 %0, 1.0" : "=v"(one));
     auto expand = [&](uint32_t word) -> v4i {
         return v4i{(int)(((word << 3) & m8) | c2), (int)(((word << 2) & m8) | c2), (int)(((word << 1) & m8) | c2),
                    (int)((word & m8) | c2)};
@@ -118,9 +136,11 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
     const bool chan_ok = c0 < s.c_out;                       // c_out is a multiple of PER
     const int id_row = ep.id_channels * ESZ, r_row = s.c_out * ESZ, xn_row = s.cwo * 4;
     const uint32_t NOWHERE = 0x7FFFFFF0u;                    // past every buffer
-    const uint32_t id_off = chan_ok ? (uint32_t)(px0 * id_row + (c0 % ep.id_channels) * ESZ) : NOWHERE;
-    const uint32_t r_off = chan_ok ? (uint32_t)(px0 * r_row + c0 * ESZ) : NOWHERE;
-    const uint32_t xn_off = chan_ok && (cl & 31) == 0 ? (uint32_t)(px0 * xn_row + (c0 >> 5) * 4) : NOWHERE;
+    int id0 = c0;
+    if (ep.id_channels != s.c_out) id0 = c0 % ep.id_channels;   // (uniform: a division is twenty instructions)
+    const uint32_t id_off = chan_ok ? __umul24((uint32_t)px0, (uint32_t)id_row) + (uint32_t)(id0 * ESZ) : NOWHERE;
+    const uint32_t r_off = chan_ok ? __umul24((uint32_t)px0, (uint32_t)r_row) + (uint32_t)(c0 * ESZ) : NOWHERE;
+    const uint32_t xn_off = chan_ok && (cl & 31) == 0 ? __umul24((uint32_t)px0, (uint32_t)xn_row) + (uint32_t)((c0 >> 5) * 4) : NOWHERE;
     // the block's rows of a tensor: base and the bytes that exist
     auto rows_of = [&](const void* base, int row_bytes) {
         const int m = 32 * b;
@@ -154,7 +174,7 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
     for (int cb = 0; cb < CB; ++cb) {
         const int ch = o0 + 32 * cb + row_to_channel(j);
         int v[NKS];
-        load_words(wres, (ch < s.c_out ? ch : s.c_out - 1) * s.cw, true, v);
+        load_words(wres, (int)__umul24((uint32_t)(ch < s.c_out ? ch : s.c_out - 1), (uint32_t)s.cw), true, v);
 #pragma unroll
         for (int i = 0; i < NKS; ++i) fw[cb][i] = expand((uint32_t)v[i]);
     }
@@ -172,6 +192,8 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
     load_params(ep.bias, pb);
     load_params(ep.slope, pa);
     load_params(ep.next_bias, pc);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) pc[k] = pc[k] + 0.0f;      // -0 becomes +0: no sum with it is -0
     if (!ep.slope) {
 #pragma unroll
         for (int k = 0; k < PER; ++k) pa[k] = 1.0f;
@@ -211,21 +233,32 @@ __global__ __launch_bounds__(256, CB == 1 ? 4 : (REAL == REAL_F32 || NKS == 4) ?
             const v4f v = *reinterpret_cast<const v4f*>(from + q);
             y[q] = v[0]; y[q + 1] = v[1]; y[q + 2] = v[2]; y[q + 3] = v[3];
         }
-        realv st;
-        float stored[PER];
+        float t[PER], stored[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            float t = __builtin_fmaf(pg[k], y[k], pb[k]);
-            t = t + (float)id[g][k];
-            const float neg = pa[k] * t;
-            t = t >= 0.0f ? t : neg;
-            st[k] = (real_t)t;
-            stored[k] = (float)st[k];
+            t[k] = plus<REAL>(id[g][k], __builtin_fmaf(pg[k], y[k], pb[k]), one);
+            const float neg = pa[k] * t[k];
+            t[k] = t[k] >= 0.0f ? t[k] : neg;
         }
+        v4i st;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) stored[k] = stored[k] + pc[k];
-        const uint32_t bits = sign_bits(stored);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, st), r_res, (int)(r_off + (uint32_t)(g * PX_STEP * r_row)), 0, 0);
+        for (int k = 0; k < PER; k += PER / 4) {
+            if constexpr (REAL == REAL_F32) {
+                st[k] = __float_as_int(t[k]);
+                stored[k] = t[k] + pc[k];
+            } else {
+                // rounded two at a time; what the stream stores is read back from the packed pair (which the asm hides: the
+                // compiler would round every element a second time)
+                int pair = __builtin_bit_cast(int, real2{(real_t)t[k], (real_t)t[k + 1]});
+                asm("" : "+v"(pair));
+                const real2 two = __builtin_bit_cast(real2, pair);
+                stored[k] = plus<REAL>(two[0], pc[k], one);
+                stored[k + 1] = plus<REAL>(two[1], pc[k + 1], one);
+                st[k / 2] = pair;
+            }
+        }
+        const uint32_t bits = sign_bits_of_sums(stored);
+        __builtin_amdgcn_raw_buffer_store_b128(st, r_res, (int)(r_off + (uint32_t)(g * PX_STEP * r_row)), 0, 0);
         // 32 / PER neighbouring lanes hold the 32 channels of one packed word
         uint32_t wd = (chan_ok ? bits : 0u) << (cl & 31);
         wd |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)wd, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]

@@ -20,4 +20,16 @@ __device__ __forceinline__ uint32_t sign_bits(const float (&v)[N])
     return bits;
 }
 
+// The same for results of an addition of which none is -0 (one summand was not -0): two instructions a value, no lane masks.
+// The maximum turns NaN, and nothing else of that sign, into a negative number.
+template <int N>
+__device__ __forceinline__ uint32_t sign_bits_of_sums(const float (&v)[N])
+{
+    uint32_t negative = 0;
+#pragma unroll
+    for (int k = N - 1; k >= 0; --k)
+        negative = __builtin_amdgcn_alignbit(negative, __float_as_uint(__builtin_fmaxf(v[k], -3.402823466e38f)), 31);
+    return ~negative & ((1u << N) - 1u);
+}
+
 }  // namespace bcnn

@@ -54,3 +54,43 @@ def test_module_stream(shape, half):
                                             real_code(half), r.ptr, xn.ptr, identity_channels=idc), "module")
         assert np.array_equal(r.get(real_np_dtype(half), m * o).reshape(m, o), want)
         assert np.array_equal(xn.get(np.uint32).reshape(m, cwo), bits)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16], ids=str)
+@pytest.mark.parametrize("c_out", [8, 64, 136])
+def test_special_values(c_out, dtype):
+    """Zeros of both signs, infinities, NaN, the types' largest and subnormal values in identity and parameters: the same
+    stream and the same bits as the vector-ALU kernel's (which has the oracle's plain comparison), NaN in the same places."""
+    gpu_device()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(72000 + c_out)
+    m, c = 999, 96
+    inf, nan, top = float("inf"), float("nan"), torch.finfo(dtype).max
+    odd = torch.tensor([0.0, -0.0, inf, -inf, nan, top, -top, 6e-8, -6e-8, 1e-45, -1e-45, 70000.0, -70000.0, 1.5, -1.5], device="cuda")
+
+    def pick(shape):
+        plain = torch.rand(shape, generator=gen, device="cuda") * 20 - 10
+        at = torch.randint(0, 2 * len(odd), shape, generator=gen, device="cuda")
+        return torch.where(at < len(odd), odd[at % len(odd)], plain)
+
+    x = torch.randint(-2 ** 31, 2 ** 31 - 1, (m, c // 32), generator=gen, device="cuda").to(torch.int32)
+    wt = torch.randint(-2 ** 31, 2 ** 31 - 1, (c_out, c // 32), generator=gen, device="cuda").to(torch.int32)
+    ident = pick((m, c_out)).to(dtype)
+    ident[: m // 2] = -0.0                              # sums that are zeros of either sign, too
+    g, b, slope, nxt = (pick((c_out,)) for _ in range(4))
+    g[::2], b[::4], nxt[::3] = 0.0, -0.0, -0.0
+    slope[::5] = 0.0
+    d = B.conv_desc(1, c, m, 1, c_out, 1, 1, 0)
+    code = {torch.float32: B.BCNN_F32, torch.float16: B.BCNN_F16, torch.bfloat16: B.BCNN_BF16}[dtype]
+    got = []
+    for variant in (B.BCNN_VARIANT_AUTO, B.BCNN_VARIANT_VALU):
+        r = torch.empty((m, c_out), dtype=dtype, device="cuda")
+        xn = torch.empty((m, (c_out + 31) // 32), dtype=torch.int32, device="cuda")
+        B.check(B.bcnn_conv2d_binary_module(d, x, wt, g, b, ident, slope, nxt, code, r, xn, variant), "module")
+        got.append((r, xn))
+    (r0, x0), (r1, x1) = got
+    raw = torch.int32 if dtype == torch.float32 else torch.int16
+    none = torch.isnan(r1)
+    assert torch.equal(torch.isnan(r0), none) and none.any() and (~none).any()
+    assert torch.equal(r0.view(raw)[~none], r1.view(raw)[~none])
+    assert torch.equal(x0, x1)
