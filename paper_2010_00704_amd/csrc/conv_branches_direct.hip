@@ -16,9 +16,15 @@ hipError_t launch_pad(DirectArgs a, const BranchArgs& b, const DirectBranch& br,
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a, b.x, b.w, (const int32_t*)nullptr, b.out, ep, br);
     };
-    if (b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NOTHING>);
-    else if (b.pad_words) go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_OPERAND>);
-    else go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NONE>);
+    if constexpr (WK > 1) {
+        if (a.s.pad && b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NOTHING>);
+        else if (a.s.pad && b.pad_words) go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_OPERAND>);
+        else go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NONE>);
+    } else {
+        // (nine taps are more than this form is chosen for: shared_plan.h)
+        if (a.s.pad) return hipErrorInvalidValue;
+        go(conv_mfma_direct_kernel<CB, PB, WC, WP, WK, OUT, BRANCH + PAD_NONE>);
+    }
     return hipGetLastError();
 }
 

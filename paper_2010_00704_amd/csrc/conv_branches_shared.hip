@@ -15,8 +15,9 @@ hipError_t launch_pad(DirectArgs a, const BranchArgs& b, const DirectBranch& br,
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a, b.x, b.w, (const int32_t*)nullptr, b.out, ep, br);
     };
-    if (b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, 1, 4, 1, OUT, BRANCH + PAD_NOTHING, WIDE>);
-    else if (b.pad_words) go(conv_mfma_direct_kernel<CB, PB, 1, 4, 1, OUT, BRANCH + PAD_OPERAND, WIDE>);
+    // (without padding every tap is inside)
+    if (a.s.pad && b.zero_pad) go(conv_mfma_direct_kernel<CB, PB, 1, 4, 1, OUT, BRANCH + PAD_NOTHING, WIDE>);
+    else if (a.s.pad && b.pad_words) go(conv_mfma_direct_kernel<CB, PB, 1, 4, 1, OUT, BRANCH + PAD_OPERAND, WIDE>);
     else go(conv_mfma_direct_kernel<CB, PB, 1, 4, 1, OUT, BRANCH + PAD_NONE, WIDE>);
     return hipGetLastError();
 }

@@ -44,9 +44,9 @@
 // shared weights the pixels are the instruction's rows, so that a tap's scale is one register a block: 16-byte scale reads
 // took as much LDS time as the weights (24.7 us against 26.7 on the first call below), and zeros as an inline start
 // operand replace a move per element and tap.  Measured, us: 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 in the
-// staged kernel, 33.7 every wave for itself, 22.9 shared (pad words 3 of that: a second load and an OR); 160 -> 160, 49 maps of
+// staged kernel, 33.7 every wave for itself, 22.9 shared, 21.5 since pad words are added behind the loads' wait (20.7 without them); 160 -> 160, 49 maps of
 // 41 x 41, float 44.6 and 24.8; 64 -> 64, 213 maps of 39 x 42, half tail 57 and 39; 384 -> 384, 2 maps of 13 x 13, bits 12.9 and, taps
-// apart, 6.6.  2 x 2 blocks a wave (two waves per SIMD) 28.8 on the first of these, 1 x 2 36.8.
+// apart, 6.6 (in a graph 6.0, and 5.1 with the pad words behind the wait).  2 x 2 blocks a wave (two waves per SIMD) 28.8 on the first of these, 1 x 2 36.8.
 #pragma once
 #include "bcnn_common.h"
 #include "branch_walk.h"
@@ -248,7 +248,8 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
     // past the buffers (taps outside the image, K padding) read as zero.
     const auto xres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(x), 0, a.x_bytes, 0x00020000);
     const auto wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(w), 0, a.w_bytes, 0x00020000);
-    struct Chunk { v4i w[CB], x[PB]; };
+    // (pad words are a second load, added when the chunk is multiplied: added at once it would wait for both loads)
+    struct Chunk { v4i w[CB], x[PB], pad[PAD == PAD_OPERAND ? PB : 1]; };
     auto fetch = [&](int chunk, Chunk& c) {
         const int u = 2 * chunk + hsel;
         if constexpr (MODE == UNITS || MODE == TAIL) {
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
             for (int cb = 0; cb < CB; ++cb) fw[cb] = expand((uint32_t)c.w[cb][ks]);
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
-                const v8i fx = expand((uint32_t)c.x[pb][ks]);
+                const v8i fx = expand((uint32_t)(PAD == PAD_OPERAND ? c.x[pb][ks] | c.pad[pb][ks] : c.x[pb][ks]));
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
                     acc[cb][pb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[cb], fx, acc[cb][pb], 4, 4, 0, 0, 0, 0);
@@ -382,7 +383,11 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                 v[at + 1] = q[1];
             } else v[at] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, off, 0, 0);
         };
-        struct Inputs { int x[PB][STEPS]; };
+        // Pad words are a second load, added when the group is multiplied: added where it is fetched it waits for both loads.  A
+        // module's tail has no registers for that: a wave less on every SIMD costs more than the wait (64 -> 64, 80 maps of 39 x 39,
+        // half 18.0 us and 19.3 added later; 200 -> 200, 20 maps of 27 x 27, float 17.0 and 18.3).
+        constexpr bool PAD_LATER = PAD == PAD_OPERAND && !MODULE;
+        struct Inputs { int x[PB][STEPS], pad[PAD_LATER ? PB : 1][STEPS]; };
         auto fetch_x = [&](int gi, Inputs& c) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < TPG; ++i) {
@@ -395,9 +400,11 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                     const int in = __builtin_amdgcn_sbfe((int)vmask[pb], (uint32_t)bit, 1u);     // all bits or none
                     load_words(xres, ((rb[pb] + xo) & in) | (~in & -16), c.x[pb], i * WIDE);
                     if constexpr (PAD == PAD_OPERAND) {
-                        if (s.ks == 3) {
+                        const int at = (((tap * s.cw + hsel * br.half + k) * 4) & ~in) | (in & -16);
+                        if constexpr (PAD_LATER) load_words(pres, at, c.pad[pb], i * WIDE);
+                        else if (!NARROW || s.ks == 3) {     // (always: the branch keeps the loads of a narrow group's taps apart, else again too many registers)
                             int p[STEPS];
-                            load_words(pres, (((tap * s.cw + hsel * br.half + k) * 4) & ~in) | (in & -16), p, i * WIDE);
+                            load_words(pres, at, p, i * WIDE);
 #pragma unroll
                             for (int q = i * WIDE; q < (i + 1) * WIDE; ++q) c.x[pb][q] |= p[q];
                         }
@@ -455,7 +462,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
         auto step = [&](const Fragments& fw, const Inputs& c, int ks, bool first) __attribute__((always_inline)) {
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
-                const v8i fx = expand((uint32_t)c.x[pb][ks]);
+                const v8i fx = expand((uint32_t)(PAD_LATER ? c.x[pb][ks] | c.pad[pb][ks] : c.x[pb][ks]));
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
                     const v8i w8 = {fw.f[cb][0], fw.f[cb][1], fw.f[cb][2], fw.f[cb][3], 0, 0, 0, 0};
@@ -631,10 +638,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                 for (int pb = 0; pb < PB; ++pb) {
                     const bool in = s.ks == 1 || ((vmask[pb] >> tap) & 1u);
                     c.x[pb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(xres, in ? (rbase[pb] + xo) * 4 : -16, 0, 0));
-                    if constexpr (PAD == PAD_OPERAND) {
-                        if (s.ks == 3)
-                            c.x[pb] |= __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(pres, in ? -16 : wo * 4, 0, 0));
-                    }
+                    if constexpr (PAD == PAD_OPERAND) c.pad[pb] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(pres, in ? -16 : wo * 4, 0, 0));
                 }
             } else {
 #pragma unroll
@@ -648,10 +652,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                     for (int pb = 0; pb < PB; ++pb) {
                         const bool in = s.ks == 1 || ((vmask[pb] >> tap) & 1u);
                         c.x[pb][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(xres, real && in ? (rbase[pb] + xo + i) * 4 : -4, 0, 0);
-                        if constexpr (PAD == PAD_OPERAND) {
-                            if (s.ks == 3)
-                                c.x[pb][i] |= (int)__builtin_amdgcn_raw_buffer_load_b32(pres, real && !in ? (wo + i) * 4 : -4, 0, 0);
-                        }
+                        if constexpr (PAD == PAD_OPERAND) c.pad[pb][i] = (int)__builtin_amdgcn_raw_buffer_load_b32(pres, real && !in ? (wo + i) * 4 : -4, 0, 0);
                     }
                 }
             }
@@ -701,6 +702,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                 const int ch = o0 - TCH * wc + cl;
                 scale_lds[tp][cl] = br.scale[(size_t)tp * s.c_out + (ch < s.c_out ? ch : s.c_out - 1)];
             }
+            static_assert(!BR || WK > 1 || PAD == PAD_NONE, "calls whose taps leave the image take the other forms");
             Chunk cur, nxt;
             fetch_group(0, 0, cur);
 #pragma unroll
@@ -728,15 +730,12 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                     for (int q = 0; q < 4; ++q) {
                         const v4f sc = *reinterpret_cast<const v4f*>(&scale_lds[tap][TCH * wc + 32 * cb + 16 * hsel + 4 * q]);
 #pragma unroll
-                        for (int pb = 0; pb < PB; ++pb) {
-                            const bool in = PAD != PAD_NOTHING || s.ks == 1 || ((vmask[pb] >> tap) & 1u);
+                        for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                             for (int k = 0; k < 4; ++k) {
-                                const float zn = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
-                                tot[cb][pb][4 * q + k] = in ? zn : tot[cb][pb][4 * q + k];
+                                tot[cb][pb][4 * q + k] = __builtin_fmaf(sc[k], acc[cb][pb][4 * q + k], tot[cb][pb][4 * q + k]);
                                 acc[cb][pb][4 * q + k] = start;
                             }
-                        }
                     }
             }
         }
