@@ -479,17 +479,31 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
             for (int cb = 0; cb < CB; ++cb) sc[cb] = scale_lds[tap][32 * cb + j];
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
-                // lane i of a half holds the validity of pixel row_to_channel(i): of the lane's r-th one in bit 8 (r / 4) + r % 4
-                const uint32_t inside = PAD == PAD_NOTHING ? (uint32_t)__ballot((vmask[pb] >> tap) & 1u) : ~0u;
-                const uint32_t mine = inside >> (4 * hsel);
+                if constexpr (PAD == PAD_NOTHING) {
+                    // Lane i of a half holds the validity of pixel row_to_channel(i): of a lane's r-th one in bit 8 (r / 4) + r % 4, of
+                    // the upper half's four bits further.  Both become a lane mask on the scalar unit (us, bit tests per lane and
+                    // this: 3x3, 256 -> 256, 64 maps of 28 x 28, bits 27.6 and 25.5; 160 -> 160, 49 maps
+                    // of 41 x 41, float 28.2 and 25.2; 96 -> 96, 30 maps of 30 x 30 8.9 and 8.0).
+                    const int inside = (int)(uint32_t)__ballot((vmask[pb] >> tap) & 1u);
+                    if (inside != -1) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int bit = 8 * (r >> 2) + (r & 3);
+                            const uint64_t lo = (uint32_t)((inside << (31 - bit)) >> 31), hi = (uint32_t)((inside << (27 - bit)) >> 31);
+                            const bool in = __builtin_amdgcn_inverse_ballot_w64(lo | hi << 32);
+#pragma unroll
+                            for (int cb = 0; cb < CB; ++cb) {
+                                const float zn = __builtin_fmaf(sc[cb], acc[cb][pb][r], tot[cb][pb][r]);
+                                tot[cb][pb][r] = in ? zn : tot[cb][pb][r];
+                            }
+                        }
+                        continue;
+                    }
+                }
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float zn = __builtin_fmaf(sc[cb], acc[cb][pb][r], tot[cb][pb][r]);
-                        const bool in = PAD != PAD_NOTHING || ((mine >> (8 * (r >> 2) + (r & 3))) & 1u);
-                        tot[cb][pb][r] = in ? zn : tot[cb][pb][r];
-                    }
+                    for (int r = 0; r < 16; ++r) tot[cb][pb][r] = __builtin_fmaf(sc[cb], acc[cb][pb][r], tot[cb][pb][r]);
             }
         };
         auto group = [&](int gi, const char* from, const Inputs& c) __attribute__((always_inline)) {
