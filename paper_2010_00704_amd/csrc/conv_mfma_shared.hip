@@ -40,7 +40,7 @@ hipError_t launch_wide(const DirectArgs& a, const DirectBranch& br, int wide, co
 
 }  // namespace
 
-int conv_mfma_shared_choose(const ConvShape& s, int kind, const DirectChoice& other) { return shared_choose(s.m, s.c_out, s.cw, s.ks, kind, other); }
+int conv_mfma_shared_choose(const ConvShape& s, int kind, const DirectChoice& other) { return shared_choose(s.m, s.c_out, s.cw, s.ks, s.stride, kind, other); }
 
 hipError_t launch_conv_mfma_shared(const ConvShape& s, const uint32_t* x, const uint32_t* w, const int32_t* thr, void* out,
                                    const ModuleEp* ep, int tile, hipStream_t stream)

@@ -50,18 +50,29 @@ inline double shared_cost(const SharedCost& c, int cb, int pb, int m, int c_out,
 }
 
 // The tile, or SHARED_NONE where `other` is estimated to be as good.  Against the tiles that do not split K this form may be
-// estimated a tenth behind (but for sums, which their stores bind): their estimates are that much too low on the calls that
-// this one is ahead on.  Over the 860 calls: bits 1.14 times the other choice on average, sums 1.05, half modules 1.03, float
-// ones 1.01; 7 calls more than 4 % behind it, 14 % at worst.  (us, other and this: bits, 3x3, 320 -> 192, 39 maps of 38 x 38
+// estimated a tenth behind: their estimates are that much too low on the calls that this one is ahead on.  Not so for sums,
+// which their stores bind, and for modules whose taps are whole 16-byte units (a multiple of four words), which those tiles walk without masks
+// (us, other and this: half module, 3x3, 110 -> 88, 73 maps of 41 x 41 20.8 and 23.0; 117 -> 224, 25 maps of 39 x 39 17.6 and 19.5;
+// of 265 such calls 88 were more than 3 % behind, 1 is).
+// Beyond 32 words a tap, where the fits end, a 3x3 filter stays on the tiles that split K: this form falls behind its estimate
+// there (half module, 1032 -> 61, 97 maps of 41 x 41 70 and 78; sums, 1083 -> 800, 14 maps of 28 x 28 49 and 63; 117 of 132 calls
+// of 33 to 48 words behind or level, 11 % on average; up to 32 words 4 to 17 % ahead).  Under stride 2, where no two rows share their
+// taps' lines, so do sums and modules from 17 words on (half module, 562 -> 268, 9016 pixels 14.8 and 16.9; sums, 672 -> 544, 15 680 pixels
+// 35 and 42; 62 calls of 17 to 32 words 1 % ahead on average, 14 of them more than 3 % behind; bits 8 to 19 % ahead).
+// Over 3000 calls that the estimates without the last two rules give to this form: bits 1.29 times the other choice on average,
+// sums 1.26, half modules 1.12, float ones 1.13; 21 of them more than 5 % behind it, 13 % at worst (sums, 3x3, 32 -> 1007,
+// 80 556 pixels 76 and 87: what is left of the estimates' error).  (us, other and this: bits, 3x3, 320 -> 192, 39 maps of 38 x 38
 // 27.9 and 16.3; 64 -> 64, 156 maps of 25 x 28 9.8 and 6.9; 1x1, 704 -> 704, 40 maps of 26 x 26 14.9 and 10.8; sums, 3x3, 468 -> 39,
 // 191 maps of 37 x 36 52 and 38.)
-inline int shared_choose(int m, int c_out, int cw, int ks, int kind, const DirectChoice& other)
+inline int shared_choose(int m, int c_out, int cw, int ks, int stride, int kind, const DirectChoice& other)
 {
     // sums of a 1x1 filter are bound by their store, which the other tiles keep busier (64 -> 672, 46 maps of 51 x 29 30.7 and 33.9)
     if (kind == SHARED_SUMS && ks == 1) return SHARED_NONE;
+    const bool split_k = other.tile == DIRECT_1x1_K4 || other.tile == DIRECT_2x2_K4;
+    if (split_k && ks == 3 && cw > (stride > 1 && kind != SHARED_BITS ? 16 : 32)) return SHARED_NONE;
     const int taps = ks * ks, steps = SharedWalk::make(cw, taps).steps(taps);
-    const bool whole_k = other.tile == DIRECT_2x1 || other.tile == DIRECT_1x1;
-    double least = other.cost * (whole_k && kind != SHARED_SUMS ? 1.1 : 1.0);
+    const bool too_low = (other.tile == DIRECT_2x1 || other.tile == DIRECT_1x1) && (kind == SHARED_BITS || (kind != SHARED_SUMS && cw % 4 != 0));
+    double least = other.cost * (too_low ? 1.1 : 1.0);
     int best = SHARED_NONE;
     for (const SharedTile& t : SHARED_TILES) {
         const SharedCost& c = t.kind[kind];

@@ -1,6 +1,6 @@
 """The direct kernel's form whose workgroups share expanded weights: every tile and width of its loads, for each kind of
 output, and in branch mode also the form whose waves take whole taps, against the vector-ALU kernels (which the other tests hold against the oracle).  Pixels, channels and words are
-ragged; operands lie a word past an allocation's start, so that the staged kernel covers none of these calls.  Which tile and
+ragged; operands lie a word past an allocation's start, so that the staged kernel covers none of these calls (but ALIGNED).  Which tile and
 width a call takes is checked on the host, from the same list, by test_host_shared_plan.py."""
 import pytest
 import torch
@@ -44,12 +44,11 @@ CONVS = [
     (SUMS, S_2X2, 3, (61, 140, 27, 26, 200, 3, 1)),
     (SUMS, S_2X2, 4, (101, 200, 27, 27, 100, 3, 1)),
     (SUMS, S_2X2, 5, (61, 260, 27, 26, 130, 3, 1)),
-    (HALF, S_1X1, 2, (101, 110, 27, 27, 70, 3, 2)),
     (HALF, S_1X1, 3, (101, 140, 27, 27, 70, 3, 2)),
     (HALF, S_1X1, 4, (61, 200, 27, 26, 33, 3, 1)),
     (HALF, S_1X1, 5, (101, 260, 27, 27, 70, 3, 2)),
     (HALF, S_2X1, 1, (101, 50, 27, 27, 100, 3, 1)),
-    (HALF, S_2X1, 2, (61, 110, 27, 26, 100, 3, 1)),
+    (HALF, S_2X1, 2, (61, 75, 27, 26, 339, 3, 1)),
     (HALF, S_2X1, 3, (101, 140, 27, 27, 33, 3, 1)),
     (HALF, S_2X1, 4, (101, 200, 27, 27, 33, 3, 1)),
     (HALF, S_2X1, 5, (101, 260, 27, 27, 33, 3, 1)),
@@ -59,6 +58,12 @@ CONVS = [
     (FLOAT, S_2X1, 3, (101, 140, 27, 27, 300, 3, 2)),
     (FLOAT, S_2X1, 4, (101, 420, 27, 27, 100, 3, 1)),
     (FLOAT, S_2X1, 5, (101, 260, 27, 27, 300, 3, 2)),
+]
+
+# modules of whole 128-channel tiles and 16-byte aligned operands, which the staged kernel covers as well
+ALIGNED = [
+    (HALF, S_1X1, 2, (39, 128, 14, 14, 640, 3, 1)),
+    (FLOAT, S_1X1, 2, (46, 128, 14, 14, 640, 3, 1)),
 ]
 
 OWN, APART, SHARED = 0, 1, 2                           # branch forms; tile 1 of APART: four waves a block
@@ -93,12 +98,15 @@ BRANCHES = [
 ]
 
 
-@pytest.mark.parametrize("kind,tile,wide,shape", CONVS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+@pytest.mark.parametrize("kind,tile,wide,shape", CONVS + ALIGNED, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_tile(kind, tile, wide, shape):
     gpu_device()
     n, c, h, w, o, k, stride = shape
     d = Draw(83000 + 17 * c + o + kind)
     (x, _, keep_x), (wt, _, keep_w) = d.packed(n, c, h, w), d.packed(o, c, k, k)
+    if (kind, tile, wide, shape) in ALIGNED:
+        keep_x, keep_w = keep_x[1:].clone(), keep_w[1:].clone()
+        x, wt = keep_x.data_ptr(), keep_w.data_ptr()
     desc = B.conv_desc(n, c, h, w, o, k, stride, k // 2)
     ho, wo = B.out_shape(desc)
     m, words, total = n * ho * wo, (o + 31) // 32, c * k * k

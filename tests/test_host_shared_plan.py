@@ -29,18 +29,19 @@ def choices(checker, calls, mode="calls"):
     return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
 
 
-def call(kind, n, c, h, w, o, k, stride):
+def call(kind, n, c, h, w, o, k, stride, staged=0):
     m = n * ((h - 1) // stride + 1) * ((w - 1) // stride + 1)
-    return (m, o, (c + 31) // 32, k, min(kind, 3) if kind < 2 else 3, kind, 0)
+    return (m, o, (c + 31) // 32, k, stride, kind if kind < 2 else 2 if staged else 3, kind, staged)
 
 
 def test_every_tile_and_width_is_reached_on_the_gpu(checker):
-    got = choices(checker, [call(kind, *shape) for kind, _, _, shape in G.CONVS])
-    assert got == [(tile, wide) for _, tile, wide, _ in G.CONVS]
-    grid = [(m, o, cw, ks, kind if kind < 2 else 3, kind, 0) for m in (196, 784, 3136, 12544, 50176, 200704) for o in (16, 64, 100, 256, 512)
-            for cw in (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 16, 18, 32) for ks in (1, 3) for kind in (G.BITS, G.SUMS, G.HALF, G.FLOAT)]
-    listed = {(kind, tile, wide) for kind, tile, wide, _ in G.CONVS}
-    reached = {(c[5], tile, wide) for c, (tile, wide) in zip(grid, choices(checker, grid)) if tile}
+    got = choices(checker, [call(kind, *shape) for kind, _, _, shape in G.CONVS] + [call(kind, *shape, staged=1) for kind, _, _, shape in G.ALIGNED])
+    assert got == [(tile, wide) for _, tile, wide, _ in G.CONVS + G.ALIGNED]
+    grid = [(m, o, cw, ks, stride, kind if kind < 2 else 3, kind, 0) for m in (196, 784, 3136, 12544, 50176, 200704) for o in (16, 64, 100, 256, 512)
+            for cw in (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 16, 18, 32) for ks in (1, 3) for stride in (1, 2) for kind in (G.BITS, G.SUMS, G.HALF, G.FLOAT)]
+    grid += [(m, o, cw, ks, stride, kind if kind < 2 else 2 if o % 128 == 0 else 3, kind, 1) for m, o, cw, ks, stride, _, kind, _ in grid if cw % 4 == 0]
+    listed = {(kind, tile, wide) for kind, tile, wide, _ in G.CONVS + G.ALIGNED}
+    reached = {(c[6], tile, wide) for c, (tile, wide) in zip(grid, choices(checker, grid)) if tile}
     assert reached <= listed, sorted(reached - listed)
 
 
@@ -54,3 +55,27 @@ def test_every_branch_form_is_reached_on_the_gpu(checker):
             for p in (2, 3, 9, 16) for out in ("bits", "f32", "module_f32", "module_f16")]
     listed = {(form, tile, wide) for form, tile, wide, _, _ in G.BRANCHES if form == G.SHARED}
     assert {c for c in choices(checker, grid, "branches") if c[0] == G.SHARED} <= listed
+
+
+@pytest.mark.parametrize("kind,shared,call", [
+    # pixels, channels out, words, filter, stride, whether the staged kernel covers the call; times in us of the other kernels and of this form
+    ("half", False, (122713, 88, 4, 3, 1, 0)),           # 20.8, 23.0
+    ("half", False, (45800, 70, 4, 3, 2, 0)),           # 11.5, 13.0
+    ("half", False, (163057, 61, 33, 3, 1, 0)),           # 70.4, 78.5
+    ("half", False, (47579, 416, 33, 3, 2, 0)),           # 123, 166
+    ("float", False, (54000, 96, 35, 3, 2, 0)),           # 45.2, 64.4
+    ("sums", False, (10976, 800, 34, 3, 1, 0)),           # 48.7, 63.1
+    ("half", False, (9016, 268, 18, 3, 2, 0)),           # 14.8, 16.9
+    ("sums", False, (15680, 544, 21, 3, 2, 0)),           # 35.0, 41.7
+    ("half", True, (42000, 339, 3, 3, 2, 0)),           # 40.7, 31.3
+    ("half", True, (41067, 576, 8, 3, 1, 1)),           # 59.2, 44.1
+    ("half", True, (83000, 96, 16, 3, 2, 1)),           # 41.0, 31.3
+    ("float", True, (83655, 96, 24, 3, 1, 1)),           # 52.1, 38.7
+    ("sums", True, (182979, 64, 40, 3, 1, 1)),           # 98.2, 71.3
+    ("bits", True, (56316, 192, 10, 3, 1, 0)),           # 27.9, 16.3
+])
+def test_measured_calls_go_to_the_faster_form(checker, kind, shared, call):
+    m, o, cw, ks, stride, staged = call
+    other, mine = {"bits": (0, G.BITS), "sums": (1, G.SUMS), "half": (3, G.HALF), "float": (3, G.FLOAT)}[kind]
+    (tile, _), = choices(checker, [(m, o, cw, ks, stride, other, mine, staged)])
+    assert (tile != 0) == shared
