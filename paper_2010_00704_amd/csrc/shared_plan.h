@@ -88,12 +88,17 @@ inline int shared_choose(int m, int c_out, int cw, int ks, int stride, int kind,
 //     order: a quarter of the chain of K-steps.  Up to three blocks a compute unit; over 700 calls 2, 2.5, 3.5 and 4 are 0.3 to
 //     2 % slower on average, none of them a call of more.  (us, the waves side by side and this: bits, 3x3, 384 -> 384, 2 maps
 //     of 13 x 13 12.9 and 6.6; 128 -> 128, 8 maps of 10 x 10, float tail 10.5 and 5.0)
-//   - every wave its own operands (direct_plan.h): at most eight words in all, of at most two a tap, so that there is
-//     little expansion to share (64 x 3 -> 128, 29 376 pixels, float 7.1, with shared weights 8.7)
+//   - every wave its own operands (direct_plan.h): at most eight words in all, of at most two a tap, or one branch of up to
+//     four words, so that there is little expansion to share (64 x 3 -> 128, 29 376 pixels, float 7.1, with shared weights 8.7;
+//     one branch, 96 -> 96, 242 452 pixels, bits 13.5 and 16.4; bits of such calls 11 % on average, sums 3 %, tails level)
 //   - shared weights for the rest, 2 x 1 blocks a wave from twelve blocks a compute unit on (8, 10, 16 and 24 are 0.5 to
-//     1.5 % slower on average; with a float tail, whose epilogue weighs more, direct_plan.h's estimates).
+//     1.5 % slower on average; with a float tail, whose epilogue weighs more, direct_plan.h's estimates, and never for narrow taps:
+//     96 x 3 -> 416, 286 117 pixels 199 with 1 x 1 blocks, 258 with 2 x 1) and where their second block does not idle too often: not for one or
+//     three blocks of 32 channels, and five under a half tail (32 x 9 -> 81, 184 730 pixels, half tail 60.6, with 1 x 1 blocks 51)
 // Together 1.33 to 1.40 times the second form alone over 700 calls of all kinds (32 to 1024 channels, 50 to 200 000 pixels, 2 to 9
-// branches); 4 of them more than 4 % behind it, 9 % at worst.
+// branches).  Of 3000 more calls above three blocks a compute unit, 14 are more than 5 % behind
+// the second form, 10 % at worst (most of them tails of nine taps of one or two words with pad words: 64 x 9 -> 85, 53 792 pixels, float 21.1 and
+// 23.6); 35 were before single branches, narrow taps and idle blocks had their rules, 24 % at worst.
 enum { BRANCH_OWN = 0, BRANCH_APART, BRANCH_SHARED };
 constexpr int APART_TAPS = 9;                                // sums of taps that fit LDS
 struct BranchChoice { int form, tile; };
@@ -102,8 +107,10 @@ inline BranchChoice branches_choose(int m, int c_out, int cw, int branches, bool
     const int64_t blocks = (((int64_t)m + 31) / 32) * ((c_out + 31) / 32);
     if (branches <= APART_TAPS && blocks <= 3 * 256) return BranchChoice{BRANCH_APART, DIRECT_1x1_K4};
     const int own = branches_direct_choose(m, c_out, cw, branches, tail, half);
-    if (cw <= 2 && cw * branches <= 8) return BranchChoice{BRANCH_OWN, own};
-    const bool wide = tail && !half ? own != DIRECT_1x1 : blocks >= 12 * 256 && c_out > 32;
+    if ((cw <= 2 && cw * branches <= 8) || (branches == 1 && cw <= 4)) return BranchChoice{BRANCH_OWN, own};
+    const int across = (c_out + 31) / 32;
+    const bool filled = across % 2 == 0 || across > (tail && half ? 5 : 3);
+    const bool wide = filled && (tail && !half ? cw > 4 && own != DIRECT_1x1 : blocks >= 12 * 256);
     return BranchChoice{BRANCH_SHARED, wide ? SHARED_2x1 : SHARED_1x1};
 }
 

@@ -78,23 +78,23 @@ BRANCHES = [
     (APART, 1, 1, "module_f16", (1, 50, 9, 7, 36, 3)),
     (SHARED, S_1X1, 1, "bits", (1, 20, 9, 7, 33, 16)),
     (SHARED, S_1X1, 1, "f32", (13, 20, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 1, "module_f16", (61, 20, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 1, "bits", (61, 20, 27, 26, 70, 9)),
+    (SHARED, S_2X1, 1, "module_f16", (61, 20, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 1, "bits", (61, 20, 27, 26, 100, 9)),
     (SHARED, S_1X1, 2, "f32", (1, 75, 9, 7, 33, 16)),
     (SHARED, S_1X1, 2, "module_f16", (13, 75, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 2, "f32", (61, 75, 27, 26, 70, 3)),
+    (SHARED, S_2X1, 2, "f32", (61, 75, 27, 26, 100, 3)),
     (SHARED, S_1X1, 3, "module_f16", (1, 140, 9, 7, 33, 16)),
     (SHARED, S_1X1, 3, "module_f32", (13, 140, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 70, 3)),
+    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 100, 3)),
     (SHARED, S_1X1, 4, "module_f32", (1, 200, 9, 7, 33, 16)),
     (SHARED, S_1X1, 4, "bits", (13, 200, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 70, 3)),
+    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 100, 3)),
     (SHARED, S_1X1, 5, "bits", (1, 260, 9, 7, 33, 16)),
     (SHARED, S_1X1, 5, "f32", (13, 260, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 5, "module_f16", (61, 260, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 5, "bits", (61, 260, 27, 26, 70, 3)),
+    (SHARED, S_2X1, 5, "module_f16", (61, 260, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 5, "bits", (61, 260, 27, 26, 100, 3)),
 ]
 
 

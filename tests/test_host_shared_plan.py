@@ -79,3 +79,19 @@ def test_measured_calls_go_to_the_faster_form(checker, kind, shared, call):
     other, mine = {"bits": (0, G.BITS), "sums": (1, G.SUMS), "half": (3, G.HALF), "float": (3, G.FLOAT)}[kind]
     (tile, _), = choices(checker, [(m, o, cw, ks, stride, other, mine, staged)])
     assert (tile != 0) == shared
+
+
+@pytest.mark.parametrize("out,form,tile,call", [
+    # pixels, channels out, words, branches; times in us of the choice and of what it was measured against
+    ("bits", G.OWN, None, (242452, 96, 3, 1)),              # 13.5, shared weights 16.4
+    ("bits", G.OWN, None, (156333, 68, 3, 1)),              # 9.6, shared weights 11.6
+    ("module_f16", G.SHARED, G.S_1X1, (184730, 81, 1, 9)),  # 51.0, 2 x 1 blocks 60.6
+    ("module_f16", G.SHARED, G.S_1X1, (139239, 85, 2, 6)),  # 33.4, 2 x 1 blocks 38.2
+    ("module_f16", G.SHARED, G.S_1X1, (22194, 142, 8, 8)),  # 17.2, 2 x 1 blocks 20.0
+    ("module_f32", G.SHARED, G.S_1X1, (286117, 416, 3, 3)), # 199, 2 x 1 blocks 258
+    ("module_f32", G.SHARED, G.S_1X1, (34983, 890, 3, 3)),  # 111, 2 x 1 blocks 134
+    ("bits", G.SHARED, G.S_2X1, (50176, 256, 8, 9)),        # 21.5, 1 x 1 blocks 24.7
+])
+def test_measured_branch_calls_go_to_the_faster_form(checker, out, form, tile, call):
+    (got, blocks, _), = choices(checker, [(*call, out.startswith("module"), out == "module_f16")], "branches")
+    assert got == form and (tile is None or blocks == tile)
