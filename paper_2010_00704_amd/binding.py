@@ -1,7 +1,9 @@
 """Binding of libbcnn.so: the C ABI of include/bcnn.h under the same names.
 
 Argument marshalling only, the hot calls' in C++ (csrc/marshal.cpp), the rest by
-ctypes.  torch supplies device memory and the stream; every step of the
+ctypes; where that extension does not load (another torch or Python than it was
+built for, no compiler), the hot calls take ctypes too, two to three microseconds
+slower each, and loading says so once.  torch supplies device memory and the stream; every step of the
 computation runs in the library's HIP kernels.  There is no CPU or PyTorch
 fallback: if the library is missing, loading raises.
 """
@@ -58,19 +60,13 @@ _marshal = None
 
 
 def lib():
-    """The loaded library.  Raises if libbcnn.so or _marshal.so has not been built."""
+    """The loaded library.  Raises if libbcnn.so has not been built."""
     global _lib, _marshal
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
                 "libbcnn.so is missing (%s): build it with `python -m paper_2010_00704_amd.build` "
                 "or __graft_entry__.build(); there is no fallback path" % LIB_PATH)
-        try:
-            from . import _marshal as marshal
-        except ImportError as e:
-            raise RuntimeError("_marshal.so is missing or does not load (%s): build it with `python -m "
-                               "paper_2010_00704_amd.build` or __graft_entry__.build(); there is no fallback path" % e) from e
-        _marshal = marshal
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         dp = ctypes.POINTER(bcnn_conv_desc)
@@ -100,15 +96,23 @@ def lib():
         for name in EXPORTS:
             if name != "bcnn_status_string":
                 getattr(L, name).restype = ctypes.c_int
-        _marshal.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS},
-                      _ptr, _desc, lambda stream: _stream(stream), torch.cuda.is_initialized, bcnn_conv_desc,
-                      ctypes.ArgumentError)
+        try:
+            from . import _marshal as marshal
+            marshal.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS},
+                         _ptr, _desc, lambda stream: _stream(stream), torch.cuda.is_initialized, bcnn_conv_desc,
+                         ctypes.ArgumentError)
+        except ImportError as e:
+            import warnings
+            warnings.warn("calls are marshalled by ctypes, some microseconds slower each: _marshal.so is missing or does not "
+                          "load (%s); build it with `python -m paper_2010_00704_amd.build`" % e, RuntimeWarning, stacklevel=2)
+            marshal = _Ctypes
+        _marshal = marshal
         _lib = L
     return _lib
 
 
 def _calls():
-    """The marshalled entry points, bound to the loaded library."""
+    """The marshalled entry points (of _marshal.so, else _Ctypes), bound to the loaded library."""
     if _lib is None:
         lib()
     return _marshal
@@ -145,6 +149,76 @@ def _desc(d):
     if isinstance(d, bcnn_conv_desc):
         return d
     return bcnn_conv_desc(*[int(v) for v in d])
+
+
+class _Ctypes:
+    """The functions of csrc/marshal.cpp by ctypes, for where that extension does not load."""
+
+    @staticmethod
+    def pack(src, dtype, outer, channels, inner, dst, stream):
+        return _lib.bcnn_pack(_ptr(src), dtype, outer, channels, inner, _ptr(dst), _stream(stream))
+
+    @staticmethod
+    def pack_bias(src, dtype, outer, channels, inner, bias, dst, stream):
+        return _lib.bcnn_pack_bias(_ptr(src), dtype, outer, channels, inner, _ptr(bias), _ptr(dst), _stream(stream))
+
+    @staticmethod
+    def pack_bias_replicated(src, dtype, outer, channels, inner, replication, bias, dst, stream):
+        return _lib.bcnn_pack_bias_replicated(_ptr(src), dtype, outer, channels, inner, int(replication), _ptr(bias), _ptr(dst),
+                                              _stream(stream))
+
+    @staticmethod
+    def avgpool_bias_sign_pack(src, real_dtype, n, h, w, channels, s, bias, pooled, x_packed, stream):
+        return _lib.bcnn_avgpool_bias_sign_pack(_ptr(src), int(real_dtype), n, h, w, channels, s, _ptr(bias), _ptr(pooled),
+                                                _ptr(x_packed), _stream(stream))
+
+    @staticmethod
+    def threshold_sign_pack(y, thr, rows, c_out, y_packed, stream):
+        return _lib.bcnn_threshold_sign_pack(_ptr(y), _ptr(thr), rows, c_out, _ptr(y_packed), _stream(stream))
+
+    @staticmethod
+    def conv2d_binary(desc, x, w, y, stream):
+        return _lib.bcnn_conv2d_binary(ctypes.byref(_desc(desc)), _ptr(x), _ptr(w), _ptr(y), _stream(stream))
+
+    @staticmethod
+    def conv2d_binary_sign_pack(desc, x, w, thr, y_packed, stream):
+        return _lib.bcnn_conv2d_binary_sign_pack(ctypes.byref(_desc(desc)), _ptr(x), _ptr(w), _ptr(thr), _ptr(y_packed),
+                                                 _stream(stream))
+
+    @staticmethod
+    def conv2d_binary_variant(desc, x, w, thr, out, variant, stream):
+        return _lib.bcnn_conv2d_binary_variant(ctypes.byref(_desc(desc)), _ptr(x), _ptr(w), _ptr(thr), _ptr(out), int(variant),
+                                               _stream(stream))
+
+    @staticmethod
+    def conv2d_binary_module(desc, x, w, bn_scale, bn_bias, identity, prelu_slope, next_bias, real_dtype, r, x_next, variant,
+                             stream, identity_channels):
+        ep = bcnn_module_epilogue(_ptr(bn_scale), _ptr(bn_bias), _ptr(identity), _ptr(prelu_slope), _ptr(next_bias),
+                                  int(real_dtype), int(identity_channels))
+        return _lib.bcnn_conv2d_binary_module(ctypes.byref(_desc(desc)), _ptr(x), _ptr(w), ctypes.byref(ep), _ptr(r),
+                                              _ptr(x_next), int(variant), _stream(stream))
+
+    @staticmethod
+    def conv2d_binary_branches(desc, branches, x, x_branch_stride, w, pad_words, pad_mode, scale, bias, z, variant, stream):
+        return _lib.bcnn_conv2d_binary_branches(ctypes.byref(_desc(desc)), int(branches), _ptr(x), int(x_branch_stride), _ptr(w),
+                                                _ptr(pad_words), int(pad_mode), _ptr(scale), _ptr(bias), _ptr(z), int(variant),
+                                                _stream(stream))
+
+    @staticmethod
+    def conv2d_binary_branches_sign_pack(desc, branches, x, x_branch_stride, w, pad_words, pad_mode, scale, bias, z_packed,
+                                         variant, stream):
+        return _lib.bcnn_conv2d_binary_branches_sign_pack(ctypes.byref(_desc(desc)), int(branches), _ptr(x), int(x_branch_stride),
+                                                          _ptr(w), _ptr(pad_words), int(pad_mode), _ptr(scale), _ptr(bias),
+                                                          _ptr(z_packed), int(variant), _stream(stream))
+
+    @staticmethod
+    def conv2d_binary_branches_module(desc, branches, x, x_branch_stride, w, pad_words, pad_mode, scale, bias, identity,
+                                      prelu_slope, next_bias, real_dtype, r, x_next, variant, stream, identity_channels):
+        ep = bcnn_module_epilogue(None, None, _ptr(identity), _ptr(prelu_slope), _ptr(next_bias), int(real_dtype),
+                                  int(identity_channels))
+        return _lib.bcnn_conv2d_binary_branches_module(ctypes.byref(_desc(desc)), int(branches), _ptr(x), int(x_branch_stride),
+                                                       _ptr(w), _ptr(pad_words), int(pad_mode), _ptr(scale), _ptr(bias),
+                                                       ctypes.byref(ep), _ptr(r), _ptr(x_next), int(variant), _stream(stream))
 
 
 def bcnn_status_string(status):

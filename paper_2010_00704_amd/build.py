@@ -30,16 +30,18 @@ def _run(cmd):
     return proc.returncode, log
 
 
-def build_marshal():
-    """Compile csrc/marshal.cpp, a Python extension on torch's C++ headers, into _marshal.so."""
+def build_marshal(path=MARSHAL_PATH, torch_version=None):
+    """Compile csrc/marshal.cpp, a Python extension on torch's C++ headers, into _marshal.so.  It loads under this Python
+    and this torch only (torch's C++ layouts differ between versions)."""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
     libs = os.path.join(root, "lib")
-    tmp = MARSHAL_PATH + ".tmp.%d" % os.getpid()
+    tmp = path + ".tmp.%d" % os.getpid()
     rc, log = _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
                     "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                    '-DBCNN_TORCH_VERSION="%s"' % (torch_version or torch.__version__),
                     "-I", os.path.join(_ROOT, "include"), "-I", sysconfig.get_paths()["include"],
                     "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
                     "-isystem", "/opt/rocm/include", os.path.join(_HERE, "csrc", "marshal.cpp"), "-o", tmp,
@@ -48,13 +50,14 @@ def build_marshal():
         if os.path.exists(tmp):
             os.remove(tmp)
         raise RuntimeError("building _marshal.so failed:\n" + log)
-    os.replace(tmp, MARSHAL_PATH)
-    return MARSHAL_PATH
+    os.replace(tmp, path)
+    return path
 
 
 def build_library(verbose=False):
     """Compile every .hip file under csrc/ (one hipcc process per file, in
-    parallel) and link them into libbcnn.so; build _marshal.so.  Always compiles."""
+    parallel) and link them into libbcnn.so; build _marshal.so (a warning where that cannot be built: the
+    binding then marshals by ctypes).  Always compiles."""
     import shutil
     import tempfile
     from concurrent.futures import ThreadPoolExecutor
@@ -69,7 +72,6 @@ def build_library(verbose=False):
         with ThreadPoolExecutor(max_workers=jobs) as pool:
             marshal = pool.submit(build_marshal)
             results = list(pool.map(lambda so: _run([HIPCC] + common + ["-c", so[0], "-o", so[1]]), zip(srcs, objs)))
-        marshal.result()
         logs = []
         for src, (rc, log) in zip(srcs, results):
             if rc != 0:
@@ -85,6 +87,13 @@ def build_library(verbose=False):
         if verbose and (logs or log.strip()):
             print("\n".join(logs + [log]))
         os.replace(tmp, LIB_PATH)
+        try:
+            marshal.result()
+        except Exception as e:                       # no host compiler, no C++ headers of torch's or Python's, ...
+            import warnings
+            if os.path.exists(MARSHAL_PATH):         # of another build
+                os.remove(MARSHAL_PATH)
+            warnings.warn("the binding marshals by ctypes, some microseconds a call slower: %s" % e, RuntimeWarning)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
     return LIB_PATH

@@ -7,7 +7,9 @@
 //
 // The rules are binding.py's, which stay the fallback for whatever is not the common case (its _ptr, _desc and _stream are
 // called for tensor subclasses, descriptors that are no bcnn_conv_desc, stream objects, and before torch has initialised the
-// device).  Nothing is kept between calls but the library's entry points and those Python objects.
+// device) and for a Python or torch that this is not built for, where it refuses to load: tensors are read by the layout
+// that torch's headers had.  Nothing is kept between calls but the library's entry points, those Python objects and
+// whether torch has initialised the device, which a forked child asks again.
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 
@@ -15,6 +17,7 @@
 
 #include <pthread.h>
 
+#include <cstdio>
 #include <cstring>
 #include <exception>
 
@@ -380,6 +383,19 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 PyMODINIT_FUNC PyInit__marshal(void)
 {
+    int major = 0, minor = 0;
+    if (std::sscanf(Py_GetVersion(), "%d.%d", &major, &minor) != 2 || major != PY_MAJOR_VERSION || minor != PY_MINOR_VERSION) {
+        PyErr_Format(PyExc_ImportError, "built for Python %d.%d", PY_MAJOR_VERSION, PY_MINOR_VERSION);
+        return nullptr;
+    }
+    PyObject* version = PyImport_ImportModule("torch.version");
+    PyObject* text = version ? PyObject_GetAttrString(version, "__version__") : nullptr;
+    const char* torch = text ? PyUnicode_AsUTF8(text) : nullptr;
+    const bool same = torch && !std::strcmp(torch, BCNN_TORCH_VERSION);
+    if (torch && !same) PyErr_Format(PyExc_ImportError, "built for torch %s, not %s", BCNN_TORCH_VERSION, torch);
+    Py_XDECREF(text);
+    Py_XDECREF(version);
+    if (!same) return nullptr;
     pthread_atfork(nullptr, nullptr, [] { device_ready = false; });
     return PyModule_Create(&module);
 }
