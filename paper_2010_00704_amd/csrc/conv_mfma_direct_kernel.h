@@ -563,16 +563,16 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                     }
                 }
             }
-        // `part` groups of a stage; the first one's inputs lie in ring[at]
-        auto walk = [&](int st, auto part, auto at) __attribute__((always_inline)) {
+        static_assert(SG == 2 || SG == 4, "the input ring's two places in turn");
+        // `part` groups of a stage; the first one's inputs lie in ring[0]
+        auto walk = [&](int st, auto part) __attribute__((always_inline)) {
             const char* from = stage + (st & 1) * STAGE;
 #pragma unroll
             for (int i = 0; i < decltype(part)::value; ++i) {
                 const int gi = st * SG + i;
-                constexpr int R = decltype(at)::value;
-                group(gi, from + i * (STEPS * CB * 1024), ring[(i + R) & 1]);
+                group(gi, from + i * (STEPS * CB * 1024), ring[i & 1]);
                 if constexpr (decltype(part)::value == SG) {
-                    fetch_x(gi + 2, ring[(i + R) & 1]);
+                    fetch_x(gi + 2, ring[i & 1]);
                     if (i == 0) {
                         put_w(st + 1, uw);
                         fetch_w(st + 2, uw);
@@ -582,29 +582,17 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
             // only LDS is shared: loads in flight stay in flight
             if constexpr (decltype(part)::value == SG) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         };
-        using C0 = std::integral_constant<int, 0>;
         using C1 = std::integral_constant<int, 1>;
         using ALL = std::integral_constant<int, SG>;
         const int n_full = n_groups / SG;
-        if constexpr (SG == 1) {
-            int st = 0;
-            for (; st + 1 < n_full; st += 2) {
-                walk(st, ALL{}, C0{});
-                walk(st + 1, ALL{}, C1{});
-            }
-            if (st < n_full) walk(st, ALL{}, C0{});
-        } else {
-            for (int st = 0; st < n_full; ++st) walk(st, ALL{}, C0{});
-        }
+        for (int st = 0; st < n_full; ++st) walk(st, ALL{});
         const int left = n_groups - n_full * SG;
-        if constexpr (SG > 1) {
-            if (left == 1) walk(n_full, C1{}, C0{});
-        }
+        if (left == 1) walk(n_full, C1{});
         if constexpr (SG == 4) {
             using C2 = std::integral_constant<int, 2>;
-            if (left == 2) walk(n_full, C2{}, C0{});
+            if (left == 2) walk(n_full, C2{});
             if (left == 3) {
-                walk(n_full, C2{}, C0{});
+                walk(n_full, C2{});
                 fetch_x(n_full * SG + 2, ring[0]);
                 group(n_full * SG + 2, stage + (n_full & 1) * STAGE + 2 * (STEPS * CB * 1024), ring[0]);
             }
@@ -731,6 +719,8 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
                     for (int r = 0; r < 16; ++r) { tot[cb][pb][r] = b[r]; acc[cb][pb][r] = start; }
             }
             __syncthreads();
+            // (the groups' walk although this form is chosen for single words, one group a tap: without it the compiler takes four to ten
+            // registers more, and a float tail's 106 instead of 96 leave a wave less on every SIMD: up to 14 % slower)
             for (int tap = 0; tap < a.taps; ++tap) {
                 for (int g = 0; g < per_tap; ++g) {
                     const bool more = g + 1 < per_tap;
