@@ -3,6 +3,7 @@
 // with them.
 #pragma once
 #include <initializer_list>
+#include <limits.h>
 #include <stdint.h>
 
 #include "direct_plan.h"
@@ -49,29 +50,42 @@ inline double shared_cost(const SharedCost& c, int cb, int pb, int m, int c_out,
     return c.fixed + c.step * steps + (c.wg + c.wg_step * steps) * wgs;
 }
 
+// Words a tap up to which this form is taken from the staged kernel and from the tiles that split K (us, other and this):
+//   - 32 under a 3x3 filter, and under stride 2 against the staged kernel, where the fits end: 673 of 916 calls of 33 to 48 words were
+//     behind, 9 % on average (half module, 1152 -> 512, stride 2, 32 585 pixels 83 and 130; sums, 1083 -> 800, 14 maps of 28 x 28
+//     49 and 63; bits, 1x1, 1152 -> 896, stride 2, 16 611 pixels 11.5 and 16.5)
+//   - fewer under stride 2, where no two rows share their taps' lines (half module, 562 -> 268, 9016 pixels 14.8 and 16.9; bits of 24
+//     and 28 words 0.87 times the staged kernel)
+//   - fewer where c_out fills the staged kernel's 128-channel tiles: half modules of 24 and 28 words 1.05
+//     times that kernel on average, but 32 of 119 behind by up to 15 %, of 32 words 0.98, and under stride 2 of 24 and 28 0.95; sums of 16 and
+//     20 words 0.95; all of them ahead below (1.1 to 1.2)
+inline int shared_words(int c_out, int ks, int stride, int kind, int other)
+{
+    if (ks == 1) return other == DIRECT_NONE && stride > 1 ? 32 : INT_MAX;
+    if (other != DIRECT_NONE) return stride > 1 && kind != SHARED_BITS ? 16 : 32;
+    if (kind == SHARED_BITS) return stride > 1 ? 20 : 32;
+    if (c_out % 128 != 0 || kind == SHARED_FLOAT) return 32;
+    return kind == SHARED_SUMS ? 12 : 20;
+}
+
 // The tile, or SHARED_NONE where `other` is estimated to be as good.  Against the tiles that do not split K this form may be
 // estimated a tenth behind: their estimates are that much too low on the calls that this one is ahead on.  Not so for sums,
 // which their stores bind, and for modules whose taps are whole 16-byte units (a multiple of four words), which those tiles walk without masks
 // (us, other and this: half module, 3x3, 110 -> 88, 73 maps of 41 x 41 20.8 and 23.0; 117 -> 224, 25 maps of 39 x 39 17.6 and 19.5;
 // of 265 such calls 88 were more than 3 % behind, 1 is).
-// Beyond 32 words a tap, where the fits end, a 3x3 filter stays on the tiles that split K: this form falls behind its estimate
-// there (half module, 1032 -> 61, 97 maps of 41 x 41 70 and 78; sums, 1083 -> 800, 14 maps of 28 x 28 49 and 63; 117 of 132 calls
-// of 33 to 48 words behind or level, 11 % on average; up to 32 words 4 to 17 % ahead).  Under stride 2, where no two rows share their
-// taps' lines, so do sums and modules from 17 words on (half module, 562 -> 268, 9016 pixels 14.8 and 16.9; sums, 672 -> 544, 15 680 pixels
-// 35 and 42; 62 calls of 17 to 32 words 1 % ahead on average, 14 of them more than 3 % behind; bits 8 to 19 % ahead).
-// Over 3000 calls that the estimates without the last two rules give to this form: bits 1.29 times the other choice on average,
-// sums 1.26, half modules 1.12, float ones 1.13; 21 of them more than 5 % behind it, 13 % at worst (sums, 3x3, 32 -> 1007,
-// 80 556 pixels 76 and 87: what is left of the estimates' error).  (us, other and this: bits, 3x3, 320 -> 192, 39 maps of 38 x 38
+// Over 3000 calls that the estimates without this rule and that of shared_words() give to this form: bits 1.29 times the other choice on average,
+// sums 1.26, half modules 1.12, float ones 1.13; 16 of them more than 5 % behind it, 13 % at worst (sums, 3x3, 32 -> 1007,
+// 80 556 pixels 76 and 87), and 61 of 3500 more that the staged kernel covers, 14 % at worst (what is left of the estimates' errors).  (us, other and this: bits, 3x3, 320 -> 192, 39 maps of 38 x 38
 // 27.9 and 16.3; 64 -> 64, 156 maps of 25 x 28 9.8 and 6.9; 1x1, 704 -> 704, 40 maps of 26 x 26 14.9 and 10.8; sums, 3x3, 468 -> 39,
 // 191 maps of 37 x 36 52 and 38.)
 inline int shared_choose(int m, int c_out, int cw, int ks, int stride, int kind, const DirectChoice& other)
 {
     // sums of a 1x1 filter are bound by their store, which the other tiles keep busier (64 -> 672, 46 maps of 51 x 29 30.7 and 33.9)
     if (kind == SHARED_SUMS && ks == 1) return SHARED_NONE;
-    const bool split_k = other.tile == DIRECT_1x1_K4 || other.tile == DIRECT_2x2_K4;
-    if (split_k && ks == 3 && cw > (stride > 1 && kind != SHARED_BITS ? 16 : 32)) return SHARED_NONE;
+    const bool whole_k = other.tile == DIRECT_2x1 || other.tile == DIRECT_1x1;
+    if (!whole_k && cw > shared_words(c_out, ks, stride, kind, other.tile)) return SHARED_NONE;
     const int taps = ks * ks, steps = SharedWalk::make(cw, taps).steps(taps);
-    const bool too_low = (other.tile == DIRECT_2x1 || other.tile == DIRECT_1x1) && (kind == SHARED_BITS || (kind != SHARED_SUMS && cw % 4 != 0));
+    const bool too_low = whole_k && (kind == SHARED_BITS || (kind != SHARED_SUMS && cw % 4 != 0));
     double least = other.cost * (too_low ? 1.1 : 1.0);
     int best = SHARED_NONE;
     for (const SharedTile& t : SHARED_TILES) {

@@ -71,7 +71,11 @@ def test_every_branch_form_is_reached_on_the_gpu(checker):
     ("half", True, (41067, 576, 8, 3, 1, 1)),           # 59.2, 44.1
     ("half", True, (83000, 96, 16, 3, 2, 1)),           # 41.0, 31.3
     ("float", True, (83655, 96, 24, 3, 1, 1)),           # 52.1, 38.7
-    ("sums", True, (182979, 64, 40, 3, 1, 1)),           # 98.2, 71.3
+    ("sums", True, (84672, 315, 8, 3, 1, 1)),           # 152, 34.8
+    ("half", False, (50176, 256, 32, 3, 1, 1)),           # 63.0, 66.8
+    ("half", False, (32585, 512, 36, 3, 2, 1)),           # 82.8, 130
+    ("half", False, (47040, 256, 36, 3, 2, 1)),           # 68.3, 97.2
+    ("bits", False, (16611, 896, 36, 1, 2, 1)),           # 11.5, 16.5
     ("bits", True, (56316, 192, 10, 3, 1, 0)),           # 27.9, 16.3
 ])
 def test_measured_calls_go_to_the_faster_form(checker, kind, shared, call):
