@@ -80,7 +80,6 @@ inline DirectChoice direct_estimate(int m, int c_out, int cw, int ks, int kind, 
     }
     return DirectChoice{best, best == DIRECT_NONE ? rival : least};
 }
-inline int direct_choose(int m, int c_out, int cw, int ks, int kind, bool staged) { return direct_estimate(m, c_out, cw, ks, kind, staged).tile; }
 
 // Branch mode: estimated time of a tile as above, with a wave's chain of groups of four K-steps in place of chunks.
 // Fits over 74 calls; rms error 14 to 19 %, the choice 1 to 2 % over the best tile on average, 24 % at worst.

@@ -1,7 +1,7 @@
 // Host-only check of the plan of the direct kernel's form with shared weights (csrc/shared_plan.h).  Without arguments: walks
 // the words of a tap for every word count and prints "mismatches: N", exit status 0 = none.  With an argument: reads calls
 // from standard input, one a line (m c_out cw ks stride kind kind staged, kind as in direct_plan.h and, for this form, as in
-// shared_plan.h), prints the tile and the words per load of each; with "branches": m c_out cw branches tail half, prints form,
+// shared_plan.h), prints the tile and the words per load of each, and the tile and the K walk of the other choice; with "branches": m c_out cw branches tail half, prints form,
 // tile and words per load.
 #include "shared_plan.h"
 
@@ -23,8 +23,10 @@ int main(int argc, char** argv)
     }
     if (argc > 1) {
         int m, c_out, cw, ks, stride, kind, mine, staged;
-        while (scanf("%d %d %d %d %d %d %d %d", &m, &c_out, &cw, &ks, &stride, &kind, &mine, &staged) == 8)
-            printf("%d %d\n", shared_choose(m, c_out, cw, ks, stride, mine, direct_estimate(m, c_out, cw, ks, kind, staged != 0)), SharedWalk::make(cw, ks * ks).wide);
+        while (scanf("%d %d %d %d %d %d %d %d", &m, &c_out, &cw, &ks, &stride, &kind, &mine, &staged) == 8) {
+            const DirectChoice other = direct_estimate(m, c_out, cw, ks, kind, staged != 0);
+            printf("%d %d %d %d\n", shared_choose(m, c_out, cw, ks, stride, mine, other), SharedWalk::make(cw, ks * ks).wide, other.tile, direct_mode(cw));
+        }
         return 0;
     }
     long bad = 0;

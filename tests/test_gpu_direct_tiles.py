@@ -1,7 +1,8 @@
-"""Every tile of the direct matrix-core kernel with every walk of K that AUTO reaches, for each kind of output, against the
-vector-ALU kernels (which the other tests hold against the oracle).  Operands lie a word past an allocation's start, so
-that the staged kernel covers none of these calls; pixels and channels are ragged.  Which tile a call takes is checked on
-the host, from the same lists, by test_host_direct_plan.py."""
+"""Every tile of the direct matrix-core kernel with every walk of K that AUTO reaches, for each kind of output, and padded branch
+calls of every output, against the vector-ALU kernels (which the other tests hold against the oracle).  Operands lie a word past
+an allocation's start, so that the staged kernel covers none of these calls; pixels and channels are ragged.  Which tile a plain
+call takes is checked on the host, from the same list, by test_host_direct_plan.py; the forms of branch calls and their
+tiles are test_gpu_shared_weights.py's."""
 import pytest
 import torch
 
@@ -10,38 +11,60 @@ from gpu_helpers import gpu_device
 
 pytestmark = pytest.mark.gpu
 
-K4_1X1, K4_2X2, T_2X1, T_1X1, T_2X2 = 1, 2, 3, 4, 5     # tiles: csrc/direct_plan.h
+K4_1X1, K4_2X2, T_2X1, T_1X1 = 1, 2, 3, 4               # tiles: csrc/direct_plan.h
 UNITS, TAIL, WORDS = 0, 1, 2                            # walks of K
-BITS, SUMS, MODULE = 0, 1, 3
+BITS, SUMS, HALF, FLOAT = 0, 1, 2, 3
 
 CONVS = [
     # kind, tile, walk, (n, c_in, h, w, c_out, filter)
-    (BITS, K4_1X1, UNITS, (1, 120, 5, 7, 33, 1)), (BITS, K4_1X1, TAIL, (1, 150, 5, 7, 33, 1)),
-    (BITS, K4_1X1, WORDS, (1, 20, 5, 7, 33, 3)), (BITS, K4_2X2, UNITS, (33, 380, 28, 28, 33, 3)),
-    (BITS, K4_2X2, TAIL, (33, 270, 28, 28, 33, 3)), (BITS, T_2X1, UNITS, (97, 125, 28, 28, 33, 1)),
-    (BITS, T_2X1, TAIL, (97, 150, 28, 28, 33, 1)), (BITS, T_2X1, WORDS, (97, 30, 28, 28, 33, 1)),
-    (BITS, T_1X1, UNITS, (9, 125, 27, 27, 33, 1)), (BITS, T_1X1, TAIL, (9, 150, 27, 27, 33, 1)),
-    (BITS, T_1X1, WORDS, (9, 30, 27, 27, 33, 1)),
-    (SUMS, K4_1X1, UNITS, (1, 120, 5, 7, 33, 1)), (SUMS, K4_1X1, TAIL, (1, 150, 5, 7, 34, 1)),
-    (SUMS, K4_1X1, WORDS, (1, 20, 5, 7, 35, 3)), (SUMS, K4_2X2, UNITS, (49, 380, 28, 28, 33, 3)),
-    (SUMS, K4_2X2, TAIL, (49, 270, 28, 28, 36, 3)), (SUMS, T_2X1, UNITS, (97, 630, 28, 28, 33, 1)),
-    (SUMS, T_2X1, TAIL, (129, 270, 28, 28, 34, 1)), (SUMS, T_2X1, WORDS, (97, 50, 28, 28, 33, 3)),
-    (SUMS, T_1X1, UNITS, (5, 125, 26, 27, 130, 1)), (SUMS, T_1X1, TAIL, (5, 150, 26, 27, 131, 1)),
+    (BITS, K4_1X1, UNITS, (1, 120, 5, 7, 33, 1)),
+    (BITS, K4_1X1, TAIL, (1, 150, 5, 7, 33, 1)),
+    (BITS, K4_1X1, WORDS, (1, 20, 5, 7, 33, 3)),
+    (BITS, K4_2X2, UNITS, (33, 380, 28, 28, 33, 3)),
+    (BITS, K4_2X2, TAIL, (33, 410, 28, 28, 33, 3)),
+    (BITS, T_1X1, UNITS, (9, 125, 27, 27, 33, 1)),
+    (BITS, T_1X1, TAIL, (9, 150, 27, 27, 33, 1)),
+    (BITS, T_1X1, WORDS, (9, 90, 27, 27, 33, 1)),
+    (SUMS, K4_1X1, UNITS, (1, 120, 5, 7, 33, 1)),
+    (SUMS, K4_1X1, TAIL, (1, 150, 5, 7, 34, 1)),
+    (SUMS, K4_1X1, WORDS, (1, 20, 5, 7, 35, 3)),
+    (SUMS, K4_2X2, UNITS, (49, 380, 28, 28, 33, 3)),
+    (SUMS, K4_2X2, TAIL, (49, 270, 28, 28, 36, 3)),
+    (SUMS, T_2X1, UNITS, (97, 630, 28, 28, 33, 1)),
+    (SUMS, T_2X1, TAIL, (129, 270, 28, 28, 34, 1)),
+    (SUMS, T_2X1, WORDS, (97, 50, 28, 28, 33, 3)),
+    (SUMS, T_1X1, UNITS, (5, 125, 26, 27, 130, 1)),
+    (SUMS, T_1X1, TAIL, (5, 150, 26, 27, 131, 1)),
     (SUMS, T_1X1, WORDS, (5, 30, 26, 27, 130, 1)),
-    (MODULE, K4_1X1, UNITS, (1, 380, 5, 7, 36, 1)), (MODULE, K4_1X1, TAIL, (1, 270, 5, 7, 33, 1)),
-    (MODULE, K4_1X1, WORDS, (1, 20, 5, 7, 36, 3)), (MODULE, K4_2X2, UNITS, (33, 500, 28, 28, 36, 3)),
-    (MODULE, K4_2X2, TAIL, (33, 410, 28, 28, 33, 3)), (MODULE, T_2X1, UNITS, (129, 125, 28, 28, 36, 3)),
-    (MODULE, T_2X1, TAIL, (97, 150, 28, 28, 33, 3)), (MODULE, T_2X1, WORDS, (97, 50, 28, 28, 100, 3)),
-    (MODULE, T_1X1, UNITS, (49, 380, 28, 28, 36, 1)), (MODULE, T_1X1, TAIL, (49, 270, 28, 28, 33, 1)),
-    (MODULE, T_1X1, WORDS, (49, 20, 28, 28, 36, 3)),
+    (HALF, K4_1X1, UNITS, (1, 380, 5, 7, 36, 1)),
+    (HALF, K4_1X1, TAIL, (1, 270, 5, 7, 33, 1)),
+    (HALF, K4_1X1, WORDS, (1, 20, 5, 7, 36, 3)),
+    (HALF, K4_2X2, UNITS, (33, 500, 28, 28, 36, 3)),
+    (HALF, K4_2X2, TAIL, (33, 410, 28, 28, 33, 3)),
+    (HALF, T_2X1, UNITS, (129, 125, 28, 28, 36, 3)),
+    (HALF, T_2X1, TAIL, (275, 270, 28, 28, 33, 1)),
+    (HALF, T_2X1, WORDS, (275, 20, 28, 28, 33, 3)),
+    (HALF, T_1X1, UNITS, (49, 380, 28, 28, 36, 1)),
+    (HALF, T_1X1, TAIL, (49, 270, 28, 28, 33, 1)),
+    (HALF, T_1X1, WORDS, (49, 20, 28, 28, 36, 3)),
+    (FLOAT, K4_1X1, UNITS, (1, 380, 5, 7, 36, 1)),
+    (FLOAT, K4_1X1, TAIL, (1, 270, 5, 7, 33, 1)),
+    (FLOAT, K4_1X1, WORDS, (1, 20, 5, 7, 36, 3)),
+    (FLOAT, K4_2X2, UNITS, (33, 500, 28, 28, 36, 3)),
+    (FLOAT, K4_2X2, TAIL, (33, 410, 28, 28, 33, 3)),
+    (FLOAT, T_2X1, UNITS, (129, 125, 28, 28, 36, 3)),
+    (FLOAT, T_2X1, TAIL, (275, 270, 28, 28, 33, 1)),
+    (FLOAT, T_2X1, WORDS, (97, 50, 28, 28, 100, 3)),
+    (FLOAT, T_1X1, UNITS, (49, 380, 28, 28, 36, 1)),
+    (FLOAT, T_1X1, TAIL, (49, 270, 28, 28, 33, 1)),
+    (FLOAT, T_1X1, WORDS, (49, 20, 28, 28, 36, 3)),
 ]
-OUTS = ["bits", "f32", "module_f32", "module_f16"]
 BRANCHES = [
-    # output, tile, (n, c_in, h, w, c_out, branches): nine taps of a 3x3 filter, or parallel ones
-    (out, tile, (n, c, 28, 28, 100 if n > 9 else 36, 9))
+    # output, (n, c_in, h, w, c_out, branches): nine taps of a 3x3 filter, or parallel ones
+    (out, (n, c, 28, 28, 100 if n > 9 else 36, 9))
     for c in (30, 220, 288)             # one word, seven (single words only), nine (a group and a single word)
-    for out, tile, n in [(o, T_1X1, 9) for o in OUTS] + [("bits", T_2X2, 97), ("f32", T_2X2, 97), ("module_f32", T_2X1, 97), ("module_f16", T_2X2, 97)]
-] + [("module_f16", T_2X1, (64, 1010, 28, 28, 100, 16))]
+    for n in (9, 97) for out in ("bits", "f32", "module_f32", "module_f16")
+] + [("module_f16", (64, 1010, 28, 28, 100, 16))]
 
 
 class Draw:
@@ -91,7 +114,7 @@ def test_tile(kind, tile, walk, shape):
         both(lambda out, v: B.bcnn_conv2d_binary_variant(desc, x, wt, None, out[0], v), [((m, o), torch.int32)])
     else:
         g, b, slope, nxt = d.real((o,), 4 / total ** 0.5), d.real((o,), 3.0), d.real((o,), 1.0), d.real((o,), 5.0)
-        for dtype, code in ((torch.float32, B.BCNN_F32), (torch.float16, B.BCNN_F16), (torch.bfloat16, B.BCNN_BF16)):
+        for dtype, code in [(torch.float32, B.BCNN_F32)] if kind == FLOAT else [(torch.float16, B.BCNN_F16), (torch.bfloat16, B.BCNN_BF16)]:
             ident = d.real((m, o), 30.0).to(dtype)
             both(lambda out, v: B.bcnn_conv2d_binary_module(desc, x, wt, g, b, ident, slope, nxt, code, out[0], out[1], v),
                  [((m, o), dtype), ((m, words), torch.int32)])
@@ -99,8 +122,8 @@ def test_tile(kind, tile, walk, shape):
 
 
 @pytest.mark.parametrize("pad_mode", ["minus", "words", "zero"])
-@pytest.mark.parametrize("out,tile,shape", BRANCHES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
-def test_branch_tile(out, tile, shape, pad_mode):
+@pytest.mark.parametrize("out,shape", BRANCHES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_padded_branches(out, shape, pad_mode):
     gpu_device()
     n, c, h, w, o, taps = shape
     k = 3 if taps == 9 else 1

@@ -1,5 +1,5 @@
 """The direct kernel's form whose workgroups share expanded weights: every tile and width of its loads, for each kind of
-output, and in branch mode also the form whose waves take whole taps, against the vector-ALU kernels (which the other tests hold against the oracle).  Pixels, channels and words are
+output, and in branch mode also the forms whose waves take whole taps or their own operands, against the vector-ALU kernels (which the other tests hold against the oracle).  Pixels, channels and words are
 ragged; operands lie a word past an allocation's start, so that the staged kernel covers none of these calls (but ALIGNED).  Which tile and
 width a call takes is checked on the host, from the same list, by test_host_shared_plan.py."""
 import pytest
@@ -67,6 +67,8 @@ ALIGNED = [
 ]
 
 OWN, APART, SHARED = 0, 1, 2                           # branch forms; tile 1 of APART: four waves a block
+T_2X1, T_1X1, T_2X2 = 3, 4, 5                          # tiles of OWN: csrc/direct_plan.h
+OUTS = ["bits", "f32", "module_f32", "module_f16"]
 BRANCHES = [
     # form, tile, words per load, output, (n, c_in, h, w, c_out, branches): nine taps of a 3x3 filter, or parallel ones
     (APART, 1, 1, "bits", (1, 20, 9, 7, 33, 9)),
@@ -76,26 +78,30 @@ BRANCHES = [
     (APART, 1, 4, "bits", (1, 420, 9, 7, 33, 9)),
     (APART, 1, 5, "f32", (1, 260, 9, 7, 33, 3)),
     (APART, 1, 1, "module_f16", (1, 50, 9, 7, 36, 3)),
+    (OWN, T_2X1, 1, "module_f32", (209, 50, 27, 27, 100, 3)),
+    (OWN, T_2X1, 2, "module_f32", (209, 75, 27, 27, 100, 1)),
+    (OWN, T_2X1, 1, "module_f16", (19, 20, 27, 27, 1000, 1)),
+    (OWN, T_2X2, 1, "bits", (209, 20, 27, 27, 33, 8)),
+    (OWN, T_2X2, 1, "f32", (209, 20, 27, 27, 36, 8)),
+    (OWN, T_2X2, 1, "module_f16", (209, 50, 27, 27, 100, 3)),
+    (OWN, T_2X2, 2, "module_f16", (209, 110, 27, 27, 100, 1)),
     (SHARED, S_1X1, 1, "bits", (1, 20, 9, 7, 33, 16)),
-    (SHARED, S_1X1, 1, "f32", (13, 20, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 1, "module_f16", (61, 20, 27, 26, 100, 9)),
-    (SHARED, S_2X1, 1, "bits", (61, 20, 27, 26, 100, 9)),
     (SHARED, S_1X1, 2, "f32", (1, 75, 9, 7, 33, 16)),
-    (SHARED, S_1X1, 2, "module_f16", (13, 75, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 2, "f32", (61, 75, 27, 26, 100, 3)),
     (SHARED, S_1X1, 3, "module_f16", (1, 140, 9, 7, 33, 16)),
-    (SHARED, S_1X1, 3, "module_f32", (13, 140, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 100, 9)),
-    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 100, 3)),
     (SHARED, S_1X1, 4, "module_f32", (1, 200, 9, 7, 33, 16)),
-    (SHARED, S_1X1, 4, "bits", (13, 200, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 100, 9)),
-    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 100, 3)),
     (SHARED, S_1X1, 5, "bits", (1, 260, 9, 7, 33, 16)),
-    (SHARED, S_1X1, 5, "f32", (13, 260, 27, 26, 70, 9)),
-    (SHARED, S_2X1, 5, "module_f16", (61, 260, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 2, "f32", (61, 75, 27, 26, 100, 3)),
+    (SHARED, S_2X1, 3, "bits", (61, 140, 27, 26, 100, 3)),
+    (SHARED, S_2X1, 4, "f32", (61, 200, 27, 26, 100, 3)),
     (SHARED, S_2X1, 5, "bits", (61, 260, 27, 26, 100, 3)),
+    (SHARED, S_2X1, 3, "module_f32", (133, 140, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 4, "module_f32", (133, 200, 27, 26, 100, 9)),
+    (SHARED, S_2X1, 5, "module_f32", (101, 260, 27, 26, 100, 9)),
 ]
+BRANCHES += [(OWN, T_1X1, wide, out, (19, c, 27, 27, 33, taps)) for wide, c, taps in ((1, 20, 3), (1, 50, 2), (2, 75, 1), (2, 110, 1)) for out in OUTS]
+BRANCHES += [(SHARED, S_1X1, wide, out, (13, c, 27, 26, 70, 9)) for wide, c in ((1, 20), (2, 75), (3, 140), (4, 200), (5, 260)) for out in OUTS]
+BRANCHES += [(SHARED, S_2X1, wide, out, (61, c, 27, 26, 100, 9)) for wide, c in ((1, 50), (2, 110), (3, 170), (4, 230), (5, 290))
+             for out in ("bits", "f32", "module_f16")]
 
 
 @pytest.mark.parametrize("kind,tile,wide,shape", CONVS + ALIGNED, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
@@ -136,7 +142,7 @@ def test_branch_form(form, tile, wide, out, shape, pad_mode):
     n, c, h, w, o, taps = shape
     k = 3 if taps == 9 else 1
     d = Draw(84000 + 17 * c + n)
-    own = taps == 3                                     # parallel branches of their own tensors, or of one
+    own = taps in (1, 3)                                # parallel branches of their own tensors, or of one
     (x, _, keep_x), (wt, _, keep_w), (pad, _, keep_p) = d.packed(n * (taps if own else 1), c, h, w), d.packed(o, c, taps), d.packed(taps, c, 1)
     desc = B.conv_desc(n, c, h, w, o, k, 1, k // 2)
     m, words = n * h * w, (o + 31) // 32

@@ -24,6 +24,7 @@ def test_every_word_is_walked_once(checker):
 
 
 def choices(checker, calls, mode="calls"):
+    """Per call: tile and words per load (0: another kernel) and the other choice's tile and walk; of branches: form, tile, words per load."""
     lines = "\n".join(" ".join(str(int(v)) for v in c) for c in calls)
     out = subprocess.run([checker, mode], input=lines, stdout=subprocess.PIPE, text=True, timeout=300, check=True)
     return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
@@ -36,25 +37,30 @@ def call(kind, n, c, h, w, o, k, stride, staged=0):
 
 def test_every_tile_and_width_is_reached_on_the_gpu(checker):
     got = choices(checker, [call(kind, *shape) for kind, _, _, shape in G.CONVS] + [call(kind, *shape, staged=1) for kind, _, _, shape in G.ALIGNED])
-    assert got == [(tile, wide) for _, tile, wide, _ in G.CONVS + G.ALIGNED]
+    assert [g[:2] for g in got] == [(tile, wide) for _, tile, wide, _ in G.CONVS + G.ALIGNED]
     grid = [(m, o, cw, ks, stride, kind if kind < 2 else 3, kind, 0) for m in (196, 784, 3136, 12544, 50176, 200704) for o in (16, 64, 100, 256, 512)
             for cw in (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 16, 18, 32) for ks in (1, 3) for stride in (1, 2) for kind in (G.BITS, G.SUMS, G.HALF, G.FLOAT)]
     grid += [(m, o, cw, ks, stride, kind if kind < 2 else 2 if o % 128 == 0 else 3, kind, 1) for m, o, cw, ks, stride, _, kind, _ in grid if cw % 4 == 0]
     listed = {(kind, tile, wide) for kind, tile, wide, _ in G.CONVS + G.ALIGNED}
-    reached = {(c[6], tile, wide) for c, (tile, wide) in zip(grid, choices(checker, grid)) if tile}
+    reached = {(c[6], tile, wide) for c, (tile, wide, _, _) in zip(grid, choices(checker, grid)) if tile}
     assert reached <= listed, sorted(reached - listed)
 
 
 def test_every_branch_form_is_reached_on_the_gpu(checker):
+    """Per kind of output, each a kernel of its own: every form, tile and, on shared weights, width of loads."""
     def tail(out):
         return out.startswith("module"), out == "module_f16"
 
+    def kernel(form, tile, wide, out):
+        return form, tile, wide if form == G.SHARED else 0, out
+
     calls = [(n * h * w, o, (c + 31) // 32, taps, *tail(out)) for _, _, _, out, (n, c, h, w, o, taps) in G.BRANCHES]
     assert choices(checker, calls, "branches") == [(form, tile, wide) for form, tile, wide, _, _ in G.BRANCHES]
-    grid = [(m, o, cw, p, *tail(out)) for m in (49, 784, 12544, 50176, 200704) for o in (32, 100, 256, 512) for cw in (1, 3, 5, 8, 9, 16, 32)
-            for p in (2, 3, 9, 16) for out in ("bits", "f32", "module_f32", "module_f16")]
-    listed = {(form, tile, wide) for form, tile, wide, _, _ in G.BRANCHES if form == G.SHARED}
-    assert {c for c in choices(checker, grid, "branches") if c[0] == G.SHARED} <= listed
+    grid = [(out, (m, o, cw, p, *tail(out))) for m in (49, 784, 12544, 50176, 200704) for o in (32, 100, 256, 512, 1000)
+            for cw in (1, 2, 3, 4, 5, 8, 9, 16, 32) for p in (1, 2, 3, 8, 9, 16) for out in G.OUTS]
+    got = choices(checker, [c for _, c in grid], "branches")
+    reached, listed = {kernel(*g, out) for (out, _), g in zip(grid, got)}, {kernel(*row[:4]) for row in G.BRANCHES}
+    assert reached <= listed, sorted(reached - listed)
 
 
 @pytest.mark.parametrize("kind,shared,call", [
@@ -81,7 +87,7 @@ def test_every_branch_form_is_reached_on_the_gpu(checker):
 def test_measured_calls_go_to_the_faster_form(checker, kind, shared, call):
     m, o, cw, ks, stride, staged = call
     other, mine = {"bits": (0, G.BITS), "sums": (1, G.SUMS), "half": (3, G.HALF), "float": (3, G.FLOAT)}[kind]
-    (tile, _), = choices(checker, [(m, o, cw, ks, stride, other, mine, staged)])
+    (tile, *_), = choices(checker, [(m, o, cw, ks, stride, other, mine, staged)])
     assert (tile != 0) == shared
 
 
