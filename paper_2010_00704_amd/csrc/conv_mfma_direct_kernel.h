@@ -384,9 +384,11 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
             } else v[at] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, off, 0, 0);
         };
         // Pad words are a second load, added when the group is multiplied: added where it is fetched it waits for both loads.  A
-        // module's tail has no registers for that: a wave less on every SIMD costs more than the wait (64 -> 64, 80 maps of 39 x 39,
-        // half 18.0 us and 19.3 added later; 200 -> 200, 20 maps of 27 x 27, float 17.0 and 18.3).
-        constexpr bool PAD_LATER = PAD == PAD_OPERAND && !MODULE;
+        // module's tail of 2 x 1 blocks, and a float one of two or four words, have no registers for that: a wave less on every SIMD can
+        // cost more than the wait (64 -> 64, 80 maps of 39 x 39, half 18.0 us and 19.3 added later; 200 -> 200, 20 maps of 27 x 27, float
+        // 17.0 and 18.3).  The other tails of 1 x 1 blocks: one word a load 1.12 times faster over 480 calls, half ones of two words 1.10, the
+        // rest level; before, 27 of those 480 were up to 12 % slower than with a wave's own operands, one is.
+        constexpr bool PAD_LATER = PAD == PAD_OPERAND && (!MODULE || (CB == 1 && !(REAL == REAL_F32 && WIDE % 2 == 0)));
         struct Inputs { int x[PB][STEPS], pad[PAD_LATER ? PB : 1][STEPS]; };
         auto fetch_x = [&](int gi, Inputs& c) __attribute__((always_inline)) {
 #pragma unroll

@@ -110,9 +110,9 @@ inline int shared_choose(int m, int c_out, int cw, int ks, int stride, int kind,
 //     96 x 3 -> 416, 286 117 pixels 199 with 1 x 1 blocks, 258 with 2 x 1) and where their second block does not idle too often: not for one or
 //     three blocks of 32 channels, and five under a half tail (32 x 9 -> 81, 184 730 pixels, half tail 60.6, with 1 x 1 blocks 51)
 // Together 1.33 to 1.40 times the second form alone over 700 calls of all kinds (32 to 1024 channels, 50 to 200 000 pixels, 2 to 9
-// branches).  Of 3000 more calls above three blocks a compute unit, 14 are more than 5 % behind
-// the second form, 10 % at worst (most of them tails of nine taps of one or two words with pad words: 64 x 9 -> 85, 53 792 pixels, float 21.1 and
-// 23.6); 35 were before single branches, narrow taps and idle blocks had their rules, 24 % at worst.
+// branches).  Of 3000 more calls above three blocks a compute unit, 14 are more than 5 % behind the second form, 10 % at worst (most of
+// them tails of nine narrow taps with pad words, which have been faster since); 35 were before single branches, narrow taps and idle
+// blocks had their rules, 24 % at worst.
 enum { BRANCH_OWN = 0, BRANCH_APART, BRANCH_SHARED };
 constexpr int APART_TAPS = 9;                                // sums of taps that fit LDS
 struct BranchChoice { int form, tile; };
