@@ -43,10 +43,11 @@
 // take whole taps of a block and scale and add their sums in order at the end (a wave's chain is a quarter as long).  With
 // shared weights the pixels are the instruction's rows, so that a tap's scale is one register a block: 16-byte scale reads
 // took as much LDS time as the weights (24.7 us against 26.7 on the first call below), and zeros as an inline start
-// operand replace a move per element and tap.  Measured, us: 3x3, 256 -> 256, 64 maps of 28 x 28, pad words, bits: 64 in the
-// staged kernel, 33.7 every wave for itself, 22.9 shared, 21.5 since pad words are added behind the loads' wait (20.7 without them); 160 -> 160, 49 maps of
-// 41 x 41, float 44.6 and 24.8; 64 -> 64, 213 maps of 39 x 42, half tail 57 and 39; 384 -> 384, 2 maps of 13 x 13, bits 12.9 and, taps
-// apart, 6.6 (in a graph 6.0, and 5.1 with the pad words behind the wait).  2 x 2 blocks a wave (two waves per SIMD) 28.8 on the first of these, 1 x 2 36.8.
+// operand replace a move per element and tap.  Measured in graphs, us: 3x3, 256 -> 256, 64 maps of 28 x 28, bits, pad words 34.9 every
+// wave for itself and 23.4 shared (a pass 33.6 and 22.2 to 23.4, by box; the staged kernel 64), -1 outside 30.7 and 22.9, nothing
+// outside 33.4 and 24.7; 512 -> 512, 10 maps of 14 x 14 12.3 and 9.4; 160 -> 160, 49 maps of 41 x 41, float 44.6 and 24.8; 64 -> 64, 213 maps of
+// 39 x 42, half tail 57 and 39; 384 -> 384, 2 maps of 13 x 13, bits 13.2 and, taps apart, 5.4.  Counters of the first of these: vector units
+// busy for 40 % of the time, matrix cores 19, LDS 24; its 1568 workgroups are one and a half rounds of four a compute unit.  2 x 2 blocks a wave (two waves per SIMD) 28.8 on the first of these, 1 x 2 36.8.
 #pragma once
 #include "bcnn_common.h"
 #include "branch_walk.h"
@@ -623,9 +624,9 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
         // A tap's words are split between the lane halves and walked in groups of four words = four K-steps with one
         // 16-byte load per row; the last group is single words (branch_walk.h).  Every load is wave-uniform but for the
         // rows' offsets and their validity.
-        // The accumulators start a tap at minus the positions that are zero on both sides, so that the tap's sum
-        // needs no correction: a completed tap costs one fma per element, tot = fma(scale, y_t, tot) in the order
-        // t = 0, 1, ... (the chain is part of the interface), and one move to restart.
+        // Positions that are zero on both sides count +1 each, a.z a tap.  Own operands: the accumulators start a tap at minus
+        // that, so a completed tap costs one fma per element, tot = fma(scale, y_t, tot) in the order t = 0, 1, ... (the
+        // chain is part of the interface), and one move to restart.  Taps apart: it is taken off where a tap's sums go to LDS.
         const BranchWalk walk = BranchWalk::make(s.cw);
         const int per_tap = walk.groups();
         const float start = (float)-a.z;                     // a.z: of one tap

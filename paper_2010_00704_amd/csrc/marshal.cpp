@@ -2,8 +2,8 @@
 //
 // A call that enqueues a kernel of a few microseconds is bound by the host.  Enqueueing a plain convolution call took 5.1 us
 // from Python, a module call 6.4, of which 3.1 to 3.7 are the HIP runtime's launch; the rest were one Python call per tensor,
-// two for the stream and ctypes' conversions.  With these functions it is 3.1 and 4.1: one 14 x 14 image, 64 channels, 5.3 -> 3.8 us
-// a pass, one 7 x 7 image, 1024 channels, 5.6 -> 4.7 (4.8 in a graph), a level of six small calls 32 -> 24.
+// two for the stream and ctypes' conversions.  With these functions it is 3.1 and 4.1: one 14 x 14 image, 64 channels, 5.3 -> 3.3 to 4.2 us
+// a pass (3.2 in a graph), one 7 x 7 image, 1024 channels, 5.6 -> 4.7 (5.1 in a graph), a level of six small calls 32 -> 24.
 //
 // The rules are binding.py's, which stay the fallback for whatever is not the common case (its _ptr, _desc and _stream are
 // called for tensor subclasses, descriptors that are no bcnn_conv_desc, stream objects, and before torch has initialised the
