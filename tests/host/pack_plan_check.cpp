@@ -3,7 +3,7 @@
 //   - every tile of the rows and every group of 64 channels is taken by exactly one wave, tiles of at most 64 positions,
 //   - tiles cover the row, groups the channels,
 //   - the launch stays below 2^32 threads, whatever the number of images (up to 2^31 - 1 output words);
-// and that measured calls go to the kernel that is faster on them.
+// that neither this plan nor that of the kernel through LDS takes an image beyond the kernels' 32-bit arithmetic; and that measured calls go to the kernel that is faster on them.
 // Prints "mismatches: N"; exit status 0 = none.
 #include "pack_plan.h"
 
@@ -38,9 +38,31 @@ static long check(int esz, int64_t outer, int64_t channels, int64_t inner, long*
     return bad;
 }
 
+// What both kernels compute in 32 bits of a source that a plan takes: an image's output by offsets of which one, 0x7FFFFF00, lies
+// past every buffer, channels and waves by number.
+static long check_addresses(int esz, int64_t outer, int64_t channels, int64_t inner, long* staged)
+{
+    const bool lds = staged_vectors(esz, 0, outer, channels, channels, inner) != 0;
+    const bool ballot = plan_ballot(esz, 0, outer, channels, channels, inner).nv != 0;
+    *staged += lds;
+    if (!lds && !ballot) return 0;
+    const int64_t words = (channels + 31) / 32;
+    const bool fits = inner * words * 4 <= 0x7FFFFF00 && channels + 64 <= 0x7FFFFFFF && outer * ((channels + 63) / 64) <= 0x7FFFFFFF;
+    if (!fits)
+        printf("image beyond 32 bits: %s, %d bytes [%lld][%lld][%lld]\n", lds ? "through LDS" : "ballot", esz, (long long)outer, (long long)channels,
+               (long long)inner);
+    return fits ? 0 : 1;
+}
+
 int main()
 {
-    long bad = 0, taken = 0;
+    long bad = 0, taken = 0, staged = 0;
+    for (int esz : {1, 2, 4})
+        for (int64_t channels : {33ll, 64ll, 1000ll, 1ll << 20, (1ll << 24) - 64, 1ll << 24, 272696320ll, 275000000ll, 1ll << 28, (1ll << 31) - 64, 1ll << 31, 1ll << 32, 1ll << 33})
+            for (int64_t inner : {5, 9, 16, 31, 32, 49, 63, 64, 100, 784})
+                for (int64_t outer : {1ll, 2ll, 7ll, 600ll, 2048ll, 1ll << 20})
+                    if (outer * inner <= 0x7FFFFFFF / ((channels + 31) / 32)) bad += check_addresses(esz, outer, channels, inner, &staged);
+    if (staged < 100) ++bad;
     const int64_t counts[] = {1, 2, 3, 4, 8, 20, 31, 32, 33, 64, 65, 100, 128, 192, 256, 257, 320, 512, 1000, 1024, 2048, 4096};
     for (int esz : {1, 2, 4})
         for (int64_t channels : counts)
