@@ -315,15 +315,18 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_branches_resident
                 __builtin_amdgcn_raw_buffer_store_b32((int)(~word & valid), res, (int)(left > 0 ? to : NOWHERE), 0, 0);
             }
         } else {
+            // (The row in the vector offset: the scalar one is left out of the bounds check, which drops the rows past the end.  Computed
+            // here: they are the same for every pass, and kept in registers they spill.)
 #pragma unroll
             for (int pb = 0; pb < P; ++pb)
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
                     const int ch = o0 + 32 * cb + j;
-                    const uint32_t to = ch < s.c_out ? (uint32_t)((32 * pb + 16 * hsel) * row_bytes + ch * 4) : NOWHERE;
+                    uint32_t to = ch < s.c_out ? (uint32_t)((32 * pb + 16 * hsel) * row_bytes + ch * 4) : NOWHERE;
+                    asm volatile("" : "+v"(to));
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(tot[pb][cb][r]), res, (int)to, r * row_bytes, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(tot[pb][cb][r]), res, (int)(to + (uint32_t)(r * row_bytes)), 0, 0);
                 }
         }
     };

@@ -88,15 +88,27 @@ def same(a, b):
     return torch.equal(a.reshape(-1).view(torch.uint8), b.reshape(-1).view(torch.uint8))
 
 
+def banded(shape, dtype):
+    """An output of rows between bands of 32 rows and more: (the whole buffer, the output in it, at an allocation's alignment)."""
+    rows, row = shape
+    band = (32 * row + 255) // 256 * 256
+    whole = torch.full((2 * band + rows * row,), 77, dtype=dtype, device="cuda")
+    return whole, whole[band:band + rows * row].view(shape)
+
+
 def both(call, outputs):
-    """The call under AUTO and on the vector ALUs: every output the same, to the bit."""
+    """The call under AUTO and on the vector ALUs: every output the same, to the bit, and neither writes around it."""
     got = []
     for variant in (B.BCNN_VARIANT_AUTO, B.BCNN_VARIANT_VALU):
-        out = [torch.full(shape, 77, dtype=dtype, device="cuda") for shape, dtype in outputs]
-        B.check(call(out, variant))
+        out = [banded(shape, dtype) for shape, dtype in outputs]
+        B.check(call([part for _, part in out], variant))
         got.append(out)
     torch.cuda.synchronize()
-    assert all(same(a, b) for a, b in zip(*got))
+    for (a, inside_a), (b, inside_b) in zip(*got):
+        assert same(inside_a, inside_b)
+        for whole, inside in ((a, inside_a), (b, inside_b)):
+            band = (whole.numel() - inside.numel()) // 2
+            assert (whole[:band] == 77).all() and (whole[-band:] == 77).all(), "write around the output"
 
 
 @pytest.mark.parametrize("kind,tile,walk,shape", CONVS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))

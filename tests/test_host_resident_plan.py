@@ -62,6 +62,9 @@ def test_branch_calls_of_the_gpu_tests(checker):
         assert takes_branches(checker, calls, out) == [(int(out == "bits" or shape[5] > 3), wide) for wide, shape in R.BRANCHES]
         assert takes_branches(checker, [s for _, s in R.BRANCHES_OF_TWO_LOADS], out) == [(0, wide) for wide, _ in R.BRANCHES_OF_TWO_LOADS]
         assert not any(t for t, _ in takes_branches(checker, calls, out, nothing_outside=True))
+    # last columns that end inside their first 16 pixels (one lane half) and inside the others
+    ends = [n * ((h - 1) // st + 1) * ((w - 1) // st + 1) % 32 for n, _, h, w, _, taps, st in calls if taps > 3]
+    assert any(0 < e < 16 for e in ends) and any(e > 16 for e in ends)
     ahead = [(64, 256, 28, 28, 256, 9, 1), (40, 320, 27, 27, 200, 9, 1), (64, 256, 28, 28, 256, 3, 1)]
     assert [t for t, _ in takes_branches(checker, ahead, "bits")] == [1, 1, 1]
     assert [t for t, _ in takes_branches(checker, ahead, "f32")] == [1, 1, 0]
