@@ -7,6 +7,10 @@
 
 namespace bcnn {
 
+// A byte offset past every buffer of up to 2 GiB, also with a load's further words added to it (-16 wraps to the buffer's start there).  The
+// bit pattern of -2.0f, which vector instructions hold as a constant.
+constexpr int PAST_ALL = (int)0xC0000000;
+
 // Shape of one convolution call as the kernels see it.
 struct ConvShape {
     int32_t n, h, w;        // input images and their extent

@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_branches_resident
 #pragma unroll
             for (int pb = 0; pb < Q; ++pb) {
                 const int in = __builtin_amdgcn_sbfe(taps[pb], (uint32_t)bit, 1u);
-                load_words(xres, ((base[pb] + xo) & in) | (~in & -16), c.x[pb]);
+                load_words(xres, ((base[pb] + xo) & in) | (~in & PAST_ALL), c.x[pb]);
             }
             ++f_tap;
         };

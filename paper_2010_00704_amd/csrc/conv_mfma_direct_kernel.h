@@ -386,12 +386,13 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) rb[pb] = (rbase[pb] + hsel * br.half) * 4;
         const auto pres = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(br.pad_words), 0, PAD == PAD_OPERAND ? a.pad_bytes : 0, 0x00020000);
+        // (no part of the offset in the scalar one, which the bounds check leaves out)
         auto load_words = [&](auto res, int off, auto& v, int at) __attribute__((always_inline)) {
             if constexpr (WIDE >= 4) {
                 const v4i q = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(res, off, 0, 0));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = q[i];
-                if constexpr (WIDE == 5) v[4] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, off, 16, 0);
+                if constexpr (WIDE == 5) v[4] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, (int)((uint32_t)off + 16u), 0, 0);
             } else if constexpr (WIDE == 3) {
                 const v3i q = __builtin_bit_cast(v3i, __builtin_amdgcn_raw_buffer_load_b96(res, off, 0, 0));
 #pragma unroll
@@ -419,9 +420,9 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
                     const int in = __builtin_amdgcn_sbfe((int)vmask[pb], (uint32_t)bit, 1u);     // all bits or none
-                    load_words(xres, ((rb[pb] + xo) & in) | (~in & -16), c.x[pb], i * WIDE);
+                    load_words(xres, ((rb[pb] + xo) & in) | (~in & PAST_ALL), c.x[pb], i * WIDE);
                     if constexpr (PAD == PAD_OPERAND) {
-                        const int at = (((tap * s.cw + hsel * br.half + k) * 4) & ~in) | (in & -16);
+                        const int at = (((tap * s.cw + hsel * br.half + k) * 4) & ~in) | (in & PAST_ALL);
                         if constexpr (PAD_LATER) load_words(pres, at, c.pad[pb], i * WIDE);
                         else if (!NARROW || s.ks == 3) {     // (always: the branch keeps the loads of a narrow group's taps apart, else again too many registers)
                             int p[STEPS];

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_mfma_resident_ker
 #pragma unroll
             for (int pb = 0; pb < P; ++pb) {
                 const int in = __builtin_amdgcn_sbfe(taps[pb], (uint32_t)bit, 1u);               // all bits or none
-                load_words(xres, ((base[pb] + xo) & in) | (~in & -16), c.x[pb]);
+                load_words(xres, ((base[pb] + xo) & in) | (~in & PAST_ALL), c.x[pb]);
             }
             const bool done = f_g + 1 == a.per_tap;
             f_g = done ? 0 : f_g + 1;

@@ -83,7 +83,8 @@ __device__ __forceinline__ ResidentPlace resident_place(const ResidentArgs& a)
     return ResidentPlace{range, (tile - range * a.n_ctiles) * RESIDENT_CHANNELS};
 }
 
-// WIDE words from a byte offset on (4-byte alignment; what lies past the tensor's end reads as zero)
+// WIDE words from a byte offset on (4-byte alignment; what lies past the tensor's end reads as zero, so no part of the offset is in the
+// scalar one, which the bounds check leaves out)
 template <int WIDE>
 __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t res, int off, int (&v)[WIDE])
 {
@@ -91,7 +92,7 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t res, int off, 
         const v4i q = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(res, off, 0, 0));
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = q[i];
-        if constexpr (WIDE == 5) v[4] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, off, 16, 0);
+        if constexpr (WIDE == 5) v[4] = (int)__builtin_amdgcn_raw_buffer_load_b32(res, (int)((uint32_t)off + 16u), 0, 0);
     } else {
         const v3i q = __builtin_bit_cast(v3i, __builtin_amdgcn_raw_buffer_load_b96(res, off, 0, 0));
 #pragma unroll

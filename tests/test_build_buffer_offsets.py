@@ -1,6 +1,6 @@
-"""Build check: every store through a buffer descriptor has all of its offset in the vector register and the instruction, none in the
+"""Build check: every access through a buffer descriptor has all of its offset in the vector register and the instruction, none in the
 scalar register.  LLVM leaves the scalar offset of the raw buffer builtins out of the bounds check, and these kernels count on that check:
-rows past the end of a ragged tile store nothing.  Every source is compiled to assembly for
+rows past the end of a ragged tile store nothing, words past a tensor's end read as zero.  Every source is compiled to assembly for
 the device and read; nothing runs, no GPU involved."""
 import os
 import re
@@ -10,13 +10,13 @@ from paper_2010_00704_amd import build
 
 
 def scalar_offsets(lines):
-    """Buffer stores with a scalar offset other than zero, and how many stores there are."""
+    """Buffer accesses with a scalar offset other than zero, and how many accesses there are."""
     found, seen, kernel = [], 0, ""
     for line in lines:
         text = line.split(";")[0].strip()
         if re.match(r"_Z[\w.$]*:$", text):
             kernel = text[:-1]
-        if not text.startswith(("buffer_store", "buffer_atomic")):
+        if not text.startswith(("buffer_load", "buffer_store", "buffer_atomic")):
             continue
         at = re.search(r"\b(?:s|ttmp)\[\d+:\d+\],\s*(\S+)", text)
         assert at, text
@@ -27,13 +27,14 @@ def scalar_offsets(lines):
 
 
 def test_the_reader_sees_a_scalar_offset():
-    good = ["_Zk:", "buffer_store_dword v0, v1, s[4:7], 0 offen offset:16", "buffer_store_dwordx4 v[0:3], off, s[4:7], 0 nt"]
-    assert scalar_offsets(good) == ([], 2)
+    good = ["_Zk:", "buffer_store_dword v0, v1, s[4:7], 0 offen offset:16", "buffer_store_dwordx4 v[0:3], off, s[4:7], 0 nt",
+            "buffer_load_dwordx4 v[0:3], v1, s[4:7], 0 offen nt", "buffer_load_dword v1, s[0:3], 0 offen lds"]
+    assert scalar_offsets(good) == ([], 4)
     assert len(scalar_offsets(good + ["buffer_store_dword v0, v1, s[4:7], s9 offen"])[0]) == 1
-    assert len(scalar_offsets(["buffer_store_dword v0, v1, s[4:7], 16 offen"])[0]) == 1
+    assert len(scalar_offsets(["buffer_load_dword v0, v1, s[4:7], 16 offen"])[0]) == 1
 
 
-def test_no_store_has_a_scalar_offset(tmp_path):
+def test_no_access_has_a_scalar_offset(tmp_path):
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
     root = os.path.dirname(os.path.dirname(os.path.abspath(build.__file__)))
     include = ["-I", os.path.join(root, "include"), "-I", os.path.join(root, "paper_2010_00704_amd", "csrc")]
@@ -47,6 +48,6 @@ def test_no_store_has_a_scalar_offset(tmp_path):
 
     with ThreadPoolExecutor(max_workers=8) as pool:
         results = list(pool.map(read, build.sources()))
-    assert sum(seen for _, seen in results) > 1000
+    assert sum(seen for _, seen in results) > 10000
     found = [hit for hits, _ in results for hit in hits]
-    assert not found, "%d stores with a scalar offset, the first: %s" % (len(found), found[:5])
+    assert not found, "%d accesses with a scalar offset, the first: %s" % (len(found), found[:5])
