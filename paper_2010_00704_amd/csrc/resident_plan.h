@@ -39,6 +39,13 @@ inline ResidentSplit resident_split(int m, int c_out)
     if (r.n_ranges > r.columns) r.n_ranges = r.columns;
     return r;
 }
+// Whether the workgroups, one a compute unit, keep `percent` of the 256 busy in every round: 130 channel tiles have one range each and
+// leave half of them idle, 290 take two rounds.  Below 2305 channels 90 % are always busy.
+inline bool resident_fills(const ResidentSplit& s, int percent)
+{
+    const int64_t workgroups = (int64_t)s.n_ctiles * s.n_ranges, rounds = (workgroups + 255) / 256;
+    return 100 * workgroups >= percent * 256 * rounds;
+}
 
 // Packed bits of 3x3 filters, 5 to 16 words a pixel, whose launch has one and a half tiles of 64 channels x 32 pixels for every SIMD
 // (1024) and more: below, the start with its expansion of all weights is what the launch takes.  Not where half of the only tile, or of every
@@ -47,6 +54,8 @@ inline ResidentSplit resident_split(int m, int c_out)
 // 3 % behind, 13 % at worst (us, before and this: 182 maps of 12 x 14, 256 -> 512 14.4 and 16.2).  With one tile a SIMD as the line
 // 17 of 180 were behind, 23 % at worst.  Of up to four words a pixel several taps share a group of K-steps: 0.95 to 1.03 times, no better than
 // level on average; 1x1 filters of up to 16 words 0.9 to 1.3.
+// Workgroups that keep 85 % of the compute units busy: over 150 calls of 1025 to 20 000 channels out, 0.93 of the time at 85 to 90 %, 1.01 at 80 to 85 %,
+// 1.35 at 50 to 60 % (54 x 54, stride 2, 256 -> 17 637 14.3 and 23.0; 344 maps of 9 x 9, 194 -> 9404 224 and 310).
 inline bool resident_takes(int m, int c_out, int cw, int ks)
 {
     if (ks != 3 || cw < 5) return false;
@@ -54,7 +63,7 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
     if (across % 2 != 0 && across < 5) return false;
     const SharedWalk walk = SharedWalk::make(cw, 9);
     const ResidentSplit split = resident_split(m, c_out);
-    return walk.steps(9) <= RESIDENT_STEPS && 2 * (int64_t)split.columns * split.n_ctiles >= 3 * 1024;
+    return walk.steps(9) <= RESIDENT_STEPS && 2 * (int64_t)split.columns * split.n_ctiles >= 3 * 1024 && resident_fills(split, 85);
 }
 
 // Branch calls (P shifted or parallel 1x1 branches, a real scale each) without a module's tail and without taps that contribute
@@ -63,6 +72,8 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
 // 1.16 times).  Over 662 calls of 400 tiles and more (us, shared weights and this, on average): bits of nine taps 0.91 times at 400 to
 // 800 tiles, 0.77 from 2048 on, of two taps 0.99 and 0.70 to 0.80, sums of nine taps 0.93 and 0.87; of the calls that the rule takes four are more than
 // 3 % behind, 5 % at worst.  Half-empty channel tiles are no worse here (38 calls 0.89, one 10 % behind).
+// Workgroups that keep 70 % of the compute units busy: over 90 calls of 1025 to 20 000 channels out, 0.93 of the time at 70 to 80 %, 1.05 at 60 to
+// 70 %, 1.2 below (bits, 41 maps of 21 x 21, three taps, 192 -> 9172 89 and 120; sums, 4 maps of 28 x 28, nine taps, 218 -> 17 775 105 and 129).
 // (an even number of taps of five words a load has no registers left)
 constexpr int RESIDENT_TAPS = 16;
 inline bool resident_takes_branches(int m, int c_out, int cw, int taps, bool bits, bool nothing_outside)
@@ -72,6 +83,7 @@ inline bool resident_takes_branches(int m, int c_out, int cw, int taps, bool bit
     if (walk.per_tap != 1 || walk.steps(taps) > RESIDENT_STEPS || (taps % 2 == 0 && walk.wide > 4)) return false;
     const ResidentSplit split = resident_split(m, c_out);
     const int64_t tiles = (int64_t)split.columns * split.n_ctiles;
+    if (!resident_fills(split, 70)) return false;
     return taps >= 4 ? tiles >= 400 : bits && tiles >= 800;
 }
 
