@@ -240,7 +240,7 @@ static int branches_entry(const bcnn_conv_desc* desc, int32_t branches, const ui
             // the forms of the direct kernel (shared_plan.h) are ahead of the vector ALUs everywhere and of the staged
             // kernel everywhere but one call in 74 (5 % there, before two of the three forms); the vector ALUs take large
             // tails of few words (auto_plan.h) and what has too many branches or bytes
-            if (!tail && bcnn::resident_takes_branches(s.m, s.c_out, s.cw, branches, fused, a.zero_pad && s.pad) && bcnn::conv_branches_direct_supported(s, a)) {
+            if (!tail && bcnn::resident_takes_branches(s.m, s.c_out, s.cw, branches, fused, x_branch_stride != 0, a.zero_pad && s.pad) && bcnn::conv_branches_direct_supported(s, a)) {
                 e = bcnn::launch_conv_branches_resident(s, a, st);
                 break;
             }

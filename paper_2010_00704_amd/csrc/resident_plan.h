@@ -68,15 +68,18 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
 
 // Branch calls (P shifted or parallel 1x1 branches, a real scale each) without a module's tail and without taps that contribute
 // nothing, 5 to 10 words a pixel (a tap is one group of K-steps).  Packed bits from 800 tiles of 64 channels x 32 pixels on, or of four and more
-// taps from 400 on, where the waves that take whole taps end; float sums of four and more taps, whose stores weigh less (of one to three taps 0.94 to
-// 1.16 times).  Over 662 calls of 400 tiles and more (us, shared weights and this, on average): bits of nine taps 0.91 times at 400 to
+// taps from 400 on, where the waves that take whole taps end; float sums of six and more taps on one tensor, whose stores weigh less (of one to three taps
+// 0.94 to 1.16 times, of four and five 0.86 to 1.17).  Not float sums of branches that have tensors of their own: two taps ahead is not early enough for
+// loads from memory that the stores delay.  Their inputs in the last-level cache 1.03 times on average over 104 calls, from memory 1.14 over 96, 1.49 at
+// worst (492 maps of 24 x 24, four taps, 160 -> 192 45 and 66; 3x3, 37 maps of 40 x 40, 192 -> 512 42 and 59); bits of such calls 0.83, from memory too.
+// Over 662 calls of 400 tiles and more (us, shared weights and this, on average): bits of nine taps 0.91 times at 400 to
 // 800 tiles, 0.77 from 2048 on, of two taps 0.99 and 0.70 to 0.80, sums of nine taps 0.93 and 0.87; of the calls that the rule takes four are more than
 // 3 % behind, 5 % at worst.  Half-empty channel tiles are no worse here (38 calls 0.89, one 10 % behind).
 // Workgroups that keep 70 % of the compute units busy: over 90 calls of 1025 to 20 000 channels out, 0.93 of the time at 70 to 80 %, 1.05 at 60 to
 // 70 %, 1.2 below (bits, 41 maps of 21 x 21, three taps, 192 -> 9172 89 and 120; sums, 4 maps of 28 x 28, nine taps, 218 -> 17 775 105 and 129).
 // (an even number of taps of five words a load has no registers left)
 constexpr int RESIDENT_TAPS = 16;
-inline bool resident_takes_branches(int m, int c_out, int cw, int taps, bool bits, bool nothing_outside)
+inline bool resident_takes_branches(int m, int c_out, int cw, int taps, bool bits, bool own, bool nothing_outside)
 {
     if (cw < 5 || taps > RESIDENT_TAPS || nothing_outside) return false;
     const SharedWalk walk = SharedWalk::make(cw, taps);
@@ -84,7 +87,8 @@ inline bool resident_takes_branches(int m, int c_out, int cw, int taps, bool bit
     const ResidentSplit split = resident_split(m, c_out);
     const int64_t tiles = (int64_t)split.columns * split.n_ctiles;
     if (!resident_fills(split, 70)) return false;
-    return taps >= 4 ? tiles >= 400 : bits && tiles >= 800;
+    if (!bits) return taps >= 6 && !own && tiles >= 400;
+    return tiles >= (taps >= 4 ? 400 : 800);
 }
 
 }  // namespace bcnn

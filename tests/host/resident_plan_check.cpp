@@ -1,7 +1,7 @@
 // Host-only check of how the kernel whose weights stay in LDS splits a call (csrc/resident_plan.h): every column of 32 pixels of
 // every channel tile is taken by exactly one pass of one wave, passes hold one to RESIDENT_PASS columns, a launch has at
 // most 256 workgroups unless there are more channel tiles, and places lie inside their LDS table.  Prints "mismatches: N"; exit
-// status 0 = none.  With lines "m c_out cw taps bits nothing_outside" on stdin and an argument, "calls" (bits of a filter) or "branches": whether
+// status 0 = none.  With lines "m c_out cw taps bits own nothing_outside" on stdin and an argument, "calls" (bits of a filter) or "branches": whether
 // the kernel takes each of them, and the words of a load.
 #include "resident_plan.h"
 
@@ -42,9 +42,9 @@ static long check(int m, int c_out, int most = RESIDENT_PASS)
 int main(int argc, char** argv)
 {
     if (argc > 1) {
-        int m, c_out, cw, taps, bits, nothing;
-        while (scanf("%d %d %d %d %d %d", &m, &c_out, &cw, &taps, &bits, &nothing) == 6)
-            printf("%d %d\n", (int)(argv[1][0] == 'c' ? resident_takes(m, c_out, cw, taps == 9 ? 3 : 1) : resident_takes_branches(m, c_out, cw, taps, bits, nothing)),
+        int m, c_out, cw, taps, bits, own, nothing;
+        while (scanf("%d %d %d %d %d %d %d", &m, &c_out, &cw, &taps, &bits, &own, &nothing) == 7)
+            printf("%d %d\n", (int)(argv[1][0] == 'c' ? resident_takes(m, c_out, cw, taps == 9 ? 3 : 1) : resident_takes_branches(m, c_out, cw, taps, bits, own, nothing)),
                    SharedWalk::make(cw, taps).wide);
         return 0;
     }

@@ -39,10 +39,16 @@ BRANCHES = [
     (3, (61, 192, 27, 26, 100, 4, 1)),
     (4, (61, 256, 27, 26, 100, 16, 1)),
     (5, (40, 300, 27, 26, 100, 7, 2)),
-    (3, (30, 130, 27, 26, 170, 5, 1)),
-] + [(wide, (61, c, 27, 26, 100, taps, 1)) for wide, c, taps in ((4, 250, 1), (3, 180, 2), (5, 260, 3))]   # few taps: bits only
+    (3, (30, 130, 27, 26, 170, 5, 1)),          # (up to five taps and tensors of their own: bits only)
+    (3, (61, 192, 27, 26, 100, 6, 1)),
+] + [(wide, (61, c, 27, 26, 100, taps, 1)) for wide, c, taps in ((4, 250, 1), (3, 180, 2), (5, 260, 3))]
 # what these kernels leave to the form with shared weights: taps of two loads
 BRANCHES_OF_TWO_LOADS = [(3, (61, 380, 27, 26, 100, 9, 1)), (4, (61, 500, 27, 26, 100, 9, 1)), (5, (61, 630, 27, 26, 100, 9, 1)), (5, (61, 260, 27, 26, 100, 2, 1))]
+
+
+def own_tensors(taps):
+    """Whether a call of the list gives each of its branches a tensor of its own."""
+    return taps in (3, 4, 7)
 
 
 @pytest.mark.parametrize("wide,shape", CALLS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
@@ -67,7 +73,7 @@ def test_branches(wide, shape, out, pad_mode):
     n, c, h, w, o, taps, stride = shape
     k = 3 if taps == 9 else 1
     d = Draw(92000 + 17 * c + o + taps)
-    own = taps in (3, 4, 7)                             # tensors of their own
+    own = own_tensors(taps)
     (x, _, keep_x), (wt, _, keep_w), (pad, _, keep_p) = d.packed(n * (taps if own else 1), c, h, w), d.packed(o, c, taps), d.packed(taps, c, 1)
     desc = B.conv_desc(n, c, h, w, o, k, stride, k // 2)
     ho, wo = B.out_shape(desc)

@@ -32,13 +32,13 @@ def ask(checker, rows, what):
 
 def takes(checker, calls):
     """Per call (n, c_in, h, w, c_out, filter, stride, pad): whether the kernel takes it, words of a load."""
-    return ask(checker, [(n * ((h + 2 * p - k) // st + 1) * ((w + 2 * p - k) // st + 1), o, (c + 31) // 32, k * k, 1, 0) for n, c, h, w, o, k, st, p in calls],
+    return ask(checker, [(n * ((h + 2 * p - k) // st + 1) * ((w + 2 * p - k) // st + 1), o, (c + 31) // 32, k * k, 1, 0, 0) for n, c, h, w, o, k, st, p in calls],
                "calls")
 
 
-def takes_branches(checker, calls, out, nothing_outside=False):
+def takes_branches(checker, calls, out, nothing_outside=False, own=R.own_tensors):
     """The same per call (n, c_in, h, w, c_out, taps, stride) of branches."""
-    return ask(checker, [(n * ((h - 1) // st + 1) * ((w - 1) // st + 1), o, (c + 31) // 32, t, out == "bits", nothing_outside) for n, c, h, w, o, t, st in calls],
+    return ask(checker, [(n * ((h - 1) // st + 1) * ((w - 1) // st + 1), o, (c + 31) // 32, t, out == "bits", own(t), nothing_outside) for n, c, h, w, o, t, st in calls],
                "branches")
 
 
@@ -60,15 +60,20 @@ def test_measured_calls(checker):
 def test_branch_calls_of_the_gpu_tests(checker):
     calls = [shape for _, shape in R.BRANCHES]
     for out in R.OUTS:
-        assert takes_branches(checker, calls, out) == [(int(out == "bits" or shape[5] > 3), wide) for wide, shape in R.BRANCHES]
+        assert takes_branches(checker, calls, out) == [(int(out == "bits" or (shape[5] > 5 and not R.own_tensors(shape[5]))), wide) for wide, shape in R.BRANCHES]
         assert takes_branches(checker, [s for _, s in R.BRANCHES_OF_TWO_LOADS], out) == [(0, wide) for wide, _ in R.BRANCHES_OF_TWO_LOADS]
         assert not any(t for t, _ in takes_branches(checker, calls, out, nothing_outside=True))
     # last columns that end inside their first 16 pixels (one lane half) and inside the others
-    ends = [n * ((h - 1) // st + 1) * ((w - 1) // st + 1) % 32 for n, _, h, w, _, taps, st in calls if taps > 3]
+    ends = [n * ((h - 1) // st + 1) * ((w - 1) // st + 1) % 32 for (n, _, h, w, _, _, st), (t, _) in zip(calls, takes_branches(checker, calls, "f32")) if t]
     assert any(0 < e < 16 for e in ends) and any(e > 16 for e in ends)
     ahead = [(64, 256, 28, 28, 256, 9, 1), (40, 320, 27, 27, 200, 9, 1), (64, 256, 28, 28, 256, 3, 1)]
     assert [t for t, _ in takes_branches(checker, ahead, "bits")] == [1, 1, 1]
     assert [t for t, _ in takes_branches(checker, ahead, "f32")] == [1, 1, 0]
+    own = [(492, 160, 24, 24, 192, 4, 1), (37, 192, 40, 40, 512, 9, 1), (64, 256, 28, 28, 256, 9, 1)]
+    assert [t for t, _ in takes_branches(checker, own, "f32", own=lambda taps: True)] == [0, 0, 0]
+    assert [t for t, _ in takes_branches(checker, own, "bits", own=lambda taps: True)] == [1, 1, 1]
+    few_taps = [(487, 225, 14, 14, 256, 5, 1), (58, 161, 30, 30, 704, 4, 1)]
+    assert not any(t for t, _ in takes_branches(checker, few_taps, "f32", own=lambda taps: False))
     many_channels = [(41, 192, 21, 21, 9172, 3, 1), (1, 192, 36, 36, 18275, 9, 1), (4, 218, 28, 28, 17775, 9, 1)]
     assert not any(t for out in R.OUTS for t, _ in takes_branches(checker, many_channels, out))
     small = [(1, 256, 28, 28, 256, 9, 1), (2, 384, 13, 13, 384, 9, 1), (64, 128, 28, 28, 256, 9, 1)]
