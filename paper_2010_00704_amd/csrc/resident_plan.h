@@ -68,7 +68,8 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
 
 // Branch calls (P shifted or parallel 1x1 branches, a real scale each) without a module's tail and without taps that contribute
 // nothing, 5 to 10 words a pixel (a tap is one group of K-steps).  Packed bits from 800 tiles of 64 channels x 32 pixels on, or of four and more
-// taps from 400 on, where the waves that take whole taps end; float sums of six and more taps on one tensor, whose stores weigh less (of one to three taps
+// taps from 400 on, and nowhere where waves take whole taps (an odd number of channel blocks: bits, nine taps, 256 -> 96, 3 maps of 49 x 49 5.2
+// there and 6.2, sums, six, 245 -> 160 4.6 and 5.5); float sums of six and more taps on one tensor, whose stores weigh less (of one to three taps
 // 0.94 to 1.16 times, of four and five 0.86 to 1.17).  Not float sums of branches that have tensors of their own: two taps ahead is not early enough for
 // loads from memory that the stores delay.  Their inputs in the last-level cache 1.03 times on average over 104 calls, from memory 1.14 over 96, 1.49 at
 // worst (492 maps of 24 x 24, four taps, 160 -> 192 45 and 66; 3x3, 37 maps of 40 x 40, 192 -> 512 42 and 59); bits of such calls 0.83, from memory too.
@@ -81,7 +82,7 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
 constexpr int RESIDENT_TAPS = 16;
 inline bool resident_takes_branches(int m, int c_out, int cw, int taps, bool bits, bool own, bool nothing_outside)
 {
-    if (cw < 5 || taps > RESIDENT_TAPS || nothing_outside) return false;
+    if (cw < 5 || taps > RESIDENT_TAPS || nothing_outside || branches_apart(m, c_out, taps)) return false;
     const SharedWalk walk = SharedWalk::make(cw, taps);
     if (walk.per_tap != 1 || walk.steps(taps) > RESIDENT_STEPS || (taps % 2 == 0 && walk.wide > 4)) return false;
     const ResidentSplit split = resident_split(m, c_out);

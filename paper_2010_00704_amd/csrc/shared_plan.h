@@ -116,10 +116,14 @@ inline int shared_choose(int m, int c_out, int cw, int ks, int stride, int kind,
 enum { BRANCH_OWN = 0, BRANCH_APART, BRANCH_SHARED };
 constexpr int APART_TAPS = 9;                                // sums of taps that fit LDS
 struct BranchChoice { int form, tile; };
+inline bool branches_apart(int m, int c_out, int branches)
+{
+    return branches <= APART_TAPS && (((int64_t)m + 31) / 32) * ((c_out + 31) / 32) <= 3 * 256;
+}
 inline BranchChoice branches_choose(int m, int c_out, int cw, int branches, bool tail, bool half)
 {
     const int64_t blocks = (((int64_t)m + 31) / 32) * ((c_out + 31) / 32);
-    if (branches <= APART_TAPS && blocks <= 3 * 256) return BranchChoice{BRANCH_APART, DIRECT_1x1_K4};
+    if (branches_apart(m, c_out, branches)) return BranchChoice{BRANCH_APART, DIRECT_1x1_K4};
     const int own = branches_direct_choose(m, c_out, cw, branches, tail, half);
     if ((cw <= 2 && cw * branches <= 8) || (branches == 1 && cw <= 4)) return BranchChoice{BRANCH_OWN, own};
     const int across = (c_out + 31) / 32;

@@ -74,6 +74,8 @@ def test_branch_calls_of_the_gpu_tests(checker):
     assert [t for t, _ in takes_branches(checker, own, "bits", own=lambda taps: True)] == [1, 1, 1]
     few_taps = [(487, 225, 14, 14, 256, 5, 1), (58, 161, 30, 30, 704, 4, 1)]
     assert not any(t for t, _ in takes_branches(checker, few_taps, "f32", own=lambda taps: False))
+    whole_taps_a_wave = [(3, 256, 49, 49, 96, 9, 1), (3, 227, 49, 49, 73, 9, 1), (2, 256, 33, 33, 352, 9, 1), (5, 192, 31, 31, 132, 4, 1)]
+    assert not any(t for out in R.OUTS for t, _ in takes_branches(checker, whole_taps_a_wave, out))
     many_channels = [(41, 192, 21, 21, 9172, 3, 1), (1, 192, 36, 36, 18275, 9, 1), (4, 218, 28, 28, 17775, 9, 1)]
     assert not any(t for out in R.OUTS for t, _ in takes_branches(checker, many_channels, out))
     small = [(1, 256, 28, 28, 256, 9, 1), (2, 384, 13, 13, 384, 9, 1), (64, 128, 28, 28, 256, 9, 1)]
