@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_branches_resident
     __shared__ struct {
         // [channel block][K-step][unit of 16 bytes = a row's words' codes]: lane half h finds row i at unit 32 h + (i ^ 8 h)
         __align__(16) char weights[CB * RESIDENT_STEPS * 1024];
-        v2i pixel[RESIDENT_COLUMNS * 32];
+        v2i pixel[RESIDENT_BRANCH_COLUMNS * 32];
         float scale[MAX_TAPS + 1][RESIDENT_CHANNELS];        // the last row: the bias
         __align__(16) int pad[PAD == PAD_OPERAND ? MAX_TAPS + 1 : 1][2][UNIT];   // [tap][lane half]
     } lds;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_branches_resident
             const int k = t % UNIT, word = ((t / UNIT) & 1) * a.half + k;
             pad = __builtin_amdgcn_raw_buffer_load_b32(pres, k < WIDE && word < s.cw ? (t / (2 * UNIT) * s.cw + word) * 4 : -4, 0, 0);
         }
-        resident_places(a, lds.pixel, columns.first, columns.count < RESIDENT_COLUMNS ? columns.count : RESIDENT_COLUMNS);
+        resident_places(a, lds.pixel, columns.first, columns.count < RESIDENT_BRANCH_COLUMNS ? columns.count : RESIDENT_BRANCH_COLUMNS);
 #pragma unroll
         for (int i = 0; i < SHARE; ++i)
             if (row0 + i * RESIDENT_WAVES < MAX_TAPS) lds.scale[row0 + i * RESIDENT_WAVES][cl] = __uint_as_float(scales[i]);
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_branches_resident
                 }
         }
     };
-    resident_columns<2>(a, columns, lds.pixel, wave, pass);
+    resident_columns<2, RESIDENT_BRANCH_COLUMNS>(a, columns, lds.pixel, wave, pass);
 }
 
 template <int WIDE>

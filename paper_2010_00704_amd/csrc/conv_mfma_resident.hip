@@ -236,7 +236,7 @@ __global__ __launch_bounds__(64 * RESIDENT_WAVES, 2) void conv_mfma_resident_ker
             }
         }
     };
-    resident_columns<RESIDENT_PASS>(a, columns, lds.pixel, wave, pass);
+    resident_columns<RESIDENT_PASS, RESIDENT_COLUMNS>(a, columns, lds.pixel, wave, pass);
 }
 
 }  // namespace

@@ -123,12 +123,12 @@ __device__ __forceinline__ void resident_places(const ResidentArgs& a, v2i* pixe
 }
 
 // Every column of the workgroup in passes of one to MOST columns: pass(std::integral_constant<int, columns>, column, its place in `pixel`).
-// The first places have been put there.
-template <int MOST, class Pass>
+// TABLE: columns that `pixel` holds; the first places have been put there.
+template <int MOST, int TABLE, class Pass>
 __device__ __forceinline__ void resident_columns(const ResidentArgs& a, const ResidentRun& columns, v2i* pixel, int wave, Pass&& pass)
 {
     for (int done = 0;;) {
-        const int here = columns.count - done < RESIDENT_COLUMNS ? columns.count - done : RESIDENT_COLUMNS;
+        const int here = columns.count - done < TABLE ? columns.count - done : TABLE;
         const ResidentRun mine = resident_run(here / RESIDENT_WAVES, here % RESIDENT_WAVES, wave);
 #pragma unroll 1
         for (int place = mine.first, left = mine.count; left > 0;) {
@@ -143,7 +143,7 @@ __device__ __forceinline__ void resident_columns(const ResidentArgs& a, const Re
         done += here;
         if (done >= columns.count) break;
         meet();
-        resident_places(a, pixel, columns.first + done, columns.count - done < RESIDENT_COLUMNS ? columns.count - done : RESIDENT_COLUMNS);
+        resident_places(a, pixel, columns.first + done, columns.count - done < TABLE ? columns.count - done : TABLE);
         meet();
     }
 }

@@ -16,7 +16,8 @@ namespace bcnn {
 constexpr int RESIDENT_WAVES = 8;                            // of a workgroup; one workgroup a compute unit
 constexpr int RESIDENT_CHANNELS = 64;                        // of a workgroup, every wave takes all of them
 constexpr int RESIDENT_STEPS = 72;                           // K-steps whose expanded weights fit LDS, 2 KB each
-constexpr int RESIDENT_COLUMNS = 40;                         // of 32 pixels, whose places lie in LDS at a time
+// Columns of 32 pixels whose places lie in LDS at a time: what the weights leave, in branch mode beside its scales and pad words.
+constexpr int RESIDENT_COLUMNS = 52, RESIDENT_BRANCH_COLUMNS = 40;
 constexpr int RESIDENT_PASS = 4;                             // columns of a wave at a time
 
 // Part `part` of a number of columns in parts whose lengths differ by one at most, the longer ones (`rest` of them) first.

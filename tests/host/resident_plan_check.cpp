@@ -10,7 +10,7 @@
 
 using namespace bcnn;
 
-static long check(int m, int c_out, int most = RESIDENT_PASS)
+static long check(int m, int c_out, int most = RESIDENT_PASS, int table = RESIDENT_COLUMNS)
 {
     const ResidentSplit split = resident_split(m, c_out);
     long bad = 0;
@@ -20,8 +20,8 @@ static long check(int m, int c_out, int most = RESIDENT_PASS)
     std::vector<int> seen(split.columns, 0);
     for (int range = 0; range < split.n_ranges; ++range) {
         const ResidentRun columns = resident_run(quotient, rest, range);
-        for (int done = 0; done < columns.count; done += RESIDENT_COLUMNS) {
-            const int here = columns.count - done < RESIDENT_COLUMNS ? columns.count - done : RESIDENT_COLUMNS;
+        for (int done = 0; done < columns.count; done += table) {
+            const int here = columns.count - done < table ? columns.count - done : table;
             for (int wave = 0; wave < RESIDENT_WAVES; ++wave) {
                 const ResidentRun mine = resident_run(here / RESIDENT_WAVES, here % RESIDENT_WAVES, wave);
                 for (int place = mine.first, left = mine.count; left > 0;) {
@@ -50,7 +50,7 @@ int main(int argc, char** argv)
     }
     long bad = 0;
     for (int c_out : {1, 32, 64, 65, 130, 256, 700, 1024, 5000, 20000})
-        for (int m : {1, 31, 32, 33, 1000, 3136, 12544, 50176, 50177, 426000, 1000001}) bad += check(m, c_out) + check(m, c_out, 2);
+        for (int m : {1, 31, 32, 33, 1000, 3136, 12544, 50176, 50177, 426000, 1000001}) bad += check(m, c_out) + check(m, c_out, 2, RESIDENT_BRANCH_COLUMNS);
     for (int m = 1; m < 60000; m += 37) bad += check(m, 256);
     printf("mismatches: %ld\n", bad);
     return bad != 0;
