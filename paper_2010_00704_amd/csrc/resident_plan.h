@@ -48,13 +48,13 @@ inline bool resident_fills(const ResidentSplit& s, int percent)
     return 100 * workgroups >= percent * 256 * rounds;
 }
 
-// Packed bits of 3x3 filters, 5 to 16 words a pixel, whose launch has one and a half tiles of 64 channels x 32 pixels for every SIMD
+// Packed bits of 3x3 filters, 5 to 16 words a pixel, whose launch has two tiles of 64 channels x 32 pixels for every SIMD
 // (1024) and more: below, the start with its expansion of all weights is what the launch takes.  Not where half of the only tile, or of every
-// second one, is channels that do not exist (32 channels: 10 of 18 calls more than 5 % behind, 22 % at worst).  Over 574 calls that the rule takes, timed
-// on this kernel and on the one that ran them before (192 to 512 channels in, 64 to 1024 out, strides 1 and 2): 0.90 of the time, eight more than
-// 3 % behind, 13 % at worst (us, before and this: 182 maps of 12 x 14, 256 -> 512 14.4 and 16.2).  With one tile a SIMD as the line
-// 17 of 180 were behind, 23 % at worst.  Of up to four words a pixel several taps share a group of K-steps: 0.95 to 1.03 times, no better than
-// level on average; 1x1 filters of up to 16 words 0.9 to 1.3.
+// second one, is channels that do not exist (32 channels: 10 of 18 calls more than 5 % behind, 22 % at worst).  Over 420 calls (130 to 512 channels in, 64 to
+// 2304 out, strides 1 and 2), timed on this kernel and on the one that ran them before, inputs from the last-level cache and from memory: 0.90 and 0.91 of
+// the time from two tiles on, 13 and 26 of them more than 3 % behind, 15 % at worst (us, from memory: 62 maps of 12 x 12, 504 -> 832 15.4 and 17.3); between one and a half and two
+// 0.98 and 0.99, 6 and 12 of 39 behind, 17 % at worst.  Of up to four words a pixel several taps share a group of K-steps: 0.95 to 1.03
+// times, no better than level on average; 1x1 filters of up to 16 words 0.9 to 1.3.
 // Workgroups that keep 85 % of the compute units busy: over 150 calls of 1025 to 20 000 channels out, 0.93 of the time at 85 to 90 %, 1.01 at 80 to 85 %,
 // 1.35 at 50 to 60 % (54 x 54, stride 2, 256 -> 17 637 14.3 and 23.0; 344 maps of 9 x 9, 194 -> 9404 224 and 310).
 inline bool resident_takes(int m, int c_out, int cw, int ks)
@@ -64,7 +64,7 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
     if (across % 2 != 0 && across < 5) return false;
     const SharedWalk walk = SharedWalk::make(cw, 9);
     const ResidentSplit split = resident_split(m, c_out);
-    return walk.steps(9) <= RESIDENT_STEPS && 2 * (int64_t)split.columns * split.n_ctiles >= 3 * 1024 && resident_fills(split, 85);
+    return walk.steps(9) <= RESIDENT_STEPS && (int64_t)split.columns * split.n_ctiles >= 2 * 1024 && resident_fills(split, 85);
 }
 
 // Branch calls (P shifted or parallel 1x1 branches, a real scale each) without a module's tail and without taps that contribute

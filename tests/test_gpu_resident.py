@@ -14,16 +14,16 @@ pytestmark = pytest.mark.gpu
 
 CALLS = [
     # words per load, (n, c_in, h, w, c_out, stride, pad)
-    (3, (30, 140, 27, 26, 190, 1, 1)),          # 5 words: halves of 3 and 2
-    (3, (71, 192, 27, 26, 64, 1, 1)),           # 6 words, all whole
-    (4, (30, 200, 29, 28, 161, 1, 0)),          # 7 words, part of the last
-    (4, (64, 256, 14, 14, 320, 1, 1)),          # 8 words, all whole
+    (3, (34, 140, 27, 26, 190, 1, 1)),          # 5 words: halves of 3 and 2
+    (3, (95, 192, 27, 26, 64, 1, 1)),           # 6 words, all whole
+    (4, (34, 200, 29, 28, 161, 1, 0)),          # 7 words, part of the last
+    (4, (70, 256, 14, 14, 320, 1, 1)),          # 8 words, all whole
     (5, (30, 320, 27, 27, 200, 1, 1)),          # 10 words, all whole
-    (5, (150, 290, 29, 27, 100, 2, 1)),          # the same, part of the last
-    (3, (40, 380, 27, 26, 128, 1, 1)),          # 12 words in two groups a tap
-    (4, (90, 500, 27, 26, 250, 2, 0)),          # 16 words in two groups, part of the last
+    (5, (160, 290, 29, 27, 100, 2, 1)),          # the same, part of the last
+    (3, (48, 380, 27, 26, 128, 1, 1)),          # 12 words in two groups a tap
+    (4, (107, 500, 27, 26, 250, 2, 0)),          # 16 words in two groups, part of the last
     (4, (64, 512, 14, 14, 512, 1, 1)),          # as many K-steps as LDS holds
-    (4, (3, 224, 11, 13, 7000, 1, 1)),          # few columns, many channel tiles: passes of one or two
+    (4, (5, 224, 11, 13, 7000, 1, 1)),          # few columns, many channel tiles: passes of one or two
     (3, (600, 129, 27, 28, 60, 1, 1)),          # 55 columns and more a workgroup: two tables of places
 ]
 

@@ -53,7 +53,7 @@ def test_calls_of_the_gpu_tests(checker):
 def test_measured_calls(checker):
     ahead = [(64, 256, 28, 28, 256, 3, 1, 1), (64, 256, 56, 56, 512, 3, 2, 1), (512, 256, 28, 28, 256, 3, 1, 1)]
     behind = [(1, 256, 54, 54, 17637, 3, 2, 1), (344, 194, 9, 9, 9404, 3, 1, 1), (28, 160, 48, 48, 18528, 3, 2, 1), (13, 256, 31, 31, 5650, 3, 1, 1),
-              (37, 320, 37, 37, 32, 3, 1, 1), (146, 384, 41, 41, 32, 3, 1, 1), (13, 320, 27, 27, 200, 3, 1, 1), (64, 512, 14, 14, 256, 1, 1, 0)]
+              (8, 297, 19, 19, 1408, 3, 1, 1), (13, 256, 28, 28, 288, 3, 1, 1), (37, 320, 37, 37, 32, 3, 1, 1), (146, 384, 41, 41, 32, 3, 1, 1), (13, 320, 27, 27, 200, 3, 1, 1), (64, 512, 14, 14, 256, 1, 1, 0)]
     assert [t for t, _ in takes(checker, ahead + behind)] == [1] * len(ahead) + [0] * len(behind)
 
 
