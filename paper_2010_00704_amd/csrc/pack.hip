@@ -633,7 +633,7 @@ hipError_t pack_dispatch(const T* src, const float* bias, int64_t outer, int64_t
                     else if (row % 4 == 0) launch(pack_staged_kernel<T, N, BIAS, false, false, NT>);
                     else launch(pack_staged_kernel<T, N, BIAS, ESZ < 4, false, NT>);
                 };
-                if (staged_streams(outer * src_channels * row)) of(std::true_type{});
+                if (staged_streams(ESZ, row, outer * src_channels * row)) of(std::true_type{});
                 else of(std::false_type{});
             }
         };

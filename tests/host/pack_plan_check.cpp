@@ -84,6 +84,17 @@ int main()
             printf("route: %d bytes [%lld][%lld][%lld]\n", r.esz, (long long)r.outer, (long long)r.channels, (long long)r.inner);
             ++bad;
         }
+    // sources that are read past the caches' lines: [outer][channels][inner]
+    const struct { int esz; int64_t outer, channels, inner; bool streams; } loads[] = {
+        {2, 256, 1024, 49, false}, {2, 2000, 1024, 49, false}, {2, 3009, 1024, 49, false}, {2, 3010, 1024, 49, true}, {1, 8000, 512, 49, false}, {1, 12038, 512, 49, true},
+        {4, 83, 1024, 49, false}, {4, 84, 1024, 49, true}, {4, 600, 256, 28, false}, {4, 10533, 256, 28, true}, {4, 2000, 1024, 9, false},
+    };
+    for (const auto& r : loads)
+        if (!staged_vectors(r.esz, 0, r.outer, r.channels, r.channels, r.inner) ||
+            staged_streams(r.esz, r.inner * r.esz, r.outer * r.channels * r.inner * r.esz) != r.streams) {
+            printf("loads: %d bytes [%lld][%lld][%lld]\n", r.esz, (long long)r.outer, (long long)r.channels, (long long)r.inner);
+            ++bad;
+        }
     const struct { int s; int64_t channels, m; bool eight; } pools[] = {
         {2, 8, 1, true}, {2, 2048, 100, true}, {3, 64, 324, false}, {4, 64, 19528, false}, {4, 8, 585, false},
         {3, 16, 138834, true}, {4, 8, 156212, true}, {5, 8, 1 << 20, false}, {1, 8, 1 << 20, false},

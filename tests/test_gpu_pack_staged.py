@@ -47,3 +47,29 @@ def test_pack_planes_through_lds(shape, kind):
         out = Guarded(n * inner * ((c + 31) // 32), dev)
         B.check(B.bcnn_pack(buf.data_ptr() + off, code, n, c, inner, out.ptr), "pack")
         assert np.array_equal(out.get(np.uint32).reshape(n, inner, -1), oracle.pack_channels(oracle.sign_f32(v32)))
+
+
+BEYOND_THE_CACHE = [
+    # element type, channels, inner: rows of whole vectors, of whole dwords and of neither
+    (torch.bfloat16, 256, 56), (torch.float16, 200, 34), (torch.float16, 130, 25), (torch.int8, 96, 64), (torch.int8, 100, 49), (torch.float32, 64, 28), (torch.float32, 65, 9),
+]
+
+
+@pytest.mark.parametrize("dtype,c,inner", BEYOND_THE_CACHE, ids=lambda v: str(v).replace("torch.", ""))
+def test_pack_planes_beyond_the_cache(dtype, c, inner):
+    """Sources of more than 288 MB are loaded past the caches' lines; their parts, each below that, are not."""
+    dev = gpu_device()
+    code = {torch.float32: B.BCNN_F32, torch.float16: B.BCNN_F16, torch.bfloat16: B.BCNN_BF16, torch.int8: B.BCNN_I8}[dtype]
+    size = torch.empty(0, dtype=dtype).element_size()
+    n = (300 << 20) // (c * inner * size) // 2 * 2
+    g = torch.Generator(device=dev)
+    g.manual_seed(c + inner)
+    x = torch.randint(-100, 101, (n, c, inner), generator=g, device=dev, dtype=torch.int8).to(dtype)
+    bias = torch.randint(-3, 4, (c,), generator=g, device=dev).float()
+    words = n * inner * ((c + 31) // 32)
+    whole, parts = Guarded(words, dev), Guarded(words, dev)
+    B.check(B.bcnn_pack_bias(x.data_ptr(), code, n, c, inner, bias, whole.ptr), "whole")
+    for k in range(2):
+        B.check(B.bcnn_pack_bias(x[k * n // 2].data_ptr(), code, n // 2, c, inner, bias, parts.ptr + 4 * k * (words // 2)), "part")
+    assert np.array_equal(whole.get(), parts.get())
+    assert len(np.unique(whole.get()[:4096])) > 100
