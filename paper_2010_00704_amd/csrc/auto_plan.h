@@ -1,10 +1,6 @@
 // Where AUTO leaves the direct matrix-core kernel out: launches of few packed words per output that their output binds.
 // Plain C++ on purpose: the entry points use these rules, and a host-only test checks measured calls.
 // (`outputs` = pixels x output channels; times in us)
-// Modules and tails whose rows are no whole 16-byte vectors (a channel count that is no multiple of four) take the direct kernel
-// without asking since it reads and writes such rows by unaligned vectors (vector ALUs and direct): float, 3x3, 64 -> 717, 30 maps of
-// 56 x 56 267 and 157; 1x1, 64 -> 511 without identity, 240 maps 684 and 426; 64 -> 65 without the stream, 120 maps 47.5 and 40.2; tails,
-// 32 x 8 -> 451, 60 maps, float 302 and 247, half 314 and 205.  What the rules below say of them is of accesses by single elements.
 #pragma once
 #include <stdint.h>
 
@@ -28,26 +24,24 @@ inline bool direct_behind_on_bits(int ks, int cw, int c_out, int64_t outputs)
 //   - without the stream or the bits out, 1x1 of up to two words: 64 -> 64 channels, 256 maps of 56 x 56 without the stream 44
 //     and 50; 15 -> 64, 122 maps of 28 x 28 without the bits 13.3 and 16.0; 64 -> 320, 3000 pixels of it level;
 //   - without identity, 1x1 of up to eight words, from 80 million outputs on: 64 -> 512, 240 maps of 56 x 56 345 and 443; 128 ->
-//     512, 120 maps 181 and 222; 64 -> 256, 64 maps (51 million) 1.14 times ahead;
-//   - rows that are no whole 16-byte vectors: up to three words there, and 3x3 of so many: 64 -> 717, 30 maps of 56 x 56 254 and
-//     279; 96 -> 717 without the stream, 1x1, 89 and 104; 64 -> 226 level.
+//     512, 120 maps 181 and 222; 64 -> 256, 64 maps (51 million) 1.14 times ahead.
+// Not where the rows are no whole 16-byte vectors, which the direct kernel reads and writes by unaligned vectors: 3x3, 64 -> 717, 30 maps of 56 x 56
+// 267 and 157; 1x1, 64 -> 511 without identity, 240 maps 684 and 426; 64 -> 65 without the stream, 120 maps 47.5 and 40.2.
 inline bool direct_behind_on_float_module(int ks, int cw, int c_out, bool has_id, bool has_r, bool has_x, int64_t outputs)
 {
-    const int few = c_out % 4 == 0 ? 2 : 3;
-    if (ks == 1 && cw <= few && !(has_r && has_x)) return outputs >= (cw <= 2 ? 4000000 : 50000000);
-    if (ks == 1 && cw <= 8 && !has_id && has_r) return outputs >= 80000000;
-    return ks == 3 && cw <= few && c_out % 4 != 0 && has_id && outputs >= 50000000;
+    if (ks != 1 || c_out % 4 != 0) return false;
+    if (cw <= 2 && !(has_r && has_x)) return outputs >= 4000000;
+    return cw <= 8 && !has_id && has_r && outputs >= 80000000;
 }
 
 // Branch sums that go on into a module's tail, `words` = branches x words per pixel: the same as for modules, and the vector ALUs
 // walk all branches at once.  Streams that fit the last-level cache are ahead on the direct kernel (vector ALUs and direct):
-// float, 128 channels x 2 -> 448, 120 maps of 56 x 56 266 and 317, 60 maps of 28 x 28 level; 320 x 2 1.2 times ahead; rows that
-// are no whole 16-byte vectors, 32 x 8 -> 451, 60 maps of 56 x 56 280 and 375, 3x3, 32 -> 717 448 and 572, 200 x 8 -> 717 1.1 times
-// ahead; half, 64 x 2 -> 451 0.95 times, 32 -> 448 0.90, 64 x 4 -> 448 1.1.
+// float, 128 channels x 2 -> 448, 120 maps of 56 x 56 266 and 317, 60 maps of 28 x 28 level; 320 x 2 1.2 times ahead; half, 32 -> 448 0.90
+// times, 64 x 4 -> 448 1.1.  Rows that are no whole 16-byte vectors are ahead there too: 32 x 8 -> 451, 60 maps of 56 x 56, float 302 and 247,
+// half 314 and 205.
 inline bool direct_behind_on_branch_tail(int cw, int words, int c_out, bool half, int64_t outputs)
 {
-    if (cw % 8 == 0 && c_out % 4 == 0) return false;         // (not measured against the vector ALUs)
-    if (c_out % 4 != 0) return outputs >= 40000000 && words <= (half ? 8 : 32);
+    if (cw % 8 == 0 || c_out % 4 != 0) return false;         // (whole units of eight words: not measured against the vector ALUs)
     return half ? outputs >= 80000000 && words <= 2 : outputs >= 40000000 && words <= 8;
 }
 

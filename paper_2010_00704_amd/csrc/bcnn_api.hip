@@ -245,7 +245,7 @@ static int branches_entry(const bcnn_conv_desc* desc, int32_t branches, const ui
                 break;
             }
             if (bcnn::conv_branches_direct_supported(s, a) &&
-                !(tail && s.c_out % 4 == 0 && bcnn::direct_behind_on_branch_tail(s.cw, s.cw * branches, s.c_out, tail->half, (int64_t)s.m * s.c_out))) {
+                !(tail && bcnn::direct_behind_on_branch_tail(s.cw, s.cw * branches, s.c_out, tail->half, (int64_t)s.m * s.c_out))) {
                 const bcnn::BranchChoice choice = bcnn::branches_choose(s.m, s.c_out, s.cw, branches, tail != nullptr, tail && tail->half);
                 e = choice.form == bcnn::BRANCH_SHARED ? bcnn::launch_conv_branches_shared(s, a, choice.tile, st)
                                                        : bcnn::launch_conv_branches_direct(s, a, choice.tile, st);
@@ -375,7 +375,7 @@ int bcnn_conv2d_binary_module(const bcnn_conv_desc* desc, const uint32_t* x_pack
             }
             const bool plain = mfma_ok && s.c_out % 128 == 0 && m.identity && m.r && m.x_next && m.id_channels % 4 == 0;
             const bool direct = bcnn::conv_mfma_direct_supported(s) &&
-                !(m.half == bcnn::REAL_F32 && s.c_out % 4 == 0 && bcnn::direct_behind_on_float_module(s.ks, s.cw, s.c_out, m.identity, m.r, m.x_next, (int64_t)s.m * s.c_out));
+                !(m.half == bcnn::REAL_F32 && bcnn::direct_behind_on_float_module(s.ks, s.cw, s.c_out, m.identity, m.r, m.x_next, (int64_t)s.m * s.c_out));
             const bcnn::DirectChoice choice = direct ? bcnn::conv_mfma_direct_choose(s, plain ? bcnn::KIND_MODULE_PLAIN : bcnn::KIND_MODULE_GENERAL, mfma_ok) : bcnn::DirectChoice{bcnn::DIRECT_NONE, 0.0};
             const int shared = direct ? bcnn::conv_mfma_shared_choose(s, m.half ? bcnn::SHARED_HALF : bcnn::SHARED_FLOAT, choice) : bcnn::SHARED_NONE;
             if (shared != bcnn::SHARED_NONE)
