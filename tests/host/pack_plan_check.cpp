@@ -4,7 +4,8 @@
 //   - tiles cover the row, groups the channels,
 //   - the launch stays below 2^32 threads, whatever the number of images (up to 2^31 - 1 output words);
 // that neither this plan nor that of the kernel through LDS takes an image beyond the kernels' 32-bit arithmetic; and that measured calls go to the kernel that is faster on them.
-// Prints "mismatches: N"; exit status 0 = none.
+// Prints "mismatches: N"; exit status 0 = none.  With an argument and lines "element bytes, address, outer, channels, source channels, inner" on
+// stdin: the vectors of a row in the kernel through LDS (0: another kernel's call) and whether its loads pass the caches' lines by.
 #include "pack_plan.h"
 
 #include <cstdio>
@@ -54,8 +55,15 @@ static long check_addresses(int esz, int64_t outer, int64_t channels, int64_t in
     return fits ? 0 : 1;
 }
 
-int main()
+int main(int argc, char**)
 {
+    if (argc > 1) {
+        int esz;
+        long long src, outer, channels, source, inner;
+        while (scanf("%d %lld %lld %lld %lld %lld", &esz, &src, &outer, &channels, &source, &inner) == 6)
+            printf("%d %d\n", staged_vectors(esz, (uintptr_t)src, outer, channels, source, inner), (int)staged_streams(esz, inner * esz, outer * source * inner * esz));
+        return 0;
+    }
     long bad = 0, taken = 0, staged = 0;
     for (int esz : {1, 2, 4})
         for (int64_t channels : {33ll, 64ll, 1000ll, 1ll << 20, (1ll << 24) - 64, 1ll << 24, 272696320ll, 275000000ll, 1ll << 28, (1ll << 31) - 64, 1ll << 31, 1ll << 32, 1ll << 33})
@@ -101,6 +109,16 @@ int main()
     };
     for (const auto& r : pools)
         if (pool_by_eight(r.s, r.channels, r.m) != r.eight) { printf("pool: %d %lld %lld\n", r.s, (long long)r.channels, (long long)r.m); ++bad; }
+    const struct { int64_t outer, channels, source; bool eight; } rows[] = {
+        {1, 9, 9, false}, {2, 130, 65, false}, {8, 9, 9, true}, {8, 33, 33, true}, {8, 21, 7, false}, {3000, 301, 301, true}, {40000, 2048, 2048, true}, {8, 2049, 2049, false},
+    };
+    for (const auto& r : rows)
+        if (ragged8_applies(r.outer, r.channels, r.source) != r.eight) { printf("rows: %lld %lld\n", (long long)r.outer, (long long)r.channels); ++bad; }
+    const struct { int s; int64_t channels, m; bool four; } ragged[] = {
+        {2, 99, 49, true}, {2, 3, 100000, false}, {4, 5, 1, true}, {1, 99, 784, false}, {1, 99, 62720, true}, {8, 99, 980, false}, {8, 99, 9800, true}, {1, 3, 1 << 20, false},
+    };
+    for (const auto& r : ragged)
+        if (pool_ragged_by_four(r.s, r.channels, r.m) != r.four) { printf("ragged pool: %d %lld %lld\n", r.s, (long long)r.channels, (long long)r.m); ++bad; }
     printf("plans: %ld\nmismatches: %ld\n", taken, bad);
     return bad ? 1 : 0;
 }

@@ -14,9 +14,23 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [
     # outer, source channels, inner, replication (channels in all: replication times as many)
-    (2048, 64, 5, 1), (1025, 128, 9, 1), (1025, 66, 9, 1), (2049, 36, 16, 1), (700, 160, 17, 1), (1024, 65, 25, 1), (690, 64, 28, 3),
-    (520, 192, 33, 1), (512, 256, 49, 1), (515, 252, 49, 1), (345, 128, 49, 3), (683, 130, 52, 1), (1024, 96, 56, 1), (512, 252, 63, 1), (2051, 60, 64, 1),
+    (2048, 64, 5, 1), (1025, 128, 9, 1), (1025, 66, 9, 1), (2049, 36, 16, 1), (700, 160, 17, 1), (1024, 65, 25, 1), (1024, 68, 25, 1), (690, 64, 28, 3),
+    (690, 192, 33, 1), (2050, 64, 30, 1), (700, 192, 23, 1), (690, 190, 44, 1), (512, 256, 49, 1), (515, 252, 49, 1), (345, 128, 49, 3), (683, 130, 52, 1), (1024, 96, 56, 1), (512, 252, 63, 1), (2051, 60, 64, 1),
 ]
+
+
+def offset(n):
+    """Where in its allocation a source starts: sources are at 4-byte alignment."""
+    return 4 if n % 2 else 0
+
+
+def element_size(dtype):
+    return torch.empty(0, dtype=dtype).element_size()
+
+
+def images(size, c, inner):
+    """An even number of them, a little more than 300 MB."""
+    return (300 << 20) // (c * inner * size) // 2 * 2
 
 
 @pytest.mark.parametrize("kind", [False, True, "bf16", "i8"], ids=["f32", "f16", "bf16", "i8"])
@@ -34,7 +48,7 @@ def test_pack_planes_through_lds(shape, kind):
         stored = real_store(v, kind)
         v32, code = real_values(stored, kind).reshape(n, c, inner), real_code(kind)
     raw = np.ascontiguousarray(stored).view(np.uint8).reshape(-1)
-    off = 4 if n % 2 else 0
+    off = offset(n)
     buf = torch.zeros(raw.size + 16, dtype=torch.uint8, device=dev)
     buf[off:off + raw.size] = torch.from_numpy(raw.copy()).to(dev)
     cr = rep * c
@@ -60,8 +74,7 @@ def test_pack_planes_beyond_the_cache(dtype, c, inner):
     """Sources of more than 288 MB are loaded past the caches' lines; their parts, each below that, are not."""
     dev = gpu_device()
     code = {torch.float32: B.BCNN_F32, torch.float16: B.BCNN_F16, torch.bfloat16: B.BCNN_BF16, torch.int8: B.BCNN_I8}[dtype]
-    size = torch.empty(0, dtype=dtype).element_size()
-    n = (300 << 20) // (c * inner * size) // 2 * 2
+    n = images(element_size(dtype), c, inner)
     g = torch.Generator(device=dev)
     g.manual_seed(c + inner)
     x = torch.randint(-100, 101, (n, c, inner), generator=g, device=dev, dtype=torch.int8).to(dtype)
