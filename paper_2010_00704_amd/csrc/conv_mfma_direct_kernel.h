@@ -857,7 +857,7 @@ __global__ __launch_bounds__(64 * WC * WP * WK, (WIDE > 0 && MODE < BRANCH && OU
     int id0 = 0, turn = 0;
     bool id_walk = false;
     if constexpr (MODULE) {
-        if (!vec) {                                          // (computed again: no register is kept through the K loop)
+        if (!vec && ep.identity) {                           // (computed again: no register is kept through the K loop)
             int c = c0;
             asm volatile("" : "+v"(c));
             id0 = first_id(c);
