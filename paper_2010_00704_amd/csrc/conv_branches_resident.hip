@@ -6,10 +6,13 @@
 // channel block and its sums start from an inline zero.  A wave has two columns of 32 pixels x two blocks of 32 channels, in turn: the
 // fold of one column's completed tap, tot = fma(scale, y_t, tot), is dealt out behind the matrix instructions of the other column, with the
 // expansion of the next input fragment: eight vector instructions behind each, pinned there by scheduling barriers.
-// Bound: the vector ALUs' issue, 8.1 instructions (8.8 with pad words) per matrix instruction of 35 cycles: 43 to 48 cycles each; and
-// the start, 4500 cycles of 35 000 (3x3, 256 -> 256, 64 maps of 28 x 28).  With the fold in one piece in front of a tap's products it was 58 cycles.
-// Measured (us, shared weights and this): that call as bits, pad words 24.4 and 19.4, -1 outside 22.8 and 17.2, float sums, pad words 23.4 and 20.3;
-// 40 maps of 27 x 27, 320 -> 200, bits, pad words 18.5 and 12.4; 1x1, three branches with tensors of their own, 256 -> 256, 64 maps of 28 x 28, bits 12.0 and 9.1.
+// Bound: the vector ALUs' issue, 8.1 instructions (8.8 with pad words) per matrix instruction of 35 cycles: 43 to 48 cycles each;
+// the start, 4500 cycles of 35 000 (3x3, 256 -> 256, 64 maps of 28 x 28); and a wave's odd column, whose pass works on a second one of nothing: that call
+// has 24 or 25 columns a workgroup, three a wave in passes of two and one, so that 77 % of its matrix instructions are wanted.  With the fold in one piece in
+// front of a tap's products it was 58 cycles.
+// Measured (us, graph replays on one card, shared weights and this): that call as bits, pad words 22.6 and 17.4, -1 outside 21.2 and 16.8, float sums, pad words
+// 23.6 and 20.5 (inputs from memory 22.9 and 22.0); 40 maps of 27 x 27, 320 -> 200, bits, pad words 18.5 and 12.7; 1x1, three branches with tensors of
+// their own, 256 -> 256, 64 maps of 28 x 28, bits 11.0 and 8.8.
 // Not for taps that contribute nothing outside (their lane masks need registers that the interleaved fold has not), taps of two groups (the fold
 // at some of them only: forms of a column under branches spill) and module tails.
 #include "conv_mfma_resident.h"

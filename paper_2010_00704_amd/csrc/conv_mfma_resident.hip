@@ -15,8 +15,9 @@
 // for long (16.7 ns per instruction; constant operands 15.7); a launch of one or two passes by its start, 8000 cycles until
 // the first product of 27 000 (3x3, 256 -> 256, 64 maps of 28 x 28): arguments 900, places of the pixels 1700, weights' loads and expansion
 // 3700, first inputs 1500.
-// Measured (us, before and this): that call 14.8 and 12.6, 64 maps of 56 x 56 under stride 2, 256 -> 512 25.8 and 21.9, 512 maps of
-// 28 x 28, 256 -> 256 81.2 and 72.5.  Tried: 1 x 7 blocks a wave (half as many LDS reads, twice the expansion: 13.3, 24.3 and 79.7), 128
+// Measured (us, graph replays on one card, the staged kernel before and this): that call 14.1 and 13.5, 64 maps of 56 x 56 under stride 2, 256 -> 512
+// 27.3 and 23.5, 512 maps of 28 x 28, 256 -> 256 82.7 and 76.3; inputs from memory 13.9 and 13.4, 28.8 and 24.7, 83.7 and 79.5.  Tried, where this one took
+// 12.6, 21.9 and 72.5 in kernel times: 1 x 7 blocks a wave (half as many LDS reads, twice the expansion: 13.3, 24.3 and 79.7), 128
 // channels a workgroup (twice the weights to expand at the start: 13.9 on the first), the first inputs asked for in front of the expansion
 // (its loads then wait for them, loads complete in order: 13.4), the start's code unrolled (instructions come from
 // memory once per launch: 1500 more of them cost 1 us), the expansion spread over the first pass's K loop (15.7: a barrier per round).

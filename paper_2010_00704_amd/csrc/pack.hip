@@ -327,9 +327,9 @@ __global__ __launch_bounds__(256) void pack_ballot_kernel(
 // The same for rows of at most 64 positions, which 64 channels hold in one piece of memory: the wave loads it lane by lane, 16 bytes
 // next to 16 bytes, and turns it around in LDS of its own, so that no load touches 64 cache lines (each a cycle of the CU's address
 // unit, eight times over for rows of 98 bytes).
-// Memory bound where the launch is long enough.  us, calls in a row on buffers beyond the last-level cache, against the kernels that ran these calls before: bfloat16 with bias,
-// 1024 channels, 256 maps of 7 x 7 8.7 -> 7.5 (3.5 TB/s); half, 64 channels, 11 196 of 3 x 3 8.1 -> 4.7; float, 300 channels, 800 of
-// 6 x 7 18.4 -> 10.8 (3.7 TB/s), 1024 channels, 128 of 7 x 7 9.2 -> 7.0, 1024 x 1024 x 3 x 3 weights 9.1 -> 8.8 (4.3 TB/s).
+// Memory bound where the launch is long enough.  us, calls in a row on buffers beyond the last-level cache, graph replays, against the kernels that ran these calls
+// before: bfloat16 with bias, 1024 channels, 256 maps of 7 x 7 9.4 -> 8.4 (3.1 TB/s); half, 64 channels, 11 196 of 3 x 3 8.7 -> 5.2; float, 300 channels, 800 of
+// 6 x 7 18.2 -> 10.4 (3.9 TB/s), 1024 channels, 128 of 7 x 7 9.4 -> 6.9, 1024 x 1024 x 3 x 3 weights 9.4 -> 9.1 (4.1 TB/s).
 // Rows of whole vectors are read back as vectors, with a vector of padding in 256 bytes (VEC: 16 lanes reach all banks); others by
 // dwords, whose odd or half strides share a bank between two lanes at most.  NV: vectors a row, rounded up.
 // NT: loads that leave no lines behind (staged_streams).

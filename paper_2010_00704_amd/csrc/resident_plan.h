@@ -74,9 +74,10 @@ inline bool resident_takes(int m, int c_out, int cw, int ks)
 // 0.94 to 1.16 times, of four and five 0.86 to 1.17).  Not float sums of branches that have tensors of their own: two taps ahead is not early enough for
 // loads from memory that the stores delay.  Their inputs in the last-level cache 1.03 times on average over 104 calls, from memory 1.14 over 96, 1.49 at
 // worst (492 maps of 24 x 24, four taps, 160 -> 192 45 and 66; 3x3, 37 maps of 40 x 40, 192 -> 512 42 and 59); bits of such calls 0.83, from memory too.
-// Over 662 calls of 400 tiles and more (us, shared weights and this, on average): bits of nine taps 0.91 times at 400 to
-// 800 tiles, 0.77 from 2048 on, of two taps 0.99 and 0.70 to 0.80, sums of nine taps 0.93 and 0.87; of the calls that the rule takes four are more than
-// 3 % behind, 5 % at worst.  Half-empty channel tiles are no worse here (38 calls 0.89, one 10 % behind).
+// Over 393 calls that the rule takes (time on shared weights and here, inputs from the last-level cache): bits 0.82 on average, of nine taps 0.88 at 400 to
+// 800 tiles and 0.79 from 2048 on, of two taps 0.77, of one 0.90, two of 236 more than 3 % behind, 10 % at worst (three taps, 161 -> 76, 24 maps of 30 x 30 4.4
+// and 4.8); sums 0.89, two of 157 behind, 4 % at worst.  Over 109 with inputs from memory: bits 0.81, none behind; sums 0.95, eleven of 81
+// behind, 14 % at worst (seven taps, 192 -> 128, 10 maps of 47 x 47 6.8 and 7.8).
 // Workgroups that keep 70 % of the compute units busy: over 90 calls of 1025 to 20 000 channels out, 0.93 of the time at 70 to 80 %, 1.05 at 60 to
 // 70 %, 1.2 below (bits, 41 maps of 21 x 21, three taps, 192 -> 9172 89 and 120; sums, 4 maps of 28 x 28, nine taps, 218 -> 17 775 105 and 129).
 // (an even number of taps of five words a load has no registers left)
